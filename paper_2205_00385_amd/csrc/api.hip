@@ -165,7 +165,10 @@ struct aarmr_mesh {
   double *r = nullptr, *z = nullptr, *pv = nullptr, *q = nullptr, *t0 = nullptr, *fm = nullptr;
   LevelBuf lv[AARMR_MAX_LEVELS];
   double* Ainv = nullptr;
-  double *gjP = nullptr, *gjT = nullptr, *gjC = nullptr, *gjTb = nullptr;
+  InvPlan plan;               // elimination of the coarsest operator
+  CoarseOrder corder;         // the order of its unknowns
+  InvTask* tasksd = nullptr;  // the plan on the device
+  double* inv_work = nullptr; // pivot inverses and panels of two steps
   double* Phi = nullptr;   // [n_rhs_max][Ns][3nn]
   double* R = nullptr;     // [Nm][3nn]
   double* KR = nullptr;    // [Nm][3nn]
@@ -532,10 +535,8 @@ int64_t layout(aarmr_mesh* m, char* base) {
     m->act = (int*)take(R * 4);
   }
   m->Ainv = (double*)take((int64_t)m->nc * m->nc * d8);
-  m->gjP = (double*)take(2 * kGJBlock * kGJBlock * d8);  // two pivot inverses
-  m->gjT = (double*)take((int64_t)m->nc * kGJBlock * d8);
-  m->gjC = (double*)take((int64_t)m->nc * kGJBlock * d8);
-  m->gjTb = (double*)take((int64_t)m->nc * kGJBlock * d8);
+  m->tasksd = (InvTask*)take((int64_t)m->plan.tasks.size() * sizeof(InvTask));
+  m->inv_work = (double*)take(inv_scratch_doubles(m->plan) * d8);
   m->Phi = (double*)take((int64_t)m->p.n_rhs_max * m->p.Ns * n3 * d8);
   m->R = (double*)take((int64_t)m->p.Nm * n3 * d8);
   m->KR = (double*)take((int64_t)m->p.Nm * n3 * d8);
@@ -749,6 +750,7 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
   const double om = m->p.omega;
   const bool fuse = m->dim == 3;
   const bool child_first = fuse && m->p.nu_pre >= 1 && l + 1 < m->nlev - 1;
+  const CoarseOrder* co = l + 1 == m->nlev - 1 ? &m->corder : nullptr;
   if (m->p.nu_pre >= 1) {
     if (!x_init) {
       launch_jacobi_first(n3, b, L.dinv, om, x, s);  // line 1, first sweep from zero
@@ -763,15 +765,15 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
     if (child_first)
       launch_restrict_jacobi(m->lg[l + 1], b, L.t, mask, C.b, C.dinv, om, C.x, s);
     else
-      launch_restrict(m->lg[l + 1], b, L.t, mask, C.b, s, m->dim);
+      launch_restrict(m->lg[l + 1], b, L.t, mask, C.b, s, m->dim, co);
   } else {
     HIP_TRY(hipMemsetAsync(x, 0, n3 * sizeof(double), s));
     HIP_TRY(hipMemsetAsync(L.t, 0, n3 * sizeof(double), s));
-    launch_restrict(m->lg[l + 1], b, L.t, mask, C.b, s, m->dim);
+    launch_restrict(m->lg[l + 1], b, L.t, mask, C.b, s, m->dim, co);
   }
   KCHECK();
   TRY(vcycle(m, l + 1, C.b, C.x, s, child_first));  // line 3
-  launch_prolong_add(G, C.x, mask, x, s, m->dim);    // line 4
+  launch_prolong_add(G, C.x, mask, x, s, m->dim, co);  // line 4
   KCHECK();
   for (int it = 0; it < m->p.nu_post; ++it) {        // line 5
     if (fuse && l == 0 && x == m->z && it == m->p.nu_post - 1) {
@@ -808,15 +810,15 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
 }
 
 // Algorithm 2's coarsest solve: the dense inverse of the coarsest Galerkin
-// operator, by Gauss-Jordan.
+// operator, its unknowns in the plan's order.
 int invert_coarsest(aarmr_mesh* m, hipStream_t s) {
   const Grid& G = m->lg[m->nlev - 1];
   if (m->dim == 2)
-    launch_q4_assemble_dense(G, m->lv[m->nlev - 1].Ke, m->Ainv, s);
+    launch_q4_assemble_dense(G, m->corder, m->lv[m->nlev - 1].Ke, m->Ainv, s);
   else
-    launch_assemble_dense(G, m->lv[m->nlev - 1].Ke, m->Ainv, s);
+    launch_assemble_dense(G, m->corder, m->lv[m->nlev - 1].Ke, m->Ainv, s);
   KCHECK();
-  launch_gj_invert(m->nc, m->Ainv, m->gjP, m->gjT, m->gjC, m->gjTb, s);
+  launch_invert(m->plan, m->tasksd, m->Ainv, m->inv_work, s);
   KCHECK();
   HIP_TRY(hipMemcpyAsync(m->mask_prev, m->mask, (m->lg[0].nn + 3) / 4 * 4,
                          hipMemcpyDeviceToDevice, s));
@@ -981,6 +983,7 @@ int vcycle32(aarmr_mesh* m, int l, const float* b, float* x, hipStream_t s,
   const uint8_t* mask = (l == 0) ? m->mask : nullptr;
   const float om = (float)m->p.omega;
   const bool child_first = m->p.nu_pre >= 1 && l + 1 < m->nlev - 1;
+  const CoarseOrder* co = l + 1 == m->nlev - 1 ? &m->corder : nullptr;
   if (m->p.nu_pre >= 1) {
     if (!x_init) {
       launch_jacobi_first_f32(n3, b, L.dinv32, om, x, s, nr);
@@ -996,14 +999,14 @@ int vcycle32(aarmr_mesh* m, int l, const float* b, float* x, hipStream_t s,
       launch_restrict_jacobi_f32(m->lg[l + 1], b, L.t32, mask, C.b32, C.dinv32, om, C.x32, s,
                                  nr);
     else
-      launch_restrict_f32(m->lg[l + 1], b, L.t32, mask, C.b32, s, nr);
+      launch_restrict_f32(m->lg[l + 1], b, L.t32, mask, C.b32, s, nr, co);
   } else {
     HIP_TRY(hipMemsetAsync(x, 0, nr * n3 * sizeof(float), s));
-    launch_restrict_f32(m->lg[l + 1], b, nullptr, mask, C.b32, s, nr);
+    launch_restrict_f32(m->lg[l + 1], b, nullptr, mask, C.b32, s, nr, co);
   }
   KCHECK();
   TRY(vcycle32(m, l + 1, C.b32, C.x32, s, child_first, nr));
-  launch_prolong_add_f32(G, C.x32, mask, x, s, nr);
+  launch_prolong_add_f32(G, C.x32, mask, x, s, nr, co);
   KCHECK();
   for (int it = 0; it < m->p.nu_post; ++it) {
     const bool last = it == m->p.nu_post - 1;
@@ -1733,6 +1736,12 @@ int aarmr_mesh_create(const aarmr_params* p, aarmr_mesh** out) {
     delete m;
     return fail(AARMR_E_INVALID, "coarsest grid above 8192 DOFs: use more levels");
   }
+  {
+    const Grid& G = m->lg[m->nlev - 1];
+    int plane = 0;
+    m->corder = make_coarse_order(G.nx + 1, G.ny + 1, G.nz + 1, dim, &plane);
+    m->plan = make_inv_plan(m->nc, plane);
+  }
   if (dim == 2) {
     q4_stiffness(p->nu, m->KE);  // unit modulus and thickness
     *out = m;
@@ -1813,6 +1822,8 @@ int aarmr_bind_workspace(aarmr_mesh* m, void* dev_ptr, int64_t bytes, void* stre
                            hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(m->Bwd, m->Bw, 576 * sizeof(double), hipMemcpyHostToDevice, s));
   }
+  HIP_TRY(hipMemcpyAsync(m->tasksd, m->plan.tasks.data(), m->plan.tasks.size() * sizeof(InvTask),
+                         hipMemcpyHostToDevice, s));
   if (m->fp32) {
     HIP_TRY(hipMemcpyAsync(m->Bw32d, m->Bw32, 576 * sizeof(float), hipMemcpyHostToDevice, s));
   }

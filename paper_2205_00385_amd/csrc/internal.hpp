@@ -11,6 +11,7 @@
 #include <string>
 
 #include "aarmr.h"
+#include "inv_plan.hpp"
 #include "walsh.hpp"
 
 namespace aarmr {
@@ -19,7 +20,6 @@ constexpr int kRedBlocks = 512;    // partial-sum blocks of one reduction
 constexpr int kFusedBlocks = 2048; // block limit of the CG updates with folded reductions
 constexpr int kRedSlots = 24;      // dot products one reduction launch can hold
 constexpr int kMaxIt = 4096;       // bound of cg_maxit (scalar history length)
-constexpr int kGJBlock = 64;       // block size of the coarsest inversion
 
 // nz == 0 is the plane-stress grid: nx * ny unit squares, (nx+1)(ny+1)
 // nodes with 2 DOFs each.
@@ -173,10 +173,12 @@ void launch_apply_l1_f32(const Grid& g, const double* Ke, const double* Kcomp, i
 void launch_diag_elemmat(const Grid& g, const double* Ke, double* dinv, float* dinv32,
                          hipStream_t s);
 // Transfers act per component; ncomp = 2 on the plane-stress grid (nz = 0).
+// o: the coarse vector's order (null: [component][node]), set where the coarse
+// level is the coarsest.
 void launch_restrict(const Grid& coarse, const double* bf, const double* tf, const uint8_t* mask,
-                     double* bc, hipStream_t s, int ncomp = 3);
+                     double* bc, hipStream_t s, int ncomp = 3, const CoarseOrder* o = nullptr);
 void launch_prolong_add(const Grid& fine, const double* xc, const uint8_t* mask, double* xf,
-                        hipStream_t s, int ncomp = 3);
+                        hipStream_t s, int ncomp = 3, const CoarseOrder* o = nullptr);
 void launch_jacobi_first(int64_t n3, const double* b, const double* dinv, double omega, double* x,
                          hipStream_t s);
 // Fused damped-Jacobi sweeps (3D hierarchy): restriction that also forms the
@@ -194,21 +196,24 @@ void launch_apply_elemmat_jacobi(const Grid& g, const double* Ke, const double* 
                                  const double* dinv, double omega, double* out, hipStream_t s);
 void launch_jacobi_update(int64_t n3, const double* b, const double* t, const double* dinv,
                           double omega, double* x, hipStream_t s);
-void launch_assemble_dense(const Grid& g, const double* Ke, double* A, hipStream_t s);
-// In-place inverse of the SPD n x n matrix A (blocked symmetric Gauss-Jordan).
-// Scratch: P holds two 64 x 64 pivot inverses, T, C and Tb one 64 x n panel
-// each.
-void launch_gj_invert(int n, double* A, double* P, double* T, double* C, double* Tb,
-                      hipStream_t s);
+// The dense coarsest operator with its unknowns in the order o, and its
+// inverse in place (A SPD) by the plan's steps.  tasks: the plan's, in device
+// memory; scratch: inv_scratch_doubles(plan) doubles.
+void launch_assemble_dense(const Grid& g, const CoarseOrder& o, const double* Ke, double* A,
+                           hipStream_t s);
+int64_t inv_scratch_doubles(const InvPlan& plan);
+void launch_invert(const InvPlan& plan, const InvTask* tasks, double* A, double* scratch,
+                   hipStream_t s);
 void launch_gemv(int n, const double* A, const double* x, double* y, hipStream_t s);
 // FP32 V-cycle pieces (vectors FP32; element matrices and the coarsest
 // inverse stay FP64 and are applied with FP32 vectors).
 void launch_apply_elemmat_f32(const Grid& g, const float* Ke, const float* v, float* y,
                               hipStream_t s, int nr = 1);
 void launch_restrict_f32(const Grid& coarse, const float* bf, const float* tf,
-                         const uint8_t* mask, float* bc, hipStream_t s, int nr = 1);
+                         const uint8_t* mask, float* bc, hipStream_t s, int nr = 1,
+                         const CoarseOrder* o = nullptr);
 void launch_prolong_add_f32(const Grid& fine, const float* xc, const uint8_t* mask, float* xf,
-                            hipStream_t s, int nr = 1);
+                            hipStream_t s, int nr = 1, const CoarseOrder* o = nullptr);
 void launch_jacobi_first_f32(int64_t n3, const float* b, const float* dinv, float omega, float* x,
                              hipStream_t s, int nr = 1);
 void launch_jacobi_update_f32(int64_t n3, const float* b, const float* t, const float* dinv,
@@ -320,7 +325,8 @@ void launch_q4_galerkin_from_coarse(const Grid& coarse, const double* Kf, double
 void launch_q4_apply_elemmat(const Grid& g, const double* Ke, const double* v, double* y,
                              hipStream_t s);
 void launch_q4_diag_elemmat(const Grid& g, const double* Ke, double* dinv, hipStream_t s);
-void launch_q4_assemble_dense(const Grid& g, const double* Ke, double* A, hipStream_t s);
+void launch_q4_assemble_dense(const Grid& g, const CoarseOrder& o, const double* Ke, double* A,
+                              hipStream_t s);
 
 // ---- filter, OC --------------------------------------------------------------
 // Cone weights max(0, r - |d|) of the filter offsets, (2R+1)^3 with

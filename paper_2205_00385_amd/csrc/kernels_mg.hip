@@ -1,8 +1,8 @@
 // Multigrid kernels of the V-cycle (Algorithm 2): Galerkin coarse operators
 // P^T A P stored as one packed symmetric 24x24 matrix per coarse element, their products and
 // diagonals, restriction P^T and interpolation P (trilinear, 2:1 per axis),
-// damped-Jacobi smoothing, and the exact coarsest solve through an explicit
-// inverse computed by blocked Gauss-Jordan elimination.
+// damped-Jacobi smoothing, and the coarsest solve's product with the explicit
+// inverse (kernels_inv.hip).
 #include <algorithm>
 
 #include "internal.hpp"
@@ -819,7 +819,7 @@ __global__ void k_diag_elemmat(int nx, int ny, int nz, const double* __restrict_
 // plane grid (cnz = 0) only the middle offset lies in the grid.
 // mask == nullptr: no fine fixed DOFs.
 // With xc non-null also the coarse level's first Jacobi sweep from zero,
-// xc = omega dc bc.
+// xc = omega dc bc.  o: the order of the coarse vector.
 template <typename T>
 __global__ void __launch_bounds__(192) k_restrict(int cnx, int cny, int cnz,
                                                   const T* __restrict__ bf,
@@ -827,8 +827,8 @@ __global__ void __launch_bounds__(192) k_restrict(int cnx, int cny, int cnz,
                                                   const uint8_t* __restrict__ mask,
                                                   T* __restrict__ bc,
                                                   const T* __restrict__ dc, T omega,
-                                                  T* __restrict__ xc, int64_t fs = 0,
-                                                  int64_t cs = 0) {
+                                                  T* __restrict__ xc, CoarseOrder o,
+                                                  int64_t fs = 0, int64_t cs = 0) {
   __shared__ T part[3][64];
   {  // load case blockIdx.z (fs, cs: fine and coarse vector strides)
     const int64_t fo = (int64_t)blockIdx.z * fs, co = (int64_t)blockIdx.z * cs;
@@ -844,11 +844,13 @@ __global__ void __launch_bounds__(192) k_restrict(int cnx, int cny, int cnz,
   const int fnx = 2 * cnx, fny = 2 * cny, fnz = 2 * cnz;
   const int64_t fnn = (int64_t)(fnx + 1) * (fny + 1) * (fnz + 1);
   T acc = 0;
+  int dst = 0;
   if (n < cnn) {
     const int I = (int)(n % (cnx + 1));
     const int64_t rest = n / (cnx + 1);
     const int J = (int)(rest % (cny + 1));
     const int K = (int)(rest / (cny + 1));
+    dst = c * o.sc + I * o.si + J * o.sj + K * o.sk;
     const int fk = 2 * K + dzi - 1;
     if (fk >= 0 && fk <= fnz) {
       const T wz = dzi == 1 ? T(1) : T(0.5);
@@ -874,8 +876,8 @@ __global__ void __launch_bounds__(192) k_restrict(int cnx, int cny, int cnz,
   __syncthreads();
   if (dzi == 0 && n < cnn) {
     const T v = part[0][lane] + part[1][lane] + part[2][lane];
-    bc[c * cnn + n] = v;
-    if (xc) xc[c * cnn + n] = omega * dc[c * cnn + n] * v;
+    bc[dst] = v;
+    if (xc) xc[dst] = omega * dc[dst] * v;
   }
 }
 
@@ -1032,20 +1034,20 @@ __global__ void __launch_bounds__(64 * kRmWaves) k_restrict_zm(
 // xf += Df P xc: thread per fine node, branch-free over the (up to) 8
 // parent nodes: along an axis an even fine index takes its parent with
 // weight 1, an odd one both neighbours with weight 1/2.  On the plane grid
-// (fnz = 0) the z pair is (0, 0) with weights (1, 0) and ncomp = 2.
+// (fnz = 0) the z pair is (0, 0) with weights (1, 0) and ncomp = 2.  o: the
+// order of the coarse vector.
 template <typename T>
 __global__ void __launch_bounds__(256) k_prolong_add(int fnx, int fny, int fnz,
                                                      const T* __restrict__ xc,
                                                      const uint8_t* __restrict__ mask,
                                                      T* __restrict__ xf, int ncomp,
-                                                     int64_t cs = 0, int64_t fs = 0) {
+                                                     CoarseOrder o, int64_t cs = 0,
+                                                     int64_t fs = 0) {
   xc += (int64_t)blockIdx.z * cs;  // load case blockIdx.z
   xf += (int64_t)blockIdx.z * fs;
   const int64_t fnn = (int64_t)(fnx + 1) * (fny + 1) * (fnz + 1);
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= fnn) return;
-  const int cnx = fnx / 2, cny = fny / 2, cnz = fnz / 2;
-  const int64_t cnn = (int64_t)(cnx + 1) * (cny + 1) * (cnz + 1);
   const int fi = (int)(n % (fnx + 1));
   const int64_t rest = n / (fnx + 1);
   const int fj = (int)(rest % (fny + 1));
@@ -1056,18 +1058,18 @@ __global__ void __launch_bounds__(256) k_prolong_add(int fnx, int fny, int fnz,
   const T wx[2] = {(fi & 1) ? T(0.5) : T(1), (fi & 1) ? T(0.5) : T(0)};
   const T wy[2] = {(fj & 1) ? T(0.5) : T(1), (fj & 1) ? T(0.5) : T(0)};
   const T wz[2] = {(fk & 1) ? T(0.5) : T(1), (fk & 1) ? T(0.5) : T(0)};
-  int64_t id[8];
+  int id[8];
   T w[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    id[q] = node_of(cnx, cny, ix[q & 1], iy[(q >> 1) & 1], iz[q >> 2]);
+    id[q] = ix[q & 1] * o.si + iy[(q >> 1) & 1] * o.sj + iz[q >> 2] * o.sk;
     w[q] = wx[q & 1] * wy[(q >> 1) & 1] * wz[q >> 2];
   }
   const uint8_t m = mask ? mask[n] : 0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     if (c >= ncomp) break;
-    const T* x = xc + c * cnn;
+    const T* x = xc + c * o.sc;
     T s = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) s = fma(w[q], x[id[q]], s);
@@ -1178,503 +1180,6 @@ __global__ void k_jacobi_update(int64_t n3, const T* __restrict__ b, const T* __
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t ro = (int64_t)blockIdx.z * rs;  // load case blockIdx.z
   if (i < n3) x[ro + i] += omega * dinv[i] * (b[ro + i] - t[ro + i]);
-}
-
-// Dense coarsest operator in SoA DOF order (c * nn + node); thread per row.
-// One wavefront per row: the row is zeroed (coalesced stores), then lanes
-// take the 81 columns of the 27-node neighbourhood (3 components each); an
-// entry is the sum, over the elements around the row's node in corner order
-// a = 0..7, of the element matrices' entries coupling the two nodes.  A row
-// with zero diagonal (a coarse DOF no free fine DOF interpolates from)
-// becomes an identity row.  32-bit indices: the coarsest order is at most
-// 8192.
-__global__ void __launch_bounds__(256) k_assemble_dense(int nx, int ny, int nz,
-                                                        const double* __restrict__ Ke,
-                                                        double* __restrict__ A) {
-  const int nxp = nx + 1, nyp = ny + 1;
-  const int nn = nxp * nyp * (nz + 1), ne = nx * ny * nz, nd = 3 * nn;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const bool active = row < nd;  // wave-uniform; every wave reaches the barrier
-  double* Ar = A + (int64_t)(active ? row : 0) * nd;
-  if (active)
-    for (int t = lane; t < nd; t += 64) Ar[t] = 0.0;
-  __syncthreads();  // the zeros are stored before the same addresses are rewritten
-  if (!active) return;
-  const int c = row / nn, n = row % nn;
-  const int i = n % nxp, j = (n / nxp) % nyp, k = n / (nxp * nyp);
-  for (int l = lane; l < 81; l += 64) {
-    const int cc = l / 27, d = l % 27;
-    const int bi = i + d % 3 - 1, bj = j + (d / 3) % 3 - 1, bk = k + d / 9 - 1;
-    if (bi < 0 || bi > nx || bj < 0 || bj > ny || bk < 0 || bk > nz) continue;
-    double acc = 0.0;
-    for (int a = 0; a < 8; ++a) {
-      const int ex = i - (a & 1), ey = j - ((a >> 1) & 1), ez = k - (a >> 2);
-      if (ex < 0 || ex >= nx || ey < 0 || ey >= ny || ez < 0 || ez >= nz) continue;
-      const int dx = bi - ex, dy = bj - ey, dz = bk - ez;  // corner of the column node
-      if (dx < 0 || dx > 1 || dy < 0 || dy > 1 || dz < 0 || dz > 1) continue;
-      const int b = dx + 2 * dy + 4 * dz;
-      const int e = ex + nx * (ey + ny * ez);
-      acc += Ke[(int64_t)sidx(3 * a + c, 3 * b + cc) * ne + e];
-    }
-    const int col = cc * nn + bi + nxp * (bj + nyp * bk);
-    Ar[col] = (col == row && acc == 0.0) ? 1.0 : acc;
-  }
-}
-
-// ---- blocked Gauss-Jordan inversion of an SPD matrix (sweep operator) -----
-// One block step with pivot block K = [k0, k0+kb) maps
-//   A_KK -> P = A_KK^-1,  A_IK -> -A_IK P,  A_KJ -> P A_KJ,
-//   A_IJ -> A_IJ - A_IK P A_KJ            (I, J outside K).
-// For symmetric A the matrix stays symmetric up to sign: after the blocks
-// before k0 are done, A_ij = A_ji when i and j are both below k0 or both at
-// or above it, and A_ij = -A_ji otherwise.  Only tiles on or above the
-// diagonal are therefore kept: with c_i = A_iK (read from the stored upper
-// triangle as A_iK for i < k0, as A_Ki for i beyond K) and T_i = P c_i,
-//   A_ij -= s_j T_i . c_j  (s_j = -1 for j < k0, +1 beyond K),
-//   A_iK  = -T_i (i < k0),  A_Kj = T_j (j beyond K).
-// After the last block the stored upper triangle is A^-1 and the lower
-// triangle is filled by transposition.
-
-// 1/x from the hardware reciprocal estimate and two Newton steps.
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-
-// 16x16 FP64 MFMA tiles over LDS (row stride ld).  Operand lane layout of
-// v_mfma_f64_16x16x4f64: A[l%16][l/16], B[l/16][l%16]; accumulator element
-// v of lane l is row l/16 + 4v, column l%16.
-__device__ __forceinline__ f64x4 mma16(const double* A, int lda, const double* B, int ldb,
-                                       f64x4 acc, double sgn_a) {
-  const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const double a = sgn_a * A[li * lda + 4 * kk + lk];
-    const double b = B[(4 * kk + lk) * ldb + li];
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-__device__ __forceinline__ f64x4 ld16(const double* C, int ldc) {
-  const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
-  f64x4 x;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) x[v] = C[(lk + 4 * v) * ldc + li];
-  return x;
-}
-
-__device__ __forceinline__ void st16(double* C, int ldc, f64x4 x, double sgn) {
-  const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) C[(lk + 4 * v) * ldc + li] = sgn * x[v];
-}
-
-// Lane (16 r + k)'s value of v for every lane of the 16-lane row r (DPP
-// row_newbcast).
-template <int K>
-__device__ __forceinline__ double row_bcast(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + K, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + K, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-// One pivot step k of gj16_wave.  The pivot S[k][k] is wave-uniform (lane
-// reads), the pivot column S[4 r4 + q][k] comes from lane k of the lane's own
-// 16-lane row (row_newbcast), and the pivot row S[k][c] from lane 16 (k/4) + c.
-template <int K>
-struct Gj16Step {
-  static __device__ __forceinline__ void run(double (&x)[4], int c, int r4) {
-    constexpr int kq = K & 3, kr = K >> 2;
-    const double rk = __shfl(x[kq], kr * 16 + c, 64);  // S[k][c]
-    const int plo = __builtin_amdgcn_readlane(__double2loint(x[kq]), kr * 16 + K);
-    const int phi = __builtin_amdgcn_readlane(__double2hiint(x[kq]), kr * 16 + K);
-    const double piv = recip(__hiloint2double(phi, plo));
-    const bool pc = (c == K);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const double ck = row_bcast<K>(x[q]);  // S[4 r4 + q][k]
-      const double upd = pc ? -ck * piv : fma(-ck * piv, rk, x[q]);
-      x[q] = (4 * r4 + q == K) ? (pc ? piv : rk * piv) : upd;
-    }
-    Gj16Step<K + 1>::run(x, c, r4);
-  }
-};
-template <>
-struct Gj16Step<16> {
-  static __device__ __forceinline__ void run(double (&)[4], int, int) {}
-};
-
-// In-place Gauss-Jordan inversion of a 16x16 block of LDS (row stride ld) by
-// one wavefront in registers: lane l holds rows 4(l/16)..4(l/16)+3 of column
-// l%16.
-__device__ __forceinline__ void gj16_wave(double* S, int ld) {
-  const int l = threadIdx.x & 63, c = l & 15, r4 = l >> 4;
-  double x[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) x[q] = S[(4 * r4 + q) * ld + c];
-  Gj16Step<0>::run(x, c, r4);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) S[(4 * r4 + q) * ld + c] = x[q];
-}
-
-// In-place Gauss-Jordan inversion of the 64x64 block sS (padded with the
-// identity beyond the pivot block size) by 256 threads, in four 16-wide
-// sub-steps J over the 4 x 4 grid of 16x16 blocks: Q = S_JJ^-1 (one
-// wavefront), then for the other blocks o, o': R_o = Q S_Jo, T_o = S_oJ Q,
-// S_oo' -= S_oJ R_o', S_Jo = R_o, S_oJ = -T_o, all on FP64 MFMA.
-__device__ __forceinline__ void gj64_block(double (*sS)[kGJBlock + 1]) {
-  constexpr int ld = kGJBlock + 1;
-  const int w = threadIdx.x >> 6;
-  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
-  for (int j = 0; j < 4; ++j) {
-    const int J0 = 16 * j;
-    if (w == 0) gj16_wave(&sS[J0][J0], ld);
-    __syncthreads();
-    const int ob = 16 * (w < j ? w : w + 1);  // wave w < 3: the w-th other block
-    f64x4 T = zero, R = zero;
-    if (w < 3) {
-      T = mma16(&sS[ob][J0], ld, &sS[J0][J0], ld, zero, 1.0);
-      R = mma16(&sS[J0][J0], ld, &sS[J0][ob], ld, zero, 1.0);
-      // no barrier before this store: S_J,ob is read only by this wave
-      st16(&sS[J0][ob], ld, R, 1.0);
-    }
-    __syncthreads();
-    for (int t = w; t < 9; t += 4) {
-      const int q1 = t / 3, q2 = t % 3;
-      const int o1 = 16 * (q1 < j ? q1 : q1 + 1), o2 = 16 * (q2 < j ? q2 : q2 + 1);
-      f64x4 c = ld16(&sS[o1][o2], ld);
-      c = mma16(&sS[o1][J0], ld, &sS[J0][o2], ld, c, -1.0);
-      st16(&sS[o1][o2], ld, c, 1.0);
-    }
-    __syncthreads();
-    if (w < 3) st16(&sS[ob][J0], ld, T, -1.0);
-    __syncthreads();
-  }
-}
-
-// Workgroup 0: pivot inverse of the first block, Pb = A_00^-1 (kb x kb).
-// The others copy the first step's panel Cb[p][i] = A[p][i] (p < kb: the
-// stored first block row), 2048 entries each.
-__global__ void __launch_bounds__(256) k_gj_pivot_first(int n, int kb,
-                                                        const double* __restrict__ A,
-                                                        double* __restrict__ Pb,
-                                                        double* __restrict__ Cb) {
-  __shared__ double sS[kGJBlock][kGJBlock + 1];
-  if (blockIdx.x > 0) {
-    const int64_t base = (int64_t)(blockIdx.x - 1) * 2048, total = (int64_t)kb * n;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int64_t x = base + threadIdx.x + 256 * r;
-      if (x < total) Cb[x] = A[x];
-    }
-    return;
-  }
-  for (int x = threadIdx.x; x < kGJBlock * kGJBlock; x += 256) {
-    const int r = x / 64, c = x % 64;
-    sS[r][c] = (r < kb && c < kb) ? A[(int64_t)r * n + c] : (r == c ? 1.0 : 0.0);
-  }
-  __syncthreads();
-  gj64_block(sS);
-  for (int x = threadIdx.x; x < kb * kb; x += 256) Pb[x] = sS[x / kb][x % kb];
-}
-
-// 64x64 FP64 tile in LDS, row p, column i at p * 64 + (i ^ 8 (p & 3)).  An
-// MFMA operand read (lanes l: row 4kk + l/16, 16 consecutive columns) then
-// spreads its four 16-lane groups over both bank halves, two groups each:
-// two passes, the minimum for 64 doubles, without padding (two tiles fill
-// the 64 KB a workgroup may hold).
-__device__ __forceinline__ int swz(int p, int i) { return p * 64 + (i ^ ((p & 3) << 3)); }
-
-// The cross part of a block step for large orders, one workgroup per block
-// row O: A_KK = Pc for O = K; otherwise T_O = c_O Pc into Tb[q][O0 + i], the
-// new cross entries A_OK = -T_O (O < K) or A_KO = T_O (O > K), and for
-// O = K+1 the next panel's rows of K.  k_gj_step<true> then forms the tiles.
-__global__ void __launch_bounds__(256) k_gj_cross(int n, int k0, int kb, double* __restrict__ A,
-                                                  const double* __restrict__ Pc,
-                                                  const double* __restrict__ Cc,
-                                                  double* __restrict__ Cn,
-                                                  double* __restrict__ Tb) {
-  __shared__ double sm[2 * kGJBlock * kGJBlock];
-  double* sP = sm;
-  double* sX = sm + kGJBlock * kGJBlock;
-  const int K = k0 / kGJBlock, O = blockIdx.x;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int li = lane & 15, lk = lane >> 4;
-  if (O == K) {
-    for (int x = tid; x < kb * kb; x += 256)
-      A[(int64_t)(k0 + x / kb) * n + k0 + x % kb] = Pc[x];
-    return;
-  }
-  const int O0 = O * kGJBlock;
-  const int orows = (n - O0 < kGJBlock) ? (n - O0) : kGJBlock;
-  double pv[16], xv[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int x = tid + 256 * r, a = x >> 6, b = x & 63;
-    pv[r] = (a < kb && b < kb) ? Pc[a * kb + b] : 0.0;
-    xv[r] = (a < kb && b < orows) ? Cc[(int64_t)a * n + O0 + b] : 0.0;
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int x = tid + 256 * r, a = x >> 6, b = x & 63;
-    sP[swz(a, b)] = pv[r];
-    sX[swz(a, b)] = xv[r];
-  }
-  __syncthreads();
-  f64x4 tacc[4];
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb) tacc[jb] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kk = 0; kk < 16; ++kk) {
-    const int p = 4 * kk + lk;
-    const double a = sX[swz(p, 16 * w + li)];
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-      tacc[jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sP[swz(p, 16 * jb + li)], tacc[jb], 0, 0, 0);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sX[swz(16 * jb + li, 16 * w + lk + 4 * v)] = tacc[jb][v];
-  if (O < K) {
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = 16 * w + lk + 4 * v, q = 16 * jb + li;
-        if (i < orows && q < kb) A[(int64_t)(O0 + i) * n + k0 + q] = -tacc[jb][v];
-      }
-  } else if (O == K + 1) {
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = 16 * w + lk + 4 * v, q = 16 * jb + li;
-        if (i < orows && q < kb) Cn[(int64_t)i * n + k0 + q] = tacc[jb][v];
-      }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {  // Tb[q][O0 + i] and, beyond K, A[k0 + q][O0 + i]
-    const int x = tid + 256 * r, q = x >> 6, i = x & 63;
-    if (q < kb && i < orows) {
-      const double t = sX[swz(q, i)];
-      Tb[(int64_t)q * n + O0 + i] = t;
-      if (O > K) A[(int64_t)(k0 + q) * n + O0 + i] = t;
-    }
-  }
-}
-
-// One block step in one launch, one workgroup per upper tile (bi <= bj).
-// The step reads the pivot inverse Pc = A_KK^-1 and the panel Cc[p][i] =
-// c_i[p] (c_i = A_iK before the step, taken from the stored upper triangle)
-// and writes the next step's Pn and Cn, so no workgroup reads what another
-// writes:
-//   tile (K, K):        A_KK = Pc;
-//   tile in row/col K:  T_O = c_O Pc for the other block O, and the new cross
-//                       entries A_OK = -T_O (O < K) or A_KO = T_O (O > K);
-//   other tiles (I, J): T_I = c_I Pc, A_IJ -= s_J T_I c_J^T (s_J = -1 for
-//                       J < K, +1 beyond), all on FP64 MFMA.
-// Entries that become the next panel (block column K+1 above the diagonal,
-// block row K+1 right of it, and A_{K,K+1}) are also written to Cn.
-// Workgroup 0 takes tile (K+1, K+1) and inverts the updated tile into Pn.
-// PRE_T: k_gj_cross has already formed T_O (into Tb[q][i]) and the row/col K
-// entries for this step; the tiles read T_I instead of forming it, and the
-// row/col K workgroups have nothing to do (large orders, where the repeated
-// T products cost more than the second launch).
-template <bool PRE_T>
-__global__ void __launch_bounds__(256) k_gj_step(int n, int k0, int kb, int nb,
-                                                 double* __restrict__ A,
-                                                 const double* __restrict__ Pc,
-                                                 double* __restrict__ Pn,
-                                                 const double* __restrict__ Cc,
-                                                 double* __restrict__ Cn,
-                                                 const double* __restrict__ Tb) {
-  __shared__ double sm[2 * kGJBlock * kGJBlock];
-  double* sP = sm;                        // Pc [p][q], later c_J [p][j]
-  double* sX = sm + kGJBlock * kGJBlock;  // c_O [p][i], later T [q][i]
-  const int K = k0 / kGJBlock;
-  const bool has_next = K + 1 < nb;
-  int bi, bj;
-  {
-    int t = blockIdx.x;
-    if (has_next) {  // workgroup 0: (K+1, K+1); the rest row-major, skipping it
-      if (t == 0) {
-        t = (K + 1) * nb - ((K + 1) * K) / 2;
-      } else {
-        --t;
-        const int nxt = (K + 1) * nb - ((K + 1) * K) / 2;
-        if (t >= nxt) ++t;
-      }
-    }
-    bi = 0;
-    while (t >= nb - bi) { t -= nb - bi; ++bi; }
-    bj = bi + t;
-  }
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int li = lane & 15, lk = lane >> 4;
-  const bool cross = bi == K || bj == K;
-  if (PRE_T && cross) return;
-  if (bi == K && bj == K) {
-    for (int x = tid; x < kb * kb; x += 256)
-      A[(int64_t)(k0 + x / kb) * n + k0 + x % kb] = Pc[x];
-    return;
-  }
-  const int O = cross ? (bi == K ? bj : bi) : bi;  // the block whose T is formed
-  const int O0 = O * kGJBlock, J0 = bj * kGJBlock, I0 = bi * kGJBlock;
-  const int orows = (n - O0 < kGJBlock) ? (n - O0) : kGJBlock;
-  // every global load in flight before the first LDS store
-  double pv[16], xv[16], cj[16];
-  f64x4 acc[4];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int x = tid + 256 * r, a = x >> 6, b = x & 63;
-    // PRE_T: xv holds T_I as [q][i] instead of c_O as [p][i]
-    pv[r] = (!PRE_T && a < kb && b < kb) ? Pc[a * kb + b] : 0.0;
-    xv[r] = (a < kb && b < orows) ? (PRE_T ? Tb : Cc)[(int64_t)a * n + O0 + b] : 0.0;
-    cj[r] = (!cross && a < kb && J0 + b < n) ? Cc[(int64_t)a * n + J0 + b] : 0.0;
-  }
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = I0 + 16 * w + lk + 4 * v, j = J0 + 16 * jb + li;
-      acc[jb][v] = (!cross && i < n && j < n) ? A[(int64_t)i * n + j] : 0.0;
-    }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int x = tid + 256 * r, a = x >> 6, b = x & 63;
-    if (!PRE_T) sP[swz(a, b)] = pv[r];
-    sX[swz(a, b)] = xv[r];
-  }
-  if (!PRE_T) {
-  __syncthreads();
-  // T[16w + i][16jb + j] = sum_p c[16w + i][p] P[p][16jb + j]
-  f64x4 tacc[4];
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb) tacc[jb] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kk = 0; kk < 16; ++kk) {
-    const int p = 4 * kk + lk;
-    const double a = sX[swz(p, 16 * w + li)];
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-      tacc[jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sP[swz(p, 16 * jb + li)], tacc[jb], 0, 0, 0);
-  }
-  __syncthreads();
-  // tacc[jb][v] = T[16w + lk + 4v][16jb + li]; stage T as [q][i]
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sX[swz(16 * jb + li, 16 * w + lk + 4 * v)] = tacc[jb][v];
-  if (cross) {  // only without PRE_T
-    if (O < K) {  // A[O0 + i][k0 + q] = -T[i][q], coalesced along q
-#pragma unroll
-      for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = 16 * w + lk + 4 * v, q = 16 * jb + li;
-          if (i < orows && q < kb) A[(int64_t)(O0 + i) * n + k0 + q] = -tacc[jb][v];
-        }
-      return;
-    }
-    if (O == K + 1) {  // next panel, rows of K: Cn[i][k0 + q] = T[i][q]
-#pragma unroll
-      for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = 16 * w + lk + 4 * v, q = 16 * jb + li;
-          if (i < orows && q < kb) Cn[(int64_t)i * n + k0 + q] = tacc[jb][v];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {  // A[k0 + q][O0 + i] = T[i][q], coalesced along i
-      const int x = tid + 256 * r, q = x >> 6, i = x & 63;
-      if (q < kb && i < orows) A[(int64_t)(k0 + q) * n + O0 + i] = sX[swz(q, i)];
-    }
-    return;
-  }
-  }  // !PRE_T: T formed and staged as [q][i] in sX
-  // tile: c_J as [p][j] replaces P
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int x = tid + 256 * r, a = x >> 6, b = x & 63;
-    sP[swz(a, b)] = cj[r];
-  }
-  __syncthreads();
-  const double ns = (J0 < k0) ? 1.0 : -1.0;  // -s_J
-#pragma unroll
-  for (int kk = 0; kk < 16; ++kk) {
-    const int p = 4 * kk + lk;
-    const double a = ns * sX[swz(p, 16 * w + li)];
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-      acc[jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sP[swz(p, 16 * jb + li)], acc[jb], 0, 0, 0);
-  }
-  const bool next_col = bj == K + 1 && bi != K + 1, next_row = bi == K + 1 && bj != K + 1;
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = I0 + 16 * w + lk + 4 * v, j = J0 + 16 * jb + li;
-      if (i < n && j < n) {
-        A[(int64_t)i * n + j] = acc[jb][v];
-        // row K+1 of the next panel: Cn[p][j] = A[(K+1)0 + p][j]
-        if (next_row) Cn[(int64_t)(i - I0) * n + j] = acc[jb][v];
-      }
-    }
-  if (next_col) {  // column K+1: Cn[p][i] = A[i][J0 + p], staged to be coalesced along i
-    __syncthreads();
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sX[swz(16 * jb + li, 16 * w + lk + 4 * v)] = acc[jb][v];
-    __syncthreads();
-    const int ncol = (n - J0 < kGJBlock) ? (n - J0) : kGJBlock;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int x = tid + 256 * r, p = x >> 6, i = x & 63;
-      if (p < ncol && I0 + i < n) Cn[(int64_t)p * n + I0 + i] = sX[swz(p, i)];
-    }
-    return;
-  }
-  if (blockIdx.x != 0 || !has_next) return;
-  // next pivot block: the tile just updated, identity beyond the matrix
-  double (*sS)[kGJBlock + 1] = reinterpret_cast<double (*)[kGJBlock + 1]>(sm);
-  const int kbn = (n - I0 < kGJBlock) ? (n - I0) : kGJBlock;
-  __syncthreads();
-#pragma unroll
-  for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int ti = 16 * w + lk + 4 * v, tj = 16 * jb + li;
-      sS[ti][tj] = (ti < kbn && tj < kbn) ? acc[jb][v] : (ti == tj ? 1.0 : 0.0);
-    }
-  __syncthreads();
-  gj64_block(sS);
-  for (int x = threadIdx.x; x < kbn * kbn; x += 256) Pn[x] = sS[x / kbn][x % kbn];
-}
-
-// Lower tiles (bi > bj) <- transpose of the upper tiles.
-__global__ void __launch_bounds__(256) k_gj_mirror(int n, double* __restrict__ A) {
-  __shared__ double sX[kGJBlock][kGJBlock + 1];
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  if (bi <= bj) return;
-  const int I0 = bi * kGJBlock, J0 = bj * kGJBlock, tid = threadIdx.x;
-  for (int x = tid; x < kGJBlock * kGJBlock; x += 256) {  // read A[J0 + r][I0 + c]
-    const int r = x / 64, c = x % 64;
-    if (J0 + r < n && I0 + c < n) sX[r][c] = A[(int64_t)(J0 + r) * n + I0 + c];
-  }
-  __syncthreads();
-  for (int x = tid; x < kGJBlock * kGJBlock; x += 256) {  // write A[I0 + r][J0 + c]
-    const int r = x / 64, c = x % 64;
-    if (I0 + r < n && J0 + c < n) A[(int64_t)(I0 + r) * n + J0 + c] = sX[c][r];
-  }
 }
 
 // y = A x for the dense (symmetric) inverse; one wavefront per row.
@@ -1822,6 +1327,16 @@ void launch_apply_l1_jacobi_f32(const Grid& g, const double* Ke, const double* K
 // to fifth level 6.1/5.2/4.7 -> 8.2/6.9/5.2).  As a z-march the fine level
 // takes 79.5 us (FP64) and 39.1 us (FP32).
 constexpr int64_t kRsMinNodes = 100000;
+
+// The order of a level's vectors: [component][node], x fastest.
+static CoarseOrder natural(const Grid& g) {
+  CoarseOrder o;
+  o.si = 1;
+  o.sj = g.nx + 1;
+  o.sk = (g.nx + 1) * (g.ny + 1);
+  o.sc = (int)g.nn;
+  return o;
+}
 template <typename T>
 static void restrict_z(const Grid& coarse, const T* bf, const T* tf, const uint8_t* mask, T* bc,
                        const T* dc, T omega, T* xc, hipStream_t s, int nr, int64_t fs,
@@ -1883,21 +1398,22 @@ void launch_restrict_jacobi_f32(const Grid& coarse, const float* bf, const float
     return;
   }
   k_restrict<float><<<dim3(nblk(coarse.nn, 64), 3, nr), 192, 0, s>>>(
-      coarse.nx, coarse.ny, coarse.nz, bf, tf, mask, bc, dinv_c, omega, xc, 3 * fnn,
-      3 * coarse.nn);
+      coarse.nx, coarse.ny, coarse.nz, bf, tf, mask, bc, dinv_c, omega, xc, natural(coarse),
+      3 * fnn, 3 * coarse.nn);
 }
 
 void launch_restrict_f32(const Grid& coarse, const float* bf, const float* tf,
-                         const uint8_t* mask, float* bc, hipStream_t s, int nr) {
+                         const uint8_t* mask, float* bc, hipStream_t s, int nr,
+                         const CoarseOrder* o) {
   const int64_t fnn = (int64_t)(2 * coarse.nx + 1) * (2 * coarse.ny + 1) * (2 * coarse.nz + 1);
-  if (coarse.nz > 0 && coarse.nn >= kRsMinNodes) {
+  if (!o && coarse.nz > 0 && coarse.nn >= kRsMinNodes) {
     restrict_z<float>(coarse, bf, tf, mask, bc, nullptr, 0.0f, nullptr, s, nr, 3 * fnn,
                       3 * coarse.nn);
     return;
   }
   k_restrict<float><<<dim3(nblk(coarse.nn, 64), 3, nr), 192, 0, s>>>(
-      coarse.nx, coarse.ny, coarse.nz, bf, tf, mask, bc, nullptr, 0.0f, nullptr, 3 * fnn,
-      3 * coarse.nn);
+      coarse.nx, coarse.ny, coarse.nz, bf, tf, mask, bc, nullptr, 0.0f, nullptr,
+      o ? *o : natural(coarse), 3 * fnn, 3 * coarse.nn);
 }
 
 // Interpolation with the coarse values in LDS on 3D grids from kPzMinNodes
@@ -1913,14 +1429,15 @@ static void prolong_z(const Grid& fine, const T* xc, const uint8_t* mask, T* xf,
 }
 
 void launch_prolong_add_f32(const Grid& fine, const float* xc, const uint8_t* mask, float* xf,
-                            hipStream_t s, int nr) {
-  const int64_t cnn = (int64_t)(fine.nx / 2 + 1) * (fine.ny / 2 + 1) * (fine.nz / 2 + 1);
-  if (fine.nz > 0 && fine.nn >= kPzMinNodes) {
+                            hipStream_t s, int nr, const CoarseOrder* o) {
+  const Grid cg = make_grid(fine.nx / 2, fine.ny / 2, fine.nz / 2);
+  const int64_t cnn = cg.nn;
+  if (!o && fine.nz > 0 && fine.nn >= kPzMinNodes) {
     prolong_z<float>(fine, xc, mask, xf, s, nr, 3 * cnn, 3 * fine.nn);
     return;
   }
   k_prolong_add<float><<<dim3(nblk(fine.nn, 256), 1, nr), 256, 0, s>>>(
-      fine.nx, fine.ny, fine.nz, xc, mask, xf, 3, 3 * cnn, 3 * fine.nn);
+      fine.nx, fine.ny, fine.nz, xc, mask, xf, 3, o ? *o : natural(cg), 3 * cnn, 3 * fine.nn);
 }
 
 void launch_jacobi_first_f32(int64_t n3, const float* b, const float* dinv, float omega, float* x,
@@ -1943,14 +1460,14 @@ void launch_diag_elemmat(const Grid& g, const double* Ke, double* dinv, float* d
 }
 
 void launch_restrict(const Grid& coarse, const double* bf, const double* tf, const uint8_t* mask,
-                     double* bc, hipStream_t s, int ncomp) {
-  if (coarse.nz > 0 && ncomp == 3 && coarse.nn >= kRsMinNodes) {
+                     double* bc, hipStream_t s, int ncomp, const CoarseOrder* o) {
+  if (!o && coarse.nz > 0 && ncomp == 3 && coarse.nn >= kRsMinNodes) {
     restrict_z<double>(coarse, bf, tf, mask, bc, nullptr, 0.0, nullptr, s, 1, 0, 0);
     return;
   }
   k_restrict<double><<<dim3(nblk(coarse.nn, 64), ncomp), 192, 0, s>>>(coarse.nx, coarse.ny, coarse.nz,
                                                                   bf, tf, mask, bc, nullptr, 0.0,
-                                                                  nullptr);
+                                                                  nullptr, o ? *o : natural(coarse));
 }
 
 void launch_restrict_jacobi(const Grid& coarse, const double* bf, const double* tf,
@@ -1962,17 +1479,18 @@ void launch_restrict_jacobi(const Grid& coarse, const double* bf, const double* 
   }
   k_restrict<double><<<dim3(nblk(coarse.nn, 64), 3), 192, 0, s>>>(coarse.nx, coarse.ny, coarse.nz,
                                                                   bf, tf, mask, bc, dinv_c, omega,
-                                                                  xc);
+                                                                  xc, natural(coarse));
 }
 
 void launch_prolong_add(const Grid& fine, const double* xc, const uint8_t* mask, double* xf,
-                        hipStream_t s, int ncomp) {
-  if (fine.nz > 0 && ncomp == 3 && fine.nn >= kPzMinNodes) {
+                        hipStream_t s, int ncomp, const CoarseOrder* o) {
+  if (!o && fine.nz > 0 && ncomp == 3 && fine.nn >= kPzMinNodes) {
     prolong_z<double>(fine, xc, mask, xf, s, 1, 0, 0);
     return;
   }
-  k_prolong_add<double><<<nblk(fine.nn, 256), 256, 0, s>>>(fine.nx, fine.ny, fine.nz, xc, mask,
-                                                           xf, ncomp);
+  k_prolong_add<double><<<nblk(fine.nn, 256), 256, 0, s>>>(
+      fine.nx, fine.ny, fine.nz, xc, mask, xf, ncomp,
+      o ? *o : natural(make_grid(fine.nx / 2, fine.ny / 2, fine.nz / 2)));
 }
 
 void launch_jacobi_first(int64_t n3, const double* b, const double* dinv, double omega, double* x,
@@ -1983,42 +1501,6 @@ void launch_jacobi_first(int64_t n3, const double* b, const double* dinv, double
 void launch_jacobi_update(int64_t n3, const double* b, const double* t, const double* dinv,
                           double omega, double* x, hipStream_t s) {
   k_jacobi_update<double><<<nblk(n3, 256), 256, 0, s>>>(n3, b, t, dinv, omega, x);
-}
-
-void launch_assemble_dense(const Grid& g, const double* Ke, double* A, hipStream_t s) {
-  k_assemble_dense<<<(unsigned)((3 * g.nn + 3) / 4), 256, 0, s>>>(g.nx, g.ny, g.nz, Ke, A);
-}
-
-void launch_gj_invert(int n, double* A, double* P, double* T, double* C, double* Tb,
-                      hipStream_t s) {
-  const int nb = (n + kGJBlock - 1) / kGJBlock;
-  const unsigned n_upper = (unsigned)(nb * (nb + 1) / 2);
-  // pivot inverses and panels alternate between two buffers each
-  double* Pb[2] = {P, P + kGJBlock * kGJBlock};
-  double* Cb[2] = {C, T};
-  // beyond 40 block rows the repeated T products of the one-launch step cost
-  // more than a separate cross launch (measured: 32 us per step at 30 block
-  // rows in one launch; 73 vs 61 us per step at 65)
-  const bool split = nb > 40;
-  const int kb0 = std::min(n, kGJBlock);
-  k_gj_pivot_first<<<(unsigned)(1 + ((int64_t)kb0 * n + 2047) / 2048), 256, 0, s>>>(n, kb0, A,
-                                                                                  Pb[0], Cb[0]);
-  int step = 0;
-  for (int k0 = 0; k0 < n; k0 += kGJBlock, ++step) {
-    const int kb = std::min(kGJBlock, n - k0);
-    if (split) {
-      k_gj_cross<<<nb, 256, 0, s>>>(n, k0, kb, A, Pb[step & 1], Cb[step & 1],
-                                    Cb[(step + 1) & 1], Tb);
-      k_gj_step<true><<<n_upper, 256, 0, s>>>(n, k0, kb, nb, A, Pb[step & 1],
-                                              Pb[(step + 1) & 1], Cb[step & 1],
-                                              Cb[(step + 1) & 1], Tb);
-    } else {
-      k_gj_step<false><<<n_upper, 256, 0, s>>>(n, k0, kb, nb, A, Pb[step & 1],
-                                               Pb[(step + 1) & 1], Cb[step & 1],
-                                               Cb[(step + 1) & 1], nullptr);
-    }
-  }
-  k_gj_mirror<<<dim3(nb, nb), 256, 0, s>>>(n, A);
 }
 
 void launch_gemv(int n, const double* A, const double* x, double* y, hipStream_t s) {

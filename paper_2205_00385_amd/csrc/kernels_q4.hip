@@ -262,39 +262,38 @@ __global__ void k_springs_galerkin(SpringSet S, int cnx, int cny, const uint8_t*
   }
 }
 
-// Dense coarsest operator in SoA DOF order (c * nn + node); one wavefront
-// per row, lanes over the columns: an entry sums, over the elements around
-// the row's node in corner order a = 0..3, the entries coupling the two nodes.
-__global__ void __launch_bounds__(256) k_q4_assemble_dense(int nx, int ny,
+// Dense coarsest operator with the unknowns in the order o; one wavefront per
+// row, zeroed first (coalesced), then lanes take the 18 columns of the 9-node
+// neighbourhood: an entry sums, over the elements around the row's node in
+// corner order a = 0..3, the entries coupling the two nodes.
+__global__ void __launch_bounds__(256) k_q4_assemble_dense(int nx, int ny, CoarseOrder o,
                                                            const double* __restrict__ Ke,
                                                            double* __restrict__ A) {
-  const int64_t nn = (int64_t)(nx + 1) * (ny + 1);
-  const int64_t ne = (int64_t)nx * ny;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int nxp = nx + 1, nn = nxp * (ny + 1), ne = nx * ny, nd = 2 * nn;
+  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (row >= 2 * nn) return;  // wave-uniform
-  const int c = (int)(row / nn);
-  const int64_t n = row % nn;
-  const int i = (int)(n % (nx + 1)), j = (int)(n / (nx + 1));
-  double* Ar = A + row * 2 * nn;
-  for (int64_t q = lane; q < 2 * nn; q += 64) {
-    const int d = (int)(q / nn);
-    const int64_t nb = q % nn;
-    const int bi = (int)(nb % (nx + 1)), bj = (int)(nb / (nx + 1));
-    double acc = 0.0;
-    if (abs(bi - i) <= 1 && abs(bj - j) <= 1) {
-      for (int a = 0; a < 4; ++a) {
-        const int ex = i - (a & 1), ey = j - (a >> 1);
-        if (ex < 0 || ex >= nx || ey < 0 || ey >= ny) continue;
-        const int dx = bi - ex, dy = bj - ey;
-        if (dx < 0 || dx > 1 || dy < 0 || dy > 1) continue;
-        const int64_t e = (int64_t)ex + (int64_t)nx * ey;
-        acc += Ke[(int64_t)s2(2 * a + c, 2 * (dx + 2 * dy) + d) * ne + e];
-      }
-    }
-    if (q == row && acc == 0.0) acc = 1.0;  // dead coarse DOF: identity row
-    Ar[q] = acc;
+  const bool active = item < nd;  // wave-uniform; every wave reaches the barrier
+  const int c = item / nn, n = item % nn;
+  const int i = n % nxp, j = n / nxp;
+  const int row = c * o.sc + i * o.si + j * o.sj;
+  double* Ar = A + (int64_t)(active ? row : 0) * nd;
+  if (active)
+    for (int t = lane; t < nd; t += 64) Ar[t] = 0.0;
+  __syncthreads();  // the zeros are stored before the same addresses are rewritten
+  if (!active || lane >= 18) return;
+  const int d = lane / 9, nb = lane % 9;
+  const int bi = i + nb % 3 - 1, bj = j + nb / 3 - 1;
+  if (bi < 0 || bi > nx || bj < 0 || bj > ny) return;
+  double acc = 0.0;
+  for (int a = 0; a < 4; ++a) {
+    const int ex = i - (a & 1), ey = j - (a >> 1);
+    if (ex < 0 || ex >= nx || ey < 0 || ey >= ny) continue;
+    const int dx = bi - ex, dy = bj - ey;
+    if (dx < 0 || dx > 1 || dy < 0 || dy > 1) continue;
+    acc += Ke[(int64_t)s2(2 * a + c, 2 * (dx + 2 * dy) + d) * ne + ex + nx * ey];
   }
+  const int col = d * o.sc + bi * o.si + bj * o.sj;
+  Ar[col] = (col == row && acc == 0.0) ? 1.0 : acc;  // dead coarse DOF: identity row
 }
 
 }  // namespace
@@ -350,8 +349,9 @@ void launch_q4_diag_elemmat(const Grid& g, const double* Ke, double* dinv, hipSt
   k_q4_diag_elemmat<<<nblk(g.nn, 256), 256, 0, s>>>(g.nx, g.ny, Ke, dinv);
 }
 
-void launch_q4_assemble_dense(const Grid& g, const double* Ke, double* A, hipStream_t s) {
-  k_q4_assemble_dense<<<(unsigned)((2 * g.nn + 3) / 4), 256, 0, s>>>(g.nx, g.ny, Ke, A);
+void launch_q4_assemble_dense(const Grid& g, const CoarseOrder& o, const double* Ke, double* A,
+                              hipStream_t s) {
+  k_q4_assemble_dense<<<(unsigned)((2 * g.nn + 3) / 4), 256, 0, s>>>(g.nx, g.ny, o, Ke, A);
 }
 
 }  // namespace aarmr
