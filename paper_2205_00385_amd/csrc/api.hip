@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "moment.hpp"
 
 using namespace aarmr;
 
@@ -72,7 +73,7 @@ int oc_scratch_ptr(double** out) {
   } while (0)
 
 struct LevelBuf {
-  double* Ke = nullptr;    // levels >= 1: packed Galerkin element matrices [300][ne]
+  double* Ke = nullptr;    // levels >= 1: element matrices, [300][ne] (3D: the stored ones), [36][ne]
   double* dinv = nullptr;  // [3][nn] inverse Jacobi diagonal
   double* b = nullptr;     // levels >= 1: right-hand side
   double* x = nullptr;     // levels >= 1: correction
@@ -82,7 +83,7 @@ struct LevelBuf {
   float* b32 = nullptr;
   float* x32 = nullptr;
   float* t32 = nullptr;
-  float* Ke32 = nullptr;  // 3D levels >= 2: FP32 copy of Ke for the FP32 V-cycle
+  float* Ke32 = nullptr;  // 3D levels >= 2 above the coarsest: FP32 element matrices [300][ne]
 };
 
 // Scalar history in device memory (indices into m->scal).
@@ -123,10 +124,6 @@ struct aarmr_mesh {
   int nc = 0;                 // coarsest dense order
   double KE[576];             // 24x24 (3D) or 8x8 (2D) row-major
   WalshConsts wk;             // reflection-blocked form of KE (3D)
-  double Mc[8 * kSymEntries]; // P_c^T KE P_c per child position, packed
-  std::vector<double> N2;     // [300][64]: P_c1^T M_c0 P_c1 per fine descendant d = 8 c1 + c0 of a level-2 parent
-  double Bw[576];             // W M_0 W / 64 in the Walsh x component basis
-  float Bw32[576];
   bool fp32 = false;          // precision == AARMR_FP32_REFINE
   int tz64 = 0, tz32 = 0;     // tuned EbE z-chunk lengths (0: default)
   SpringSet springs{};        // grounded springs (plane stress)
@@ -134,22 +131,17 @@ struct aarmr_mesh {
   char* ws = nullptr;
   int64_t ws_bytes = 0;
   double* KEd = nullptr;
-  double* Mcd = nullptr;      // P_c^T KE P_c of the 8 children, packed
-  double* N2d = nullptr;      // N2 on the device
-  int* list2 = nullptr;       // level-2 parents with a flagged level-1 child
-  int* count2 = nullptr;
-  double* Bwd = nullptr;      // Bw on the device
-  float* Bw32d = nullptr;
-  double* Y1 = nullptr;       // level-1 element products [24][ne1]
-  double* Kcomp1 = nullptr;   // compact copy of the flagged parents' matrices
-  int cap1 = 0;               // its capacity (parents)
-  int nflag1 = 0;             // flagged level-1 parents of the current hierarchy
-  float* Y1f = nullptr;
+  float Bw32[576];            // W M_0 W / 64 in the Walsh x component basis (refinement form)
+  float* Bw32d = nullptr;     // on the device
+  float* Y1f = nullptr;       // level-1 element products [24][ne1] (refinement form)
+  std::vector<double> Cm[AARMR_MAX_LEVELS];   // matrices per unit moment (refinement form)
+  double* Cmd[AARMR_MAX_LEVELS] = {};         // on the device
+  LevelTable lt;              // 3D: flags, lists, moments and stored matrices per coarse level
+  int nspecial[AARMR_MAX_LEVELS] = {};  // special nodes per level of the current hierarchy
+  int nstored1 = 0;                     // stored elements of level 1
+  bool counts_ready = false;            // read back since the last hierarchy build
   float* E32 = nullptr;       // FP32 moduli (refinement form)
   float *r32 = nullptr, *z32 = nullptr, *p32 = nullptr, *q32 = nullptr, *d32 = nullptr;
-  uint8_t* eflag1 = nullptr;  // level-1 parents touching a fixed DOF
-  int* list1 = nullptr;       // their indices
-  int* count1 = nullptr;
   double* E = nullptr;
   double* E_prev = nullptr;
   double* dE = nullptr;
@@ -355,33 +347,6 @@ void child_galerkin(const double* KE, double* Mc) {
   }
 }
 
-// Nt[entry][8 c1 + c0] = (P_c1^T M_c0 P_c1)[entry]: the contribution of fine
-// descendant c0 of level-1 child c1 to a level-2 parent's Galerkin matrix,
-// per unit modulus (packed entries, stored transposed).  So a parent whose level-1 children touch no fixed DOF has the
-// matrix sum_d E_d N_d over its 64 fine descendants.
-void grandchild_galerkin(const double* Mc, double* N) {
-  auto phi = [](int pos, int A) { return pos == 1 ? 0.5 : ((pos >> 1) == A ? 1.0 : 0.0); };
-  for (int c1 = 0; c1 < 8; ++c1) {
-    const int dx = c1 & 1, dy = (c1 >> 1) & 1, dz = c1 >> 2;
-    double P[8][8];  // P[b][A]: child corner b from parent corner A
-    for (int b = 0; b < 8; ++b)
-      for (int A = 0; A < 8; ++A)
-        P[b][A] = phi(dx + (b & 1), A & 1) * phi(dy + ((b >> 1) & 1), (A >> 1) & 1) *
-                  phi(dz + (b >> 2), A >> 2);
-    for (int c0 = 0; c0 < 8; ++c0) {
-      const double* M = Mc + c0 * kSymEntries;
-      for (int I = 0; I < 24; ++I)
-        for (int J = I; J < 24; ++J) {
-          double acc = 0.0;
-          for (int b = 0; b < 8; ++b)
-            for (int b2 = 0; b2 < 8; ++b2)
-              acc += P[b][I / 3] * M[sym_index(3 * b + I % 3, 3 * b2 + J % 3)] * P[b2][J / 3];
-          N[(int64_t)sym_index(I, J) * 64 + 8 * c1 + c0] = acc;
-        }
-    }
-  }
-}
-
 // Check M_c = R_c M_0 R_c for every child c, where R_c mirrors the parent in
 // the axes set in c: (R_c v)[3b + s] = (-1)^(bit s of c) v[3(b ^ c) + s].
 bool mirror_children(const double* Mc) {
@@ -446,6 +411,94 @@ bool walsh_parent_check(const double* Mc, const double* Bw) {
   return true;
 }
 
+// C[entry][m] (28 to a row, the last zero): the packed matrix of a level-l
+// element per unit of its moment m, from the moment operator on unit vectors.
+void moment_matrices(const WalshConsts& K, int level, double* C) {
+  const double gam = 1.0 / (1 << level);
+  double w[8][8];  // w[a][k] = (-1)^popcount(k & a) gam^popcount(k)
+  for (int a = 0; a < 8; ++a)
+    for (int k = 0; k < 8; ++k) {
+      const int n = __builtin_popcount(k);
+      const double g = n == 0 ? 1.0 : n == 1 ? gam : n == 2 ? gam * gam : gam * gam * gam;
+      w[a][k] = (__builtin_popcount(k & a) & 1) ? -g : g;
+    }
+  for (int m = 0; m < 28; ++m)
+    for (int col = 0; col < 24; ++col) {
+      Moments27<double> M;
+      for (double& x : M.m) x = 0.0;
+      if (m < 27) M.m[m] = 1.0;
+      double h[8][3] = {}, z[8][3];
+      for (int k = 0; k < 8; ++k) h[k][col % 3] = w[col / 3][k];
+      moment_apply(K, M, h, z);
+      for (int r = 0; r <= col; ++r) {
+        double t = 0.0;
+        for (int k = 0; k < 8; ++k) t += w[r / 3][k] * z[k][r % 3];
+        C[sym_index(r, col) * 28 + m] = t;
+      }
+    }
+}
+
+// The moment form of a level-2 element (the operator the coarse-level kernels
+// evaluate) against sum_d E_d P_d^T KE P_d for moduli E_d = 1 + d / 64 and one
+// vector.
+bool moment_check(const double* KE, const WalshConsts& K) {
+  constexpr int n = 4;
+  double v[24], want[24] = {}, got[24] = {}, scale = 0.0;
+  for (int q = 0; q < 24; ++q) v[q] = ((q * 7) % 11) / 11.0 - 0.4;
+  Moments27<double> M;
+  for (double& m : M.m) m = 0.0;
+  for (int d = 0; d < n * n * n; ++d) {
+    const int x[3] = {d % n, (d / n) % n, d / (n * n)};
+    const double E = 1.0 + d / 64.0;
+    double P[8][8], w[24];
+    for (int b = 0; b < 8; ++b)
+      for (int A = 0; A < 8; ++A) {
+        P[b][A] = 1.0;
+        for (int a = 0; a < 3; ++a) {
+          const double t = (x[a] + ((b >> a) & 1)) / (double)n;
+          P[b][A] *= (A >> a) & 1 ? t : 1.0 - t;
+        }
+      }
+    for (int b = 0; b < 8; ++b)
+      for (int c = 0; c < 3; ++c) {
+        w[3 * b + c] = 0.0;
+        for (int A = 0; A < 8; ++A) w[3 * b + c] += P[b][A] * v[3 * A + c];
+      }
+    for (int r = 0; r < 24; ++r) {
+      double t = 0.0;
+      for (int q = 0; q < 24; ++q) t += KE[r * 24 + q] * w[q];
+      for (int A = 0; A < 8; ++A) want[3 * A + r % 3] += E * P[r / 3][A] * t;
+    }
+    double tau[3][3];
+    for (int a = 0; a < 3; ++a) {
+      const double t = n - 1 - 2 * x[a];
+      tau[a][0] = 1.0;
+      tau[a][1] = t;
+      tau[a][2] = t * t;
+    }
+    for (int m = 0; m < 27; ++m) M.m[m] += E * tau[0][m % 3] * tau[1][(m / 3) % 3] * tau[2][m / 9];
+  }
+  double h[8][3], z[8][3], sc[8];
+  for (int k = 0; k < 8; ++k) {
+    sc[k] = std::pow(1.0 / n, __builtin_popcount(k));
+    for (int c = 0; c < 3; ++c) {
+      h[k][c] = 0.0;
+      for (int a = 0; a < 8; ++a)
+        h[k][c] += sc[k] * ((__builtin_popcount(k & a) & 1) ? -v[3 * a + c] : v[3 * a + c]);
+    }
+  }
+  moment_apply(K, M, h, z);
+  double err = 0.0;
+  for (int a = 0; a < 8; ++a)
+    for (int c = 0; c < 3; ++c) {
+      for (int k = 0; k < 8; ++k)
+        got[3 * a + c] += sc[k] * ((__builtin_popcount(k & a) & 1) ? -z[k][c] : z[k][c]);
+      err = std::max(err, std::fabs(got[3 * a + c] - want[3 * a + c]));
+      scale = std::max(scale, std::fabs(want[3 * a + c]));
+    }
+  return err <= 1e-12 * scale;
+}
+
 // DOFs of level l (dim per node).
 inline int64_t ndof(const aarmr_mesh* m, int l) { return m->dim * m->lg[l].nn; }
 
@@ -463,20 +516,26 @@ int64_t layout(aarmr_mesh* m, char* base) {
   const bool solid = m->dim == 3;
   const int64_t nsym = solid ? kSymEntries : kSymEntries2;
   m->KEd = (double*)take(576 * d8);
-  if (solid) {  // level-1 Walsh product (3D only)
-    m->Mcd = (double*)take(8 * kSymEntries * d8);
-    m->N2d = (double*)take(64 * kSymEntries * d8);
-    if (m->nlev > 2) {
-      m->list2 = (int*)take(m->lg[2].ne * 4);
-      m->count2 = (int*)take(4);
+  if (solid) {  // coarse levels: flags, lists, moments
+    LevelTable& T = m->lt;
+    T.nlev = m->nlev;
+    for (int l = 1; l < m->nlev; ++l) {
+      const Grid& G = m->lg[l];
+      T.nx[l] = G.nx;
+      T.ny[l] = G.ny;
+      T.nz[l] = G.nz;
+      T.ne[l] = (int)G.ne;
+      T.nn[l] = (int)G.nn;
+      T.eflag[l] = (uint8_t*)take(G.ne);
+      T.special[l] = (uint8_t*)take(G.nn);
+      T.eidx[l] = (int*)take(G.ne * 4);
+      T.elist[l] = (int*)take(G.ne * 4);
+      T.nlist[l] = (int*)take(G.nn * 4);
+      T.corner[l] = (int*)take(8 * G.nn * 4);
+      if (l >= 2 && l < m->nlev - 1) T.mom[l] = (double*)take(27 * G.ne * d8);
     }
-    m->eflag1 = (uint8_t*)take(m->lg[1].ne);
-    m->list1 = (int*)take(m->lg[1].ne * 4);
-    m->count1 = (int*)take(4);
-    m->Bwd = (double*)take(576 * d8);
-    m->Y1 = (double*)take(24 * m->lg[1].ne * d8);
-    m->cap1 = (int)std::min<int64_t>(m->lg[1].ne, std::max<int64_t>(m->lg[1].ne / 8, 1024));
-    m->Kcomp1 = (double*)take((int64_t)kSymEntries * m->cap1 * d8);
+    T.part = (int*)take(level_list_blocks(m->lg, m->nlev) * 4);
+    T.counts = (int*)take(2 * AARMR_MAX_LEVELS * 4);
   }
   m->E = (double*)take(g.ne * d8);
   m->E_prev = (double*)take(g.ne * d8);
@@ -504,6 +563,7 @@ int64_t layout(aarmr_mesh* m, char* base) {
     LevelBuf& L = m->lv[l];
     const int64_t nl = ndof(m, l);
     L.Ke = (double*)take(G.ne * nsym * d8);
+    if (solid) m->lt.Kst[l] = L.Ke;
     L.dinv = (double*)take(nl * d8);
     L.b = (double*)take(nl * d8);
     L.x = (double*)take(nl * d8);
@@ -530,7 +590,10 @@ int64_t layout(aarmr_mesh* m, char* base) {
         L.b32 = (float*)take(R * m3 * f4);
         L.x32 = (float*)take(R * m3 * f4);
       }
-      if (solid && l >= 2 && l < m->nlev - 1) L.Ke32 = (float*)take(m->lg[l].ne * nsym * f4);
+      if (l >= 2 && l < m->nlev - 1) {
+        L.Ke32 = (float*)take(m->lg[l].ne * kSymEntries * f4);
+        m->Cmd[l] = (double*)take(28 * kSymEntries * d8);
+      }
     }
     m->act = (int*)take(R * 4);
   }
@@ -670,13 +733,47 @@ int orth_svd(aarmr_mesh* m, int Nm, int* kept, hipStream_t s) {
   return AARMR_OK;
 }
 
-// The flagged level-1 parent count of the current hierarchy, copied by setup
-// into the pinned staging area (doubles 72.., after the scalar read-backs at
-// 0..3 and the flag word at 64); the first call after a setup synchronises.
-int flagged_count(aarmr_mesh* m, hipStream_t s) {
-  if (m->nflag1 >= 0) return AARMR_OK;
+// The special-node counts of the current hierarchy, copied by the build into
+// the pinned staging area (doubles 72.., after the scalar read-backs at 0..3
+// and the flag word at 64); the first call after a build synchronises.
+int level_counts(aarmr_mesh* m, hipStream_t s) {
+  if (m->counts_ready) return AARMR_OK;
   HIP_TRY(hipStreamSynchronize(s));
-  m->nflag1 = *reinterpret_cast<const int*>(m->hpin + 72);
+  const int* h = reinterpret_cast<const int*>(m->hpin + 72);
+  for (int l = 1; l < m->nlev; ++l) m->nspecial[l] = h[2 * l + 1];
+  m->nstored1 = h[2];
+  m->counts_ready = true;
+  return AARMR_OK;
+}
+
+// What the product of coarse level l reads (3D).
+LevelArgs level_args(const aarmr_mesh* m, int l) {
+  const LevelTable& T = m->lt;
+  return LevelArgs{l,          T.nx[l],      T.ny[l],    T.nz[l],    m->nspecial[l], 1.0 / (1 << l),
+                   T.mom[l],   T.special[l], T.nlist[l], T.corner[l], T.Kst[l]};
+}
+
+// Product of coarse level l (3D), by launch_level_product's modes.
+int level_product(aarmr_mesh* m, int l, int mode, const double* v, double* y, const double* b,
+                  hipStream_t s) {
+  TRY(level_counts(m, s));
+  launch_level_product(level_args(m, l), m->wk, m->E, mode, v, y, b, m->lv[l].dinv, m->p.omega, s);
+  KCHECK();
+  return AARMR_OK;
+}
+
+int level_product32(aarmr_mesh* m, int l, int mode, const float* v, float* y, const float* b,
+                    hipStream_t s, int nr) {
+  const LevelBuf& L = m->lv[l];
+  const float om = (float)m->p.omega;
+  if (l == 1) {
+    TRY(level_counts(m, s));
+    launch_apply_l1_f32(m->lg[1], m->lt.Kst[1], m->Bw32d, m->E32, m->lt.eflag[1], m->lt.elist[1],
+                        m->nstored1, mode, v, m->Y1f, y, b, L.dinv32, om, nr, s);
+  } else {
+    launch_apply_elemmat_f32(m->lg[l], L.Ke32, mode, v, y, b, L.dinv32, om, nr, s);
+  }
+  KCHECK();
   return AARMR_OK;
 }
 
@@ -715,12 +812,8 @@ int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
   if (l == 0) {
     launch_ebe(m->lg[0], m->wk, m->E, m->mask, v, y, any_input ? 0 : 2, s, m->tz64);
     ++m->sweeps;
-  } else if (l == 1) {
-    TRY(flagged_count(m, s));
-    launch_apply_l1(m->lg[1], m->lv[1].Ke, m->Kcomp1, m->cap1, m->Bwd, m->E, m->eflag1,
-                    m->list1, m->count1, m->nflag1, v, m->Y1, y, s);
   } else {
-    launch_apply_elemmat(m->lg[l], m->lv[l].Ke, v, y, s);
+    return level_product(m, l, 0, v, y, nullptr, s);
   }
   KCHECK();
   return AARMR_OK;
@@ -731,10 +824,11 @@ int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
 // by the kernel that produced b).  On the 3D hierarchy the sweeps are fused
 // into neighbouring kernels: the restriction forms the coarse level's first
 // sweep, and below the finest level the last post-smoothing sweep is the
-// epilogue of its operator product.  On levels >= 2 that product writes into
-// L.t and the level's x and t buffers swap roles, so there x must be L.x; on
-// the finest level this is done only for the solver's own z (m->z, which
-// swaps with t0), a caller's buffer gets the separate sweep.
+// epilogue of its operator product, which writes into L.t, and the level's x
+// and t buffers swap roles, so there x must be L.x; on the finest level this is
+// done only for the solver's own z (m->z, which swaps with t0), a caller's
+// buffer gets the separate sweep.  The coarse levels' product before the
+// restriction forms the residual itself.
 int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
            bool x_init = false) {
   if (l == m->nlev - 1) {
@@ -761,11 +855,18 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
       launch_jacobi_update(n3, b, L.t, L.dinv, om, x, s);
       KCHECK();
     }
-    TRY(apply(m, l, x, L.t, s));  // line 2: residual, restricted
-    if (child_first)
-      launch_restrict_jacobi(m->lg[l + 1], b, L.t, mask, C.b, C.dinv, om, C.x, s);
+    // line 2: residual, restricted
+    const bool res = fuse && l >= 1;  // L.t holds b - A x, not A x
+    if (res)
+      TRY(level_product(m, l, 2, x, L.t, b, s));
     else
-      launch_restrict(m->lg[l + 1], b, L.t, mask, C.b, s, m->dim, co);
+      TRY(apply(m, l, x, L.t, s));
+    const double* rb = res ? L.t : b;
+    const double* rt = res ? nullptr : L.t;
+    if (child_first)
+      launch_restrict_jacobi(m->lg[l + 1], rb, rt, mask, C.b, C.dinv, om, C.x, s);
+    else
+      launch_restrict(m->lg[l + 1], rb, rt, mask, C.b, s, m->dim, co);
   } else {
     HIP_TRY(hipMemsetAsync(x, 0, n3 * sizeof(double), s));
     HIP_TRY(hipMemsetAsync(L.t, 0, n3 * sizeof(double), s));
@@ -790,16 +891,9 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
       continue;
     }
     if (fuse && l >= 1 && it == m->p.nu_post - 1) {
-      if (l == 1) {
-        TRY(flagged_count(m, s));
-        launch_apply_l1_jacobi(m->lg[1], L.Ke, m->Kcomp1, m->cap1, m->Bwd, m->E, m->eflag1,
-                               m->list1, m->count1, m->nflag1, x, m->Y1, b, L.dinv, om, s);
-      } else {
-        if (x != L.x) return fail(AARMR_E_STATE, "V-cycle iterate is not the level's buffer");
-        launch_apply_elemmat_jacobi(G, L.Ke, x, b, L.dinv, om, L.t, s);
-        std::swap(L.x, L.t);
-      }
-      KCHECK();
+      if (x != L.x) return fail(AARMR_E_STATE, "V-cycle iterate is not the level's buffer");
+      TRY(level_product(m, l, 1, x, L.t, b, s));
+      std::swap(L.x, L.t);
       continue;
     }
     TRY(apply(m, l, x, L.t, s));
@@ -874,36 +968,24 @@ int build_mg(aarmr_mesh* m, hipStream_t s) {
   }
   launch_diag_fine(g, m->KEd, m->E, m->mask, m->lv[0].dinv, m->lv[0].dinv32, s);
   KCHECK();
-  // Below a coarser level, the level-1 matrices of parents without a fixed
-  // fine DOF are never stored: the level-1 product forms them from the moduli,
-  // the level-1 diagonal and the level-2 Galerkin matrices come from the
-  // moduli too.  Only as the coarsest level are they assembled.
-  const bool l1_all = m->nlev == 2;
+  launch_level_lists(m->lt, m->mask, s);
+  KCHECK();
+  // the special-node counts size the products' launches: fetched without a
+  // stall, read at the first coarse product
+  HIP_TRY(hipMemcpyAsync(m->hpin + 72, m->lt.counts, 2 * m->nlev * sizeof(int),
+                         hipMemcpyDeviceToHost, s));
+  m->counts_ready = false;
   for (int l = 1; l < m->nlev; ++l) {
-    if (l == 1) {
-      launch_galerkin_from_fine(m->lg[1], m->KEd, m->Mcd, m->E, m->mask, m->eflag1, m->list1,
-                                m->count1, m->lv[1].Ke, m->Kcomp1, m->cap1, s, l1_all);
-      KCHECK();
-      // the flagged count sizes the level-1 launches: fetched without a
-      // stall, read at the first level-1 product (nflag1 < 0 until then)
-      HIP_TRY(hipMemcpyAsync(m->hpin + 72, m->count1, sizeof(int), hipMemcpyDeviceToHost, s));
-      m->nflag1 = -1;
-    } else {
-      if (l == 2)
-        launch_galerkin_l2_from_fine(m->lg[2], m->N2d, m->Mcd, m->E, m->eflag1, m->list2,
-                                     m->count2, m->lv[1].Ke, m->lv[2].Ke, s);
-      else
-        launch_galerkin_from_coarse(m->lg[l], m->lv[l - 1].Ke, m->lv[l].Ke, s);
-      if (m->fp32 && l < m->nlev - 1)  // the FP32 V-cycle's copy (the coarsest uses its inverse)
-        launch_to_f32(m->lg[l].ne * kSymEntries, m->lv[l].Ke, m->lv[l].Ke32, s);
-    }
+    if (l >= 2 && l < m->nlev - 1) launch_level_moments(m->lg[l], l, m->E, m->lt.mom[l - 1], m->lt.mom[l], s);
+    launch_level_store(m->lt, l, m->wk, m->E, m->mask, s);
     KCHECK();
+    if (m->lv[l].Ke32) {
+      launch_elemmat_f32(m->lg[l], m->Cmd[l], m->lt.mom[l], m->lt.Kst[l], m->lt.elist[l],
+                         m->lt.counts + 2 * l, m->lv[l].Ke32, s);
+      KCHECK();
+    }
     if (l < m->nlev - 1) {
-      if (l == 1)
-        launch_diag_l1(m->lg[1], m->lv[1].Ke, m->Mcd, m->E, m->eflag1, m->lv[1].dinv,
-                       m->lv[1].dinv32, s);
-      else
-        launch_diag_elemmat(m->lg[l], m->lv[l].Ke, m->lv[l].dinv, m->lv[l].dinv32, s);
+      launch_level_diag(m->lt, l, m->wk, m->E, m->lv[l].dinv, m->lv[l].dinv32, s);
       KCHECK();
     }
   }
@@ -953,12 +1035,8 @@ int apply32(aarmr_mesh* m, int l, const float* v, float* y, hipStream_t s, int n
   if (l == 0) {
     launch_ebe_f32(m->lg[0], m->wk, m->E32, m->mask, v, y, 2, s, m->tz32, nr);
     ++m->sweeps;
-  } else if (l == 1) {
-    TRY(flagged_count(m, s));
-    launch_apply_l1_f32(m->lg[1], m->lv[1].Ke, m->Kcomp1, m->cap1, m->Bw32d, m->E32,
-                        m->eflag1, m->list1, m->count1, m->nflag1, v, m->Y1f, y, s, nr);
   } else {
-    launch_apply_elemmat_f32(m->lg[l], m->lv[l].Ke32, v, y, s, nr);
+    return level_product32(m, l, 0, v, y, nullptr, s, nr);
   }
   KCHECK();
   return AARMR_OK;
@@ -994,12 +1072,17 @@ int vcycle32(aarmr_mesh* m, int l, const float* b, float* x, hipStream_t s,
       launch_jacobi_update_f32(n3, b, L.t32, L.dinv32, om, x, s, nr);
       KCHECK();
     }
-    TRY(apply32(m, l, x, L.t32, s, nr));
-    if (child_first)
-      launch_restrict_jacobi_f32(m->lg[l + 1], b, L.t32, mask, C.b32, C.dinv32, om, C.x32, s,
-                                 nr);
+    const bool res = l >= 1;  // L.t32 holds b - A x, not A x
+    if (res)
+      TRY(level_product32(m, l, 2, x, L.t32, b, s, nr));
     else
-      launch_restrict_f32(m->lg[l + 1], b, L.t32, mask, C.b32, s, nr, co);
+      TRY(apply32(m, l, x, L.t32, s, nr));
+    const float* rb = res ? L.t32 : b;
+    const float* rt = res ? nullptr : L.t32;
+    if (child_first)
+      launch_restrict_jacobi_f32(m->lg[l + 1], rb, rt, mask, C.b32, C.dinv32, om, C.x32, s, nr);
+    else
+      launch_restrict_f32(m->lg[l + 1], rb, rt, mask, C.b32, s, nr, co);
   } else {
     HIP_TRY(hipMemsetAsync(x, 0, nr * n3 * sizeof(float), s));
     launch_restrict_f32(m->lg[l + 1], b, nullptr, mask, C.b32, s, nr, co);
@@ -1021,17 +1104,9 @@ int vcycle32(aarmr_mesh* m, int l, const float* b, float* x, hipStream_t s,
       continue;
     }
     if (l >= 1 && last) {
-      if (l == 1) {
-        TRY(flagged_count(m, s));
-        launch_apply_l1_jacobi_f32(m->lg[1], L.Ke, m->Kcomp1, m->cap1, m->Bw32d, m->E32,
-                                   m->eflag1, m->list1, m->count1, m->nflag1, x, m->Y1f, b,
-                                   L.dinv32, om, s, nr);
-      } else {
-        if (x != L.x32) return fail(AARMR_E_STATE, "V-cycle iterate is not the level's buffer");
-        launch_apply_elemmat_jacobi_f32(G, L.Ke32, x, b, L.dinv32, om, L.t32, s, nr);
-        std::swap(L.x32, L.t32);
-      }
-      KCHECK();
+      if (x != L.x32) return fail(AARMR_E_STATE, "V-cycle iterate is not the level's buffer");
+      TRY(level_product32(m, l, 1, x, L.t32, b, s, nr));
+      std::swap(L.x32, L.t32);
       continue;
     }
     TRY(apply32(m, l, x, L.t32, s, nr));
@@ -1748,24 +1823,30 @@ int aarmr_mesh_create(const aarmr_params* p, aarmr_mesh** out) {
     return AARMR_OK;
   }
   hex8_stiffness(p->nu, m->KE);  // unit modulus; E0 enters through SIMP
-  child_galerkin(m->KE, m->Mc);
-  m->N2.resize(64 * kSymEntries);
-  grandchild_galerkin(m->Mc, m->N2.data());
-  walsh_child(m->Mc, m->Bw);
-  for (int x = 0; x < 576; ++x) m->Bw32[x] = (float)m->Bw[x];
-  if (!walsh_parent_check(m->Mc, m->Bw)) {
-    delete m;
-    return fail(AARMR_E_INVALID, "Walsh form of the level-1 operator does not reproduce it");
-  }
   m->fp32 = (p->precision == AARMR_FP32_REFINE);
-  if (!mirror_children(m->Mc)) {
-    delete m;
-    return fail(AARMR_E_INVALID, "child Galerkin matrices are not mirror images of child 0's");
+  if (m->fp32) {
+    double Mc[8 * kSymEntries], Bw[576];  // P_c^T KE P_c per child position; W M_0 W / 64
+    child_galerkin(m->KE, Mc);
+    walsh_child(Mc, Bw);
+    for (int x = 0; x < 576; ++x) m->Bw32[x] = (float)Bw[x];
+    if (!walsh_parent_check(Mc, Bw) || !mirror_children(Mc)) {
+      delete m;
+      return fail(AARMR_E_INVALID, "Walsh form of the level-1 operator does not reproduce it");
+    }
   }
   if (!walsh_form(m->KE, &m->wk)) {
     delete m;
     return fail(AARMR_E_INVALID, "element stiffness lacks the reflection-blocked structure");
   }
+  if (!moment_check(m->KE, m->wk)) {
+    delete m;
+    return fail(AARMR_E_INVALID, "moment form of the coarse operators does not reproduce them");
+  }
+  if (m->fp32)
+    for (int l = 2; l < m->nlev - 1; ++l) {
+      m->Cm[l].resize(28 * kSymEntries);
+      moment_matrices(m->wk, l, m->Cm[l].data());
+    }
   *out = m;
   return AARMR_OK;
 }
@@ -1816,17 +1897,14 @@ int aarmr_bind_workspace(aarmr_mesh* m, void* dev_ptr, int64_t bytes, void* stre
   layout(m, m->ws);
   hipStream_t s = S(stream);
   HIP_TRY(hipMemcpyAsync(m->KEd, m->KE, 576 * sizeof(double), hipMemcpyHostToDevice, s));
-  if (m->dim == 3) {
-    HIP_TRY(hipMemcpyAsync(m->Mcd, m->Mc, 8 * kSymEntries * sizeof(double), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(m->N2d, m->N2.data(), 64 * kSymEntries * sizeof(double),
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(m->Bwd, m->Bw, 576 * sizeof(double), hipMemcpyHostToDevice, s));
+  if (m->fp32) {
+    HIP_TRY(hipMemcpyAsync(m->Bw32d, m->Bw32, 576 * sizeof(float), hipMemcpyHostToDevice, s));
+    for (int l = 2; l < m->nlev - 1; ++l)
+      HIP_TRY(hipMemcpyAsync(m->Cmd[l], m->Cm[l].data(), m->Cm[l].size() * sizeof(double),
+                             hipMemcpyHostToDevice, s));
   }
   HIP_TRY(hipMemcpyAsync(m->tasksd, m->plan.tasks.data(), m->plan.tasks.size() * sizeof(InvTask),
                          hipMemcpyHostToDevice, s));
-  if (m->fp32) {
-    HIP_TRY(hipMemcpyAsync(m->Bw32d, m->Bw32, 576 * sizeof(float), hipMemcpyHostToDevice, s));
-  }
   HIP_TRY(hipMemsetAsync(m->flags, 0, 64, s));
   HIP_TRY(hipMemsetAsync(m->mask, 0, (m->lg[0].nn + 3) / 4 * 4, s));
   launch_fill(m->lg[0].ne, 1.0, m->ones_dv, s);

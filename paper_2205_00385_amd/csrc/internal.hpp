@@ -116,62 +116,74 @@ void launch_dc_accum(int64_t ne, const double* rho, const double* energy, double
                      double p, double* dc, int first, hipStream_t s);
 
 // ---- multigrid ------------------------------------------------------------
-// Coarse element matrices are symmetric 24x24 and stored packed (upper
-// triangle, row-major: 300 entries) and entry-major, Ke[sym_index(r,c) *
-// n_elem + e], so that threads on consecutive elements read consecutive
-// addresses.
+// Stored element matrices are symmetric 24x24, packed (upper triangle,
+// row-major: 300 entries) and entry-major, K[sym_index(r,c) * n_elem + w], w an
+// element's place in its level's list of stored elements (kernels_level.hip).
 constexpr int kSymEntries = 300;
 __host__ __device__ constexpr int sym_index(int r, int c) {
   return r <= c ? r * 24 - (r * (r - 1)) / 2 + (c - r) : c * 24 - (c * (c - 1)) / 2 + (r - c);
 }
-// Level-1 operators from the fine moduli: fast path for every parent, exact
-// masked product for the parents flagged in eflag (1 = touches a fixed DOF),
-// whose indices are listed in list[0..*count); list entries w < cap are also
-// stored compactly, Kcomp[entry][w].
-// all: also the fast-path matrices of the unflagged parents (needed only when
-// level 1 is the coarsest; otherwise nothing reads them).
-void launch_galerkin_from_fine(const Grid& coarse, const double* KE, const double* Mc,
-                               const double* E, const uint8_t* mask, uint8_t* eflag, int* list,
-                               int* count, double* Kc, double* Kcomp, int cap, hipStream_t s,
-                               bool all);
-// Level-2 Galerkin matrices from the fine moduli (N2: [64][300] descendant
-// matrices) for parents without a flagged level-1 child; the others from the
-// stored flagged level-1 matrices K1 and the moduli.  list2/count2: scratch.
-void launch_galerkin_l2_from_fine(const Grid& l2, const double* N2, const double* Mc,
-                                  const double* E, const uint8_t* eflag1, int* list2, int* count2,
-                                  const double* K1, double* K2, hipStream_t s);
-// Level-1 inverse Jacobi diagonal from the moduli (unflagged parents) and the
-// stored matrices (flagged ones).
-void launch_diag_l1(const Grid& g, const double* Ke, const double* Mc, const double* E,
-                    const uint8_t* eflag, double* dinv, float* dinv32, hipStream_t s);
-void launch_galerkin_from_coarse(const Grid& coarse, const double* Kf, double* Kc, hipStream_t s);
-void launch_apply_elemmat(const Grid& g, const double* Ke, const double* v, double* y,
+// The coarse levels' buffers (index 0 unused, null).
+struct LevelTable {
+  int nlev = 0;
+  int nx[AARMR_MAX_LEVELS] = {}, ny[AARMR_MAX_LEVELS] = {}, nz[AARMR_MAX_LEVELS] = {};
+  int ne[AARMR_MAX_LEVELS] = {}, nn[AARMR_MAX_LEVELS] = {};
+  uint8_t* eflag[AARMR_MAX_LEVELS] = {};    // [ne] 1: contains a fixed fine DOF
+  uint8_t* special[AARMR_MAX_LEVELS] = {};  // [nn] 1: node of a flagged element
+  int* eidx[AARMR_MAX_LEVELS] = {};         // [ne] place in the list of stored elements, or -1
+  int* elist[AARMR_MAX_LEVELS] = {};        // [ne] stored elements: those with a special node
+  int* nlist[AARMR_MAX_LEVELS] = {};        // [nn] special nodes
+  int* corner[AARMR_MAX_LEVELS] = {};       // [8][nn] stored elements around the special nodes
+  double* mom[AARMR_MAX_LEVELS] = {};       // levels >= 2: [27][ne] moments of the moduli
+  double* Kst[AARMR_MAX_LEVELS] = {};       // [300][ne] stored matrices
+  int* part = nullptr;                      // level_list_blocks() counts
+  int* counts = nullptr;                    // [2 level]: stored elements, [2 level + 1]: special nodes
+};
+// What one level's product reads; nspecial as read back by the host.
+struct LevelArgs {
+  int level, nx, ny, nz, nspecial;
+  double gam;  // 2^-level
+  const double* mom;
+  const uint8_t* special;
+  const int* nlist;
+  const int* corner;
+  const double* Kst;
+};
+int64_t level_list_blocks(const Grid* lg, int nlev);
+// Flags, lists and special nodes of every level >= 1 from the fine mask.
+void launch_level_lists(const LevelTable& T, const uint8_t* mask, hipStream_t s);
+// Moments of a level >= 2: from the fine moduli (2) or from the level above.
+void launch_level_moments(const Grid& g, int level, const double* E, const double* child, double* mom,
                           hipStream_t s);
-// Level-1 product through the Walsh form of the child matrices:
-// Bw = W M_0 W / 64 (24 x 24, Walsh x component basis, index 3k + s), Y a
-// [24][ne] element-product buffer.  Flagged parents (eflag 1, indices in
-// list[0..*count), nflag = *count as read back by the host) use their stored Ke.
-void launch_apply_l1(const Grid& g, const double* Ke, const double* Kcomp, int cap,
-                     const double* Bw, const double* Ef, const uint8_t* eflag, const int* list,
-                     const int* count, int nflag, const double* v, double* Y, double* y,
-                     hipStream_t s);
-// FP32 forms of the Jacobi-fused products and restriction (as the FP64 ones).
-void launch_apply_l1_jacobi_f32(const Grid& g, const double* Ke, const double* Kcomp, int cap,
-                                const float* Bw, const float* Ef, const uint8_t* eflag,
-                                const int* list, const int* count, int nflag, float* x, float* Y,
-                                const float* b, const float* dinv, float omega, hipStream_t s, int nr = 1);
-void launch_apply_elemmat_jacobi_f32(const Grid& g, const float* Ke, const float* v,
-                                     const float* b, const float* dinv, float omega, float* out,
-                                     hipStream_t s, int nr = 1);
+// Matrices of the listed elements; level l - 1 done before level l.
+void launch_level_store(const LevelTable& T, int level, const WalshConsts& K, const double* E,
+                        const uint8_t* mask, hipStream_t s);
+void launch_level_diag(const LevelTable& T, int level, const WalshConsts& K, const double* E,
+                       double* dinv, float* dinv32, hipStream_t s);
+// mode 0: y = A v; 1: y = v + omega jd (jb - A v); 2: y = jb - A v.  y distinct
+// from v.  E: the fine moduli (level 1).
+void launch_level_product(const LevelArgs& L, const WalshConsts& K, const double* E, int mode,
+                          const double* v, double* y, const double* jb, const double* jd,
+                          double omega, hipStream_t s);
+// FP32 products of the refinement form (kernels_l32.hip), modes as above; nr
+// load cases one after another.  Level 1: Bw = W M_0 W / 64 (24 x 24, M_0 child
+// 0's Galerkin matrix, Walsh x component basis, index 3k + s), Y a [24][ne]
+// element-product buffer per load case, nlist the stored elements as read back
+// by the host.  Levels >= 2: element matrices Ke, made by launch_elemmat_f32
+// from the moments (C: [300][28], the matrix per unit moment) and the stored
+// matrices.
+void launch_elemmat_f32(const Grid& g, const double* C, const double* mom, const double* Kst,
+                        const int* list, const int* count, float* K, hipStream_t s);
+void launch_apply_elemmat_f32(const Grid& g, const float* Ke, int mode, const float* v, float* y,
+                              const float* jb, const float* jd, float omega, int nr,
+                              hipStream_t s);
+void launch_apply_l1_f32(const Grid& g, const double* Kst, const float* Bw, const float* Ef,
+                         const uint8_t* eflag, const int* list, int nlist, int mode,
+                         const float* v, float* Y, float* y, const float* jb, const float* jd,
+                         float omega, int nr, hipStream_t s);
 void launch_restrict_jacobi_f32(const Grid& coarse, const float* bf, const float* tf,
                                 const uint8_t* mask, float* bc, const float* dinv_c, float omega,
                                 float* xc, hipStream_t s, int nr = 1);
-void launch_apply_l1_f32(const Grid& g, const double* Ke, const double* Kcomp, int cap,
-                         const float* Bw, const float* Ef, const uint8_t* eflag, const int* list,
-                         const int* count, int nflag, const float* v, float* Y, float* y,
-                         hipStream_t s, int nr = 1);
-void launch_diag_elemmat(const Grid& g, const double* Ke, double* dinv, float* dinv32,
-                         hipStream_t s);
 // Transfers act per component; ncomp = 2 on the plane-stress grid (nz = 0).
 // o: the coarse vector's order (null: [component][node]), set where the coarse
 // level is the coarsest.
@@ -181,19 +193,11 @@ void launch_prolong_add(const Grid& fine, const double* xc, const uint8_t* mask,
                         hipStream_t s, int ncomp = 3, const CoarseOrder* o = nullptr);
 void launch_jacobi_first(int64_t n3, const double* b, const double* dinv, double omega, double* x,
                          hipStream_t s);
-// Fused damped-Jacobi sweeps (3D hierarchy): restriction that also forms the
-// coarse level's first sweep xc = omega dinv_c bc; the level-1 product that
-// ends in x += omega dinv (b - A x) in place; the stored-matrix product that
-// writes out = v + omega dinv (b - A v) (out distinct from v).
+// The restriction that also forms the coarse level's first damped-Jacobi sweep
+// xc = omega dinv_c bc.
 void launch_restrict_jacobi(const Grid& coarse, const double* bf, const double* tf,
                             const uint8_t* mask, double* bc, const double* dinv_c, double omega,
                             double* xc, hipStream_t s);
-void launch_apply_l1_jacobi(const Grid& g, const double* Ke, const double* Kcomp, int cap,
-                            const double* Bw, const double* Ef, const uint8_t* eflag,
-                            const int* list, const int* count, int nflag, double* x, double* Y,
-                            const double* b, const double* dinv, double omega, hipStream_t s);
-void launch_apply_elemmat_jacobi(const Grid& g, const double* Ke, const double* v, const double* b,
-                                 const double* dinv, double omega, double* out, hipStream_t s);
 void launch_jacobi_update(int64_t n3, const double* b, const double* t, const double* dinv,
                           double omega, double* x, hipStream_t s);
 // The dense coarsest operator with its unknowns in the order o, and its
@@ -205,10 +209,8 @@ int64_t inv_scratch_doubles(const InvPlan& plan);
 void launch_invert(const InvPlan& plan, const InvTask* tasks, double* A, double* scratch,
                    hipStream_t s);
 void launch_gemv(int n, const double* A, const double* x, double* y, hipStream_t s);
-// FP32 V-cycle pieces (vectors FP32; element matrices and the coarsest
+// FP32 V-cycle pieces (vectors FP32; moments, stored matrices and the coarsest
 // inverse stay FP64 and are applied with FP32 vectors).
-void launch_apply_elemmat_f32(const Grid& g, const float* Ke, const float* v, float* y,
-                              hipStream_t s, int nr = 1);
 void launch_restrict_f32(const Grid& coarse, const float* bf, const float* tf,
                          const uint8_t* mask, float* bc, hipStream_t s, int nr = 1,
                          const CoarseOrder* o = nullptr);
@@ -228,8 +230,6 @@ void launch_multidot_f32(const DotSetT<float>& d, const RedScratch& rs, hipStrea
 void launch_cg_p_f32(int64_t n, const double* rz_new, const double* rz_old, const float* z,
                      float* p, hipStream_t s);
 // Refinement transfers: dst32 = src64 / sqrt(*nrm2);  x64 += sqrt(*nrm2) d32.
-// dst = (float)src, elementwise.
-void launch_to_f32(int64_t n, const double* src, float* dst, hipStream_t s);
 void launch_to_f32_scaled(int64_t n, const double* src, const double* nrm2, float* dst,
                           hipStream_t s);
 void launch_add_scaled_f32(int64_t n, const float* d, const double* nrm2, double* x,
