@@ -33,6 +33,11 @@ __device__ __forceinline__ int xcd_slot(int w, int total) {
 // mask == nullptr: no fine fixed DOFs.
 // With xc non-null also the coarse level's first Jacobi sweep from zero,
 // xc = omega dc bc.  o: the order of the coarse vector.
+// These levels are bound by latency, not by bytes: a thread issues its nine
+// (with tf eighteen) values, the masks and dc at once, at clamped indexes
+// whose terms are left out of the sum by a select, and node numbers are
+// divided in 32 bits (average over the levels: 24x12x12, FP64 5.0 -> 3.4 us;
+// 96x48x48, FP64 6.9 -> 4.5 us; 56x40x64 x 4, FP32 8.8 -> 6.9 us).
 template <typename T>
 __global__ void __launch_bounds__(192) k_restrict(int cnx, int cny, int cnz,
                                                   const T* __restrict__ bf,
@@ -43,54 +48,66 @@ __global__ void __launch_bounds__(192) k_restrict(int cnx, int cny, int cnz,
                                                   T* __restrict__ xc, CoarseOrder o,
                                                   int64_t fs = 0, int64_t cs = 0) {
   __shared__ T part[3][64];
-  {  // load case blockIdx.z (fs, cs: fine and coarse vector strides)
-    const int64_t fo = (int64_t)blockIdx.z * fs, co = (int64_t)blockIdx.z * cs;
+  const int lane = threadIdx.x & 63, dzi = threadIdx.x >> 6;
+  const int c = blockIdx.y;
+  const uint32_t cxp = cnx + 1, cyp = cny + 1, cnn = cxp * cyp * (cnz + 1);
+  const uint32_t fxp = 2 * cnx + 1, fyp = 2 * cny + 1;
+  const int fnz = 2 * cnz;
+  {  // load case blockIdx.z (fs, cs: fine and coarse vector strides), component c
+    const int64_t fnn = (int64_t)fxp * fyp * (fnz + 1);
+    const int64_t fo = (int64_t)blockIdx.z * fs + c * fnn, co = (int64_t)blockIdx.z * cs;
     bf += fo;
     if (tf) tf += fo;
     bc += co;
     if (xc) xc += co;
   }
-  const int lane = threadIdx.x & 63, dzi = threadIdx.x >> 6;
-  const int c = blockIdx.y;
-  const int64_t cnn = (int64_t)(cnx + 1) * (cny + 1) * (cnz + 1);
-  const int64_t n = (int64_t)blockIdx.x * 64 + lane;
-  const int fnx = 2 * cnx, fny = 2 * cny, fnz = 2 * cnz;
-  const int64_t fnn = (int64_t)(fnx + 1) * (fny + 1) * (fnz + 1);
+  const uint32_t n = blockIdx.x * 64 + lane, nc = n < cnn ? n : cnn - 1;
+  const uint32_t rest = nc / cxp, K = rest / cyp;
+  const int I = (int)(nc - rest * cxp), J = (int)(rest - K * cyp);
+  const int dst = c * o.sc + I * o.si + J * o.sj + (int)K * o.sk;
+  const int fk = 2 * (int)K + dzi - 1;
+  const bool zok = fk >= 0 && fk <= fnz;
+  const T d = (xc && dzi == 0) ? dc[dst] : T(0);
+  uint32_t f[9];
+  T val[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const int fi = min(max(2 * I + q % 3 - 1, 0), (int)fxp - 1);
+    const int fj = min(max(2 * J + q / 3 - 1, 0), (int)fyp - 1);
+    f[q] = (uint32_t)fi + fxp * ((uint32_t)fj + fyp * (uint32_t)(zok ? fk : 0));
+    val[q] = bf[f[q]];
+  }
+  uint32_t fixed = 0;  // bit q: node q's DOF is fixed
+  if (mask) {
+    uint32_t m[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) m[q] = mask[f[q]];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) fixed |= ((m[q] >> c) & 1u) << q;
+  }
+  if (tf) {
+    T t[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) t[q] = tf[f[q]];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) val[q] -= t[q];
+  }
   T acc = 0;
-  int dst = 0;
-  if (n < cnn) {
-    const int I = (int)(n % (cnx + 1));
-    const int64_t rest = n / (cnx + 1);
-    const int J = (int)(rest % (cny + 1));
-    const int K = (int)(rest / (cny + 1));
-    dst = c * o.sc + I * o.si + J * o.sj + K * o.sk;
-    const int fk = 2 * K + dzi - 1;
-    if (fk >= 0 && fk <= fnz) {
-      const T wz = dzi == 1 ? T(1) : T(0.5);
+  const T wz = dzi == 1 ? T(1) : T(0.5);
 #pragma unroll
-      for (int dy = -1; dy <= 1; ++dy) {
-        const int fj = 2 * J + dy;
-        if (fj < 0 || fj > fny) continue;
-        const T wyz = (dy ? T(0.5) : T(1)) * wz;
-#pragma unroll
-        for (int dx = -1; dx <= 1; ++dx) {
-          const int fi = 2 * I + dx;
-          if (fi < 0 || fi > fnx) continue;
-          const T w = (dx ? T(0.5) : T(1)) * wyz;
-          const int64_t f = node_of(fnx, fny, fi, fj, fk);
-          const bool fixed = mask && ((mask[f] >> c) & 1);
-          const T val = tf ? bf[c * fnn + f] - tf[c * fnn + f] : bf[c * fnn + f];
-          if (!fixed) acc = fma(w, val, acc);
-        }
-      }
-    }
+  for (int q = 0; q < 9; ++q) {
+    const int fi = 2 * I + q % 3 - 1, fj = 2 * J + q / 3 - 1;
+    const T w = (q % 3 != 1 ? T(0.5) : T(1)) * ((q / 3 != 1 ? T(0.5) : T(1)) * wz);
+    const bool use = zok && fi >= 0 && fi < (int)fxp && fj >= 0 && fj < (int)fyp &&
+                     !((fixed >> q) & 1u);
+    acc = use ? fma(w, val[q], acc) : acc;
   }
   part[dzi][lane] = acc;
   __syncthreads();
   if (dzi == 0 && n < cnn) {
     const T v = part[0][lane] + part[1][lane] + part[2][lane];
     bc[dst] = v;
-    if (xc) xc[dst] = omega * dc[dst] * v;
+    if (xc) xc[dst] = omega * d * v;
   }
 }
 
@@ -244,49 +261,48 @@ __global__ void __launch_bounds__(64 * kRmWaves) k_restrict_zm(
   }
 }
 
-// xf += Df P xc: thread per fine node, branch-free over the (up to) 8
-// parent nodes: along an axis an even fine index takes its parent with
-// weight 1, an odd one both neighbours with weight 1/2.  On the plane grid
-// (fnz = 0) the z pair is (0, 0) with weights (1, 0) and ncomp = 2.  o: the
-// order of the coarse vector.
-template <typename T>
+// xf += Df P xc: thread per fine node and NC components (from NC grid.y on),
+// branch-free over the (up to) 8 parent nodes: along an axis an even fine index takes its
+// parent with weight 1, an odd one both neighbours with weight 1/2.  On the
+// plane grid (fnz = 0) the z pair is (0, 0) with weights (1, 0).  o: the
+// order of the coarse vector.  As in k_restrict every load is issued before
+// the first is used, and the indexes are 32-bit.
+template <typename T, int NC>
 __global__ void __launch_bounds__(256) k_prolong_add(int fnx, int fny, int fnz,
                                                      const T* __restrict__ xc,
                                                      const uint8_t* __restrict__ mask,
-                                                     T* __restrict__ xf, int ncomp,
-                                                     CoarseOrder o, int64_t cs = 0,
-                                                     int64_t fs = 0) {
-  xc += (int64_t)blockIdx.z * cs;  // load case blockIdx.z
-  xf += (int64_t)blockIdx.z * fs;
-  const int64_t fnn = (int64_t)(fnx + 1) * (fny + 1) * (fnz + 1);
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                     T* __restrict__ xf, CoarseOrder o,
+                                                     int64_t cs = 0, int64_t fs = 0) {
+  const int c0 = blockIdx.y * NC;
+  const uint32_t fxp = fnx + 1, fyp = fny + 1, fnn = fxp * fyp * (fnz + 1);
+  const uint32_t n = blockIdx.x * 256 + threadIdx.x;
   if (n >= fnn) return;
-  const int fi = (int)(n % (fnx + 1));
-  const int64_t rest = n / (fnx + 1);
-  const int fj = (int)(rest % (fny + 1));
-  const int fk = (int)(rest / (fny + 1));
+  xc += (int64_t)blockIdx.z * cs + (int64_t)c0 * o.sc;  // load case blockIdx.z
+  xf += (int64_t)blockIdx.z * fs + (int64_t)c0 * fnn;
+  T old[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) old[c] = xf[(int64_t)c * fnn + n];
+  const uint32_t m = mask ? mask[n] : 0u;
+  const uint32_t rest = n / fxp, fk = rest / fyp;
+  const int fi = (int)(n - rest * fxp), fj = (int)(rest - fk * fyp);
   const int ix[2] = {fi >> 1, (fi + 1) >> 1};
   const int iy[2] = {fj >> 1, (fj + 1) >> 1};
-  const int iz[2] = {fk >> 1, (fk + 1) >> 1};
+  const int iz[2] = {(int)fk >> 1, ((int)fk + 1) >> 1};
   const T wx[2] = {(fi & 1) ? T(0.5) : T(1), (fi & 1) ? T(0.5) : T(0)};
   const T wy[2] = {(fj & 1) ? T(0.5) : T(1), (fj & 1) ? T(0.5) : T(0)};
   const T wz[2] = {(fk & 1) ? T(0.5) : T(1), (fk & 1) ? T(0.5) : T(0)};
-  int id[8];
-  T w[8];
+  T x[NC][8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    id[q] = ix[q & 1] * o.si + iy[(q >> 1) & 1] * o.sj + iz[q >> 2] * o.sk;
-    w[q] = wx[q & 1] * wy[(q >> 1) & 1] * wz[q >> 2];
-  }
-  const uint8_t m = mask ? mask[n] : 0;
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (c >= ncomp) break;
-    const T* x = xc + c * o.sc;
+    for (int q = 0; q < 8; ++q)
+      x[c][q] = xc[c * o.sc + ix[q & 1] * o.si + iy[(q >> 1) & 1] * o.sj + iz[q >> 2] * o.sk];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
     T s = 0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) s = fma(w[q], x[id[q]], s);
-    if (!((m >> c) & 1)) xf[c * fnn + n] += s;
+    for (int q = 0; q < 8; ++q) s = fma(wx[q & 1] * wy[(q >> 1) & 1] * wz[q >> 2], x[c][q], s);
+    if (!((m >> (c0 + c)) & 1u)) xf[(int64_t)c * fnn + n] = old[c] + s;
   }
 }
 
@@ -517,16 +533,35 @@ static void prolong_z(const Grid& fine, const T* xc, const uint8_t* mask, T* xf,
       fine.nx, fine.ny, fine.nz, gx, xc, mask, xf, cs, fs);
 }
 
+// The per-node kernel: one component per thread where three would leave
+// compute units without a workgroup (25x13x13 nodes, FP64: 4.2 -> 3.2 us),
+// all three from one workgroup per compute unit up, where the shared index
+// work and masks count (97x49x49 nodes, FP64: 6.6 against 7.4 us; 57x41x65
+// nodes x 4, FP32: 6.6 against 8 us).
+constexpr int64_t kPnBlocks = 256;
+template <typename T>
+static void prolong_nodes(const Grid& fine, const T* xc, const uint8_t* mask, T* xf, int ncomp,
+                          const CoarseOrder* o, hipStream_t s, int nr) {
+  const Grid cg = make_grid(fine.nx / 2, fine.ny / 2, fine.nz / 2);
+  const CoarseOrder co = o ? *o : natural(cg);
+  const unsigned nb = nblk(fine.nn, 256);
+  const int64_t cs = ncomp * cg.nn, fs = ncomp * fine.nn;
+  if (ncomp == 3 && (int64_t)nb * nr >= kPnBlocks)
+    k_prolong_add<T, 3><<<dim3(nb, 1, nr), 256, 0, s>>>(fine.nx, fine.ny, fine.nz, xc, mask, xf,
+                                                        co, cs, fs);
+  else
+    k_prolong_add<T, 1><<<dim3(nb, ncomp, nr), 256, 0, s>>>(fine.nx, fine.ny, fine.nz, xc, mask,
+                                                            xf, co, cs, fs);
+}
+
 void launch_prolong_add_f32(const Grid& fine, const float* xc, const uint8_t* mask, float* xf,
                             hipStream_t s, int nr, const CoarseOrder* o) {
-  const Grid cg = make_grid(fine.nx / 2, fine.ny / 2, fine.nz / 2);
-  const int64_t cnn = cg.nn;
   if (!o && fine.nz > 0 && fine.nn >= kPzMinNodes) {
+    const int64_t cnn = make_grid(fine.nx / 2, fine.ny / 2, fine.nz / 2).nn;
     prolong_z<float>(fine, xc, mask, xf, s, nr, 3 * cnn, 3 * fine.nn);
     return;
   }
-  k_prolong_add<float><<<dim3(nblk(fine.nn, 256), 1, nr), 256, 0, s>>>(
-      fine.nx, fine.ny, fine.nz, xc, mask, xf, 3, o ? *o : natural(cg), 3 * cnn, 3 * fine.nn);
+  prolong_nodes<float>(fine, xc, mask, xf, 3, o, s, nr);
 }
 
 void launch_jacobi_first_f32(int64_t n3, const float* b, const float* dinv, float omega, float* x,
@@ -572,9 +607,7 @@ void launch_prolong_add(const Grid& fine, const double* xc, const uint8_t* mask,
     prolong_z<double>(fine, xc, mask, xf, s, 1, 0, 0);
     return;
   }
-  k_prolong_add<double><<<nblk(fine.nn, 256), 256, 0, s>>>(
-      fine.nx, fine.ny, fine.nz, xc, mask, xf, ncomp,
-      o ? *o : natural(make_grid(fine.nx / 2, fine.ny / 2, fine.nz / 2)));
+  prolong_nodes<double>(fine, xc, mask, xf, ncomp, o, s, 1);
 }
 
 void launch_jacobi_first(int64_t n3, const double* b, const double* dinv, double omega, double* x,
