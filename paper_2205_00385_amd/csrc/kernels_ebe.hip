@@ -24,6 +24,8 @@
 // double-buffered LDS exchange per layer.  The next node plane is loaded
 // while the current one is processed.  No atomics: every node is
 // written once by its owner, so results are deterministic.
+#include <algorithm>
+
 #include "internal.hpp"
 #include "walsh.hpp"
 
@@ -78,7 +80,7 @@ constexpr uint32_t kOutside = 0x80000000u;
 // 32-lane rows: a row segment of y is 30 nodes, so per owned node half as
 // many cache lines are shared with the neighbouring tile as with 16 lanes.
 // A workgroup has ROWS x-rows (2 per wavefront) and owns ROWS - 1 node rows;
-// ROWS is one of {8, 12, 16} (ebe_rows below).
+// ROWS is one of {8, 12, 16} (ebe_shape below).
 constexpr int kLanes = 32;           // element columns per x-row
 constexpr int kTileX = kLanes - 2;   // node columns owned per row
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit dwords (gfx9)
@@ -413,11 +415,6 @@ __global__ void k_identity_rows(int64_t nn, const uint8_t* __restrict__ mask,
     if ((m >> c) & 1u) y[c * nn + n] = v[c * nn + n];
 }
 
-// z-chunk of node planes per workgroup.  A chunk costs one extra element
-// layer (the carry is primed from the layer below it); the length is chosen
-// by the number of rounds over the device's resident workgroup slots times
-// the plane steps per chunk (see launch_ebe_r), at least 4 planes per chunk
-// unless a tuned length (2 or more) is given.
 // Prefetch distance: two node planes in flight for the 16-row tile (a
 // 512-thread workgroup leaves registers to spare at its occupancy of two
 // wavefronts per SIMD; 256x128x128: 70 -> 67 us), one for the smaller tiles,
@@ -426,63 +423,84 @@ __global__ void k_identity_rows(int64_t nn, const uint8_t* __restrict__ mask,
 #define AARMR_EBE_PF(ROWS) ((ROWS) == 16 ? 2 : 1)
 #endif
 
-// Tile rows.  The launch shape word `shape` carries a tuned z-chunk length
-// in its low 16 bits (0: residency-sized) and a tuned ROWS in the bits above
-// (0: the default, 16 rows).  Sixteen rows measured fastest on both the
-// 96x48x48 and the 256x128x128 grid: 8.8 and 66.7 us against 9.2 and 76 us
-// with 8 rows and 14 and 83 us with 12, although a 512-thread workgroup of
-// this kernel leaves a third of the wavefront slots of a compute unit empty.
-#ifndef AARMR_EBE_ROWS
-#define AARMR_EBE_ROWS 16
-#endif
-
-int ebe_rows(int shape) {
-  const int tuned = shape >> 16;
-  if (tuned == 8 || tuned == 12 || tuned == 16) return tuned;
-  return AARMR_EBE_ROWS;
+// Launch shape: tile rows and z-chunk length (node planes per workgroup; a
+// chunk costs one extra element layer, which primes its carry).  The shape
+// word `shape` carries a tuned z-chunk length in its low 16 bits and a tuned
+// ROWS (8, 12 or 16) in the bits above; 0 leaves either to the rule below.
+//
+// A launch takes a fixed time plus t + 1 layer steps, and a step takes
+// longer the more workgroups share a compute unit: on small grids the chain
+// of steps is the launch's time, on large ones the rows it wastes are.  The
+// rule takes the shape with the least base + (t + 1) (step0 + step k), k =
+// workgroups per compute unit, with the constants (us) fitted to measured
+// launches of t = 2..16, k = 1..4.  Eight rows win while they leave one or
+// two workgroups per compute unit, sixteen above.  FP64 product (CG's, with
+// its dot product), against sixteen rows and at least 4 planes a chunk:
+// 24x12x12 8.9 -> 5.9 us (8 rows, 2 planes), 40x32x40 9.7 -> 6.4 us, 96x48x48
+// 10.2 -> 8.9 us (8 rows, 3 planes); at 96x64x64 (16 rows, 6 planes) 13.1 us
+// against 12.9 us, at 256x128x128 66.7 us against 76 us with 8 rows.  FP32:
+// 40x32x40 8.3 -> 6.9 us, 96x64x64 11.8 -> 10.1 us; there a chunk keeps at
+// least 4 planes (2 would take 5.6 us), because lock-step load cases and
+// concurrent solves pay for the extra layers: 16 batched solves of 16..64
+// elements an axis with 4 cases each take 27.5 ms so, 28.3 ms with 2 planes.
+// The products' bits do not depend on the shape; the number of load cases is
+// left out of it, so that the dot products' partials don't depend on that
+// either.
+struct EbeShape {
+  int rows, tz;
+};
+static EbeShape ebe_shape(const Grid& g, int shape, bool f32) {
+  struct Cost {
+    int rows;
+    double base, step0, step;
+  };
+  static const Cost kCost[2][3] = {
+      {{16, 3.9, 0.0, 0.95}, {12, 3.3, 0.0, 0.93}, {8, 3.2, 0.25, 0.45}},
+      {{16, 3.4, 0.1, 0.66}, {12, 3.3, 0.2, 0.55}, {8, 3.1, 0.1, 0.35}}};
+  static const int cus = [] {  // thread-safe one-time init
+    int dev = 0, n = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+    return n > 0 ? n : 256;
+  }();
+  const int rows_req = shape >> 16, tz_req = shape & 0xFFFF;
+  const int planes = g.nz + 1;
+  EbeShape best{16, planes};
+  if (rows_req == 8 || rows_req == 12) best.rows = rows_req;
+  if (tz_req > 0) {
+    best.tz = tz_req < planes ? tz_req : planes;
+  } else {
+    double least = -1.0;
+    for (const Cost& c : kCost[f32]) {
+      if (rows_req ? c.rows != best.rows : c.rows == 12) continue;
+      const int64_t tiles = (int64_t)((g.nx + kTileX) / kTileX) * ((g.ny + c.rows - 1) / (c.rows - 1));
+      for (int n = 1; n <= planes; ++n) {
+        const int t = (planes + n - 1) / n;
+        if (t < (f32 ? 4 : 2)) break;
+        const int64_t k = (tiles * ((planes + t - 1) / t) + cus - 1) / cus;
+        // a step of one small workgroup is bound by its own chain
+        const double step = std::max(f32 && c.rows == 8 ? 0.62 : 0.0, c.step0 + c.step * k);
+        const double cost = c.base + (t + 1) * step;
+        if (least < 0.0 || cost < least) {
+          least = cost;
+          best = {c.rows, t};
+        }
+      }
+    }
+  }
+  best.tz = std::max(best.tz, 2);
+  return best;
 }
 
 template <typename T, int ROWS, bool MASK_IN, bool JAC, bool DOT>
 static int launch_ebe_r(const Grid& g, const WalshConsts& K, const T* E, const uint8_t* mask,
-                        const T* v, T* y, int tz_req, hipStream_t s, const T* jb, const T* jd,
+                        const T* v, T* y, int tz, hipStream_t s, const T* jb, const T* jd,
                         T omega, double* part, int nr, int pst) {
   constexpr int kThreads = kLanes * ROWS;
   constexpr int kTileY = ROWS - 1;
-  // resident workgroups of this kernel on the device (thread-safe one-time init)
-  static const int slots = [] {
-    int dev = 0, cus = 0, per_cu = 0;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, k_ebe_z<T, ROWS, MASK_IN, AARMR_EBE_PF(ROWS), JAC, DOT>, kThreads, 0);
-    return (cus > 0 && per_cu > 0) ? cus * per_cu : 512;
-  }();
   const int gx = (g.nx + 1 + kTileX - 1) / kTileX;
   const int gy = (g.ny + 1 + kTileY - 1) / kTileY;
   const int planes = g.nz + 1;
-  int tz = planes;
-  if (tz_req > 0) {
-    tz = tz_req < planes ? tz_req : planes;  // tuned z-chunk length
-  } else {
-    // Chunks of t planes take about ceil(workgroups / slots) rounds of t + 1
-    // plane steps (a chunk also primes its carry with one layer), so take
-    // the length with the fewest steps, at least 4 planes a chunk.  Grids
-    // with fewer tiles than slots get one round of the shortest chunks that
-    // fit; larger ones get a split whose last round is well filled.
-    const int64_t tiles = (int64_t)gx * gy;
-    int64_t best = -1;
-    for (int n = 1; n <= planes; ++n) {
-      const int t = (planes + n - 1) / n;
-      if (t < 4 && n > 1) break;
-      const int64_t chunks = (planes + t - 1) / t;
-      const int64_t cost = (tiles * chunks + slots - 1) / slots * (t + 1);
-      if (best < 0 || cost < best) {
-        best = cost;
-        tz = t;
-      }
-    }
-  }
-  if (tz < 2) tz = 2;
   const int gz = (planes + tz - 1) / tz;
   k_ebe_z<T, ROWS, MASK_IN, AARMR_EBE_PF(ROWS), JAC, DOT>
       <<<dim3((unsigned)(gx * gy * gz), 1, (unsigned)nr), kThreads, 0, s>>>(
@@ -495,8 +513,9 @@ static int launch_ebe_t(const Grid& g, const WalshConsts& K, const T* E, const u
                         const T* v, T* y, int shape, hipStream_t s, const T* jb = nullptr,
                         const T* jd = nullptr, T omega = 0, double* part = nullptr, int nr = 1,
                         int pst = 0) {
-  const int tz = shape & 0xFFFF;
-  switch (ebe_rows(shape)) {
+  const EbeShape sh = ebe_shape(g, shape, sizeof(T) == 4);
+  const int tz = sh.tz;
+  switch (sh.rows) {
     case 8:
       return launch_ebe_r<T, 8, MASK_IN, JAC, DOT>(g, K, E, mask, v, y, tz, s, jb, jd, omega, part,
                                                    nr, pst);
