@@ -325,16 +325,15 @@ int aarmr_oc_update(aarmr_mesh* m, const double* x, const double* dc, const doub
  * synchronise (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): it calls no hipMalloc, hipFree or allocating
  * library routine and reads nothing back, so the whole update is
- * stream-ordered.  Its scratch (bisection state and the volume partials of
- * the trial multipliers, 28,736 bytes) lives in a static device array that
- * each GPU holds until the process ends; the call clears what must start at
- * zero.  Every call on one GPU shares that array, so calls that overlap on
- * one GPU (other streams, other threads) race: serialise them.  The
- * partials are per reduction block, not per element, so every grid fits.
- * It issues all 67 launch pairs of the at most 200 bisection steps (pairs
- * after convergence return at once) instead of stopping at the first one
- * after convergence.  Needs the mesh's bound workspace for the filter
- * tables, as aarmr_oc_update does.  Outputs are bitwise those of
+ * stream-ordered.  Its scratch (bisection states and the volume partials of
+ * the trial multipliers, 127,104 bytes) lives in a static device array that
+ * each GPU holds until the process ends; nothing in it is read before the
+ * call has written it.  Every call on one GPU shares that array, so calls that
+ * overlap on one GPU (other streams, other threads) race: serialise them.  The
+ * partials are per workgroup, not per element, so every grid fits.
+ * It issues all 40 launches of the at most 200 bisection steps (launches
+ * after convergence return at once) instead of as many as are needed.  Needs
+ * the mesh's bound workspace for the filter tables, as aarmr_oc_update does.  Outputs are bitwise those of
  * aarmr_oc_update.  Errors: AARMR_E_NO_WORKSPACE, AARMR_E_INVALID (null
  * argument, rmin <= 0), AARMR_E_HIP (symbol lookup or launch). */
 int aarmr_oc_update_noalloc(aarmr_mesh* m, const double* x, const double* dc, const double* dv,
@@ -343,10 +342,10 @@ int aarmr_oc_update_noalloc(aarmr_mesh* m, const double* x, const double* dc, co
 
 /* Autotuner of the fine-grid operator's launch shape.  The z-marching
  * kernel runs tiles of 30 node columns by ROWS - 1 node rows of the x-y
- * plane (ROWS in {8, 12, 16}; 16 by default), each marching over a
- * chunk of node planes.
- * The autotuner times every tile height (16 being the default) with the
- * residency-sized default chunk length and candidate lengths 2..n_z+1 on this
+ * plane (ROWS in {8, 12, 16}; 8 or 16 by default, by a rule on the grid),
+ * each marching over a chunk of node planes.
+ * The autotuner times the default shape, and every tile height (16 where
+ * rows = 0) with candidate chunk lengths 2..n_z+1, on this
  * mesh's grid (scratch operands: the solver state is untouched), the best of
  * 3 rounds of 5 launches each after a warm-up, and keeps the fastest for the
  * mesh's later products (FP64 and, in the refinement form, FP32).
@@ -363,7 +362,7 @@ int aarmr_autotune(aarmr_mesh* m, int32_t* tz_out, void* stream);
  * the words an earlier aarmr_autotune returned for the same grid): tz64 for
  * FP64 products, tz32 for the refinement form's FP32 products.  A shape word
  * is chunk_length | (tile_rows << 16): chunk length 0 (default) or >= 2
- * (lengths above n_z + 1 are clamped to it), tile rows 0 (default, 16),
+ * (lengths above n_z + 1 are clamped to it), tile rows 0 (the default),
  * 8, 12 or 16.  0 restores both defaults.  Host-only, takes effect at the
  * next product.  Errors: AARMR_E_INVALID (null mesh, a negative word, a
  * chunk length of 1, other tile rows). */

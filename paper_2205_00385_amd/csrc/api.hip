@@ -28,13 +28,10 @@ int fail(int code, const std::string& msg) {
   return code;
 }
 
-// Static scratch of the allocation-free OC update: the bisection state
-// (5 doubles, padded to 8) and the volume partials of the seven trial
-// multipliers, [7][kRedBlocks].  Each GPU holds its own copy until the
+// Static scratch of the allocation-free OC update: the bisection's states and
+// volume partials (kOcScratchDoubles).  Each GPU holds its own copy until the
 // process ends; host code must use the address hipGetSymbolAddress returns
 // for the current device, never the array's name.
-constexpr int kOcScratchLam = 8;
-constexpr int kOcScratchDoubles = kOcScratchLam + 7 * kRedBlocks;
 static __device__ __align__(256) double oc_scratch[kOcScratchDoubles];
 
 constexpr int kMaxDevices = 64;
@@ -95,7 +92,6 @@ constexpr int SC_TOTAL = SC_MISC + 512;
 // misc slots
 constexpr int M_FF = 0, M_RR0 = 1, M_NRM = 2, M_C = 3, M_EPS = 4, M_VOL = 5;
 constexpr int M_RR64 = 6;      // FP64 residual norm^2 of a refinement step
-constexpr int M_OC = 8;        // 5 slots: l1, l2, lmid, done, steps
 constexpr int M_KPHI = 16;     // Ns*Ns
 constexpr int M_G = 120;       // Ns  (Phi^T dK r)
 constexpr int M_C2 = 132;      // Ns  (K_Phi^-1 g)
@@ -189,7 +185,7 @@ struct aarmr_mesh {
   hipEvent_t ev_fine = nullptr, ev_mg = nullptr;
   bool mg_pending = false;     // a build on `side` not yet joined into the caller's stream
   bool spec_mg = false;        // the last reduced-model attempt was rejected
-  int oc_pairs = 0;            // OC launch pairs the last update needed
+  int oc_rounds = 9;           // bisection launches the last OC update needed (at first: a guess)
   int64_t sweeps = 0;
   // Reuse of the coarsest inverse across designs (AARMR_REUSE_COARSEST):
   // Ainv may stay the inverse of an earlier design's coarsest operator for
@@ -604,7 +600,8 @@ int64_t layout(aarmr_mesh* m, char* base) {
   m->R = (double*)take((int64_t)m->p.Nm * n3 * d8);
   m->KR = (double*)take((int64_t)m->p.Nm * n3 * d8);
   m->scal = (double*)take(R * SC_TOTAL * d8);  // one block of scalars per load case
-  m->partial = (double*)take((int64_t)kRedSlots * kRedBlocks * d8);
+  // reduction partials; the OC bisection's scratch between solves
+  m->partial = (double*)take(std::max(kRedSlots * kRedBlocks, kOcScratchDoubles) * d8);
   if (m->dim == 3) {  // CG's p^T A p and r^T z partials from the fine-grid products
     const int64_t cap = ebe_partials_max(m->lg[0]);
     m->part_cap = (int)cap;
@@ -2339,34 +2336,31 @@ int aarmr_oc_update(aarmr_mesh* m, const double* x, const double* dc, const doub
   if (!(m->p.rmin > 0.0)) return fail(AARMR_E_INVALID, "OC needs the filter (rmin > 0)");
   hipStream_t s = S(stream);
   const Grid& g = m->lg[0];
-  double* lam = m->scal + SC_MISC + M_OC;
   // the volume of the filtered trial density, sum_e (H x / Hs)_e, is the
   // weighted sum sum_j cw_j x_j: no filter inside the bisection
   const double target = volfrac * (double)g.ne;
-  const int nparts = kRedBlocks;
-  launch_oc_init(lam, s);
-  KCHECK();
-  // three bisection steps per launch pair, 200 at most (the kernels count
-  // them; pairs after the end return at once).  The done flag is first read
-  // after one pair more than the previous call needed, then every 4 pairs.
-  const int first = std::min(67, std::max(4, m->oc_pairs + 1));
-  for (int it = 0; it < 67; ++it) {
-    launch_oc_step3(g.ne, x, dc, dv, m->cw, move, m->p.oc_eta, lam, m->partial, nparts, s);
-    launch_oc_bisect3(lam, m->partial, nparts, target, s);
+  // As many launches as the previous call needed, then the update and its
+  // filter, and only then the done flag: when it is not set, two launches more
+  // and both again (launches after the end return at once).  A filtered
+  // density that takes the place of an input waits for the flag.
+  const bool apart = rho_phys_new != x && rho_phys_new != dc && rho_phys_new != dv;
+  for (int r = 0, upto = std::max(1, m->oc_rounds);; upto = std::min(kOcMaxRounds, upto + 2)) {
+    for (; r < upto; ++r)
+      launch_oc_round(g.ne, x, dc, dv, m->cw, move, m->p.oc_eta, target, r, m->partial, s);
+    launch_oc_final(g.ne, x, dc, dv, move, m->p.oc_eta, target, r, m->partial, x_new, s);
+    if (apart) launch_filter(m->fg, m->p.rmin, m->Wf, 0, m->Hs, x_new, rho_phys_new, s);
     KCHECK();
-    if (it + 1 >= first && (it + 1 - first) % 4 == 0) {
-      double h[2];
-      const double* src[2] = {lam + 3, lam + 4};
-      TRY(read_scalars(m, src, 2, h, s));
-      if (h[0] != 0.0) {
-        m->oc_pairs = ((int)h[1] + 2) / 3;
-        break;
-      }
+    double h[2];
+    const double* state = m->partial + (r & 1) * kOcState;
+    const double* src[2] = {state + 3, state + 4};
+    TRY(read_scalars(m, src, 2, h, s));
+    if (h[0] != 0.0) {  // set after 200 steps at the latest
+      m->oc_rounds = std::max(1, ((int)h[1] + kOcLevels - 1) / kOcLevels);
+      break;
     }
+    if (r >= kOcMaxRounds) return fail(AARMR_E_STATE, "OC bisection did not end");
   }
-  launch_oc_final(g.ne, x, dc, dv, move, m->p.oc_eta, lam, x_new, s);
-  KCHECK();
-  launch_filter(m->fg, m->p.rmin, m->Wf, 0, m->Hs, x_new, rho_phys_new, s);
+  if (!apart) launch_filter(m->fg, m->p.rmin, m->Wf, 0, m->Hs, x_new, rho_phys_new, s);
   KCHECK();
   return AARMR_OK;
 }
@@ -2378,28 +2372,16 @@ int aarmr_oc_update_noalloc(aarmr_mesh* m, const double* x, const double* dc, co
   if (!x || !dc || !dv || !x_new || !rho_phys_new) return fail(AARMR_E_INVALID, "null argument");
   if (!(m->p.rmin > 0.0)) return fail(AARMR_E_INVALID, "OC needs the filter (rmin > 0)");
   const Grid& g = m->lg[0];
-  // the partials are per reduction block, not per element: any grid fits
-  const int nparts = kRedBlocks;
-  if (kOcScratchLam + 7 * nparts > kOcScratchDoubles)
-    return fail(AARMR_E_INVALID, "OC scratch above its static maximum");
-  double* base = nullptr;
-  TRY(oc_scratch_ptr(&base));
+  // the partials are per workgroup, not per element: any grid fits
+  double* scratch = nullptr;
+  TRY(oc_scratch_ptr(&scratch));
   hipStream_t s = S(stream);
-  double* lam = base;
-  double* partial = base + kOcScratchLam;
   const double target = volfrac * (double)g.ne;
-  // the bisection state starts from the kernel's fill, never from what the
-  // array held after an earlier call
-  launch_oc_init(lam, s);
-  KCHECK();
-  // no read-back: every pair is issued (at most 200 bisection steps in 67
-  // pairs; pairs after convergence return at once)
-  for (int it = 0; it < 67; ++it) {
-    launch_oc_step3(g.ne, x, dc, dv, m->cw, move, m->p.oc_eta, lam, partial, nparts, s);
-    launch_oc_bisect3(lam, partial, nparts, target, s);
-    KCHECK();
-  }
-  launch_oc_final(g.ne, x, dc, dv, move, m->p.oc_eta, lam, x_new, s);
+  // no read-back: every launch of the at most 200 steps is issued (launches
+  // after the end return at once)
+  for (int r = 0; r < kOcMaxRounds; ++r)
+    launch_oc_round(g.ne, x, dc, dv, m->cw, move, m->p.oc_eta, target, r, scratch, s);
+  launch_oc_final(g.ne, x, dc, dv, move, m->p.oc_eta, target, kOcMaxRounds, scratch, x_new, s);
   KCHECK();
   launch_filter(m->fg, m->p.rmin, m->Wf, 0, m->Hs, x_new, rho_phys_new, s);
   KCHECK();

@@ -338,17 +338,24 @@ void launch_filter(const Grid& g, double r, const double* W, int mode, const dou
                    const double* in, double* out, hipStream_t s);
 void launch_fill(int64_t n, double v, double* out, hipStream_t s);
 void launch_fill_f32(int64_t n, float v, float* out, hipStream_t s);
-// OC bisection, three levels per launch pair: block partials of the volume
-// sum_j cw_j x_new_j for the seven multipliers three levels can visit
-// (nparts blocks), then the bisection steps on lam; x_new at the last
-// multiplier evaluated.
-void launch_oc_step3(int64_t ne, const double* x, const double* dc, const double* dv,
-                     const double* cw, double move, double eta, const double* lam,
-                     double* partial, int nparts, hipStream_t s);
-void launch_oc_bisect3(double* lam, const double* partial, int nparts, double target,
-                       hipStream_t s);
+// OC bisection, kOcLevels steps per launch.  Launch `round` (0, 1, ...) walks
+// the steps that launch round - 1's volumes decide and leaves the partials of
+// the volumes sum_j cw_j x_new_j for the kOcTrials multipliers of the next
+// steps; launch_oc_final, after launches 0..round - 1, walks the last ones and,
+// if the bisection is done, forms x_new at the last multiplier evaluated
+// (else x_new is left alone).  scratch: kOcScratchDoubles,
+// two states (l1, l2, lmid, done, steps; launch r writes state r & 1) and two
+// sets of partials; nothing in it need be cleared.
+constexpr int kOcLevels = 5, kOcTrials = (1 << kOcLevels) - 1;
+constexpr int kOcParts = 256, kOcThreads = 512;  // workgroups and their threads
+constexpr int kOcState = 8;
+constexpr int kOcMaxRounds = 200 / kOcLevels;  // the bisection takes 200 steps at most
+constexpr int kOcScratchDoubles = 2 * kOcState + 2 * kOcTrials * kOcParts;
+void launch_oc_round(int64_t ne, const double* x, const double* dc, const double* dv,
+                     const double* cw, double move, double eta, double target, int round,
+                     double* scratch, hipStream_t s);
 void launch_oc_final(int64_t ne, const double* x, const double* dc, const double* dv, double move,
-                     double eta, const double* lam, double* xnew, hipStream_t s);
-void launch_oc_init(double* lam, hipStream_t s);
+                     double eta, double target, int round, double* scratch, double* xnew,
+                     hipStream_t s);
 
 }  // namespace aarmr

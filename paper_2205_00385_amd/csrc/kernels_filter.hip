@@ -2,6 +2,8 @@
 // bisection of the optimality-criteria update.
 #include <cmath>
 
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace aarmr {
@@ -83,18 +85,6 @@ __global__ void __launch_bounds__(256) k_filter(int nx, int ny, int nz, int Rrt,
   out[e] = mode == 0 ? s / Hs[e] : s;
 }
 
-// lam[0] = l1, lam[1] = l2, lam[2] = current midpoint, lam[3] = done flag,
-// lam[4] = bisection steps taken (at most 200).
-__global__ void k_oc_init(double* lam) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    lam[0] = 0.0;
-    lam[1] = 1e9;
-    lam[2] = 0.5e9;
-    lam[3] = 0.0;
-    lam[4] = 0.0;
-  }
-}
-
 // The OC update of one element at multiplier lmid.
 __device__ inline double oc_x(double xe, double B, double lmid, double move, double eta) {
   double v = xe * (eta == 0.5 ? sqrt(B / lmid) : pow(B / lmid, eta));
@@ -102,92 +92,153 @@ __device__ inline double oc_x(double xe, double B, double lmid, double move, dou
   return fmax(v, fmax(0.0, xe - move));
 }
 
-// Three bisection levels per launch.  The seven multipliers a three-level
-// bisection of [lam[0], lam[1]] can visit, in heap order (t: midpoint;
-// 2t + 1: its left half's midpoint, 2t + 2: its right half's), computed with
-// the same expressions the one-level steps would use; for each, block
-// partials of sum_j c_j x_new_j, the volume of the filtered x_new (c =
-// H^T (1 / Hs), the column weights of the normalised filter), in the
-// summation order of a one-level step, so every decision is bitwise the one
-// the one-level bisection takes.
-__global__ void __launch_bounds__(256) k_oc_step3(int64_t ne, const double* __restrict__ x,
-                                                  const double* __restrict__ dc,
-                                                  const double* __restrict__ dv,
-                                                  const double* __restrict__ cw, double move,
-                                                  double eta, const double* __restrict__ lam,
-                                                  double* __restrict__ partial) {
-  __shared__ double red[7][4];
-  if (lam[3] != 0.0) return;  // block-uniform
-  const double l1 = lam[0], l2 = lam[1];
-  double lm[7];
-  lm[0] = 0.5 * (l1 + l2);
-  lm[1] = 0.5 * (l1 + lm[0]);
-  lm[2] = 0.5 * (lm[0] + l2);
-  lm[3] = 0.5 * (l1 + lm[1]);
-  lm[4] = 0.5 * (lm[1] + lm[0]);
-  lm[5] = 0.5 * (lm[0] + lm[2]);
-  lm[6] = 0.5 * (lm[2] + l2);
-  double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ne;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const double B = fmax(0.0, -dc[e]) / dv[e];
-    const double xe = x[e], c = cw[e];
-#pragma unroll
-    for (int t = 0; t < 7; ++t) acc[t] = fma(c, oc_x(xe, B, lm[t], move, eta), acc[t]);
-  }
-#pragma unroll
-  for (int t = 0; t < 7; ++t) {
-    double a = acc[t];
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-    if ((threadIdx.x & 63) == 0) red[t][threadIdx.x >> 6] = a;
-  }
-  __syncthreads();
-  if (threadIdx.x < 7) {
-    const int t = threadIdx.x;
-    partial[t * kRedBlocks + blockIdx.x] = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
-  }
-}
+// State of the bisection: the bracket, the last multiplier evaluated, whether
+// the end is reached ((l2 - l1)/(l1 + l2) <= 1e-3, or the 200th step) and the
+// steps taken.  As doubles l1, l2, lmid, done, steps in memory (kOcState
+// apart).
+struct OcState {
+  double l1, l2, lmid, done, steps;
+};
 
-// The volumes of the seven multipliers (partials summed in a fixed order),
-// then up to three bisection steps along the path the decisions take; lam[2]
-// records the last multiplier evaluated, lam[3] = 1 once (l2-l1)/(l1+l2) <= 1e-3
-// or after the 200th step.
-__global__ void __launch_bounds__(512) k_oc_bisect3(double* lam, const double* __restrict__ partial,
-                                                    int nparts, double target) {
-  __shared__ double vol[7];
-  if (lam[3] != 0.0) return;
-  const int t = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (t < 7) {  // wave t sums trial t's partials
-    double acc = 0.0;
-    for (int b = lane; b < nparts; b += 64) acc += partial[t * kRedBlocks + b];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if (lane == 0) vol[t] = acc;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  int h = 0;  // heap index of the multiplier evaluated next
-  for (int level = 0; level < 3 && lam[3] == 0.0; ++level) {
-    const double lmid = 0.5 * (lam[0] + lam[1]);
-    lam[2] = lmid;
-    if (vol[h] > target) {
-      lam[0] = lmid;
-      h = 2 * h + 2;
-    } else {
-      lam[1] = lmid;
-      h = 2 * h + 1;
+// Launch `round` of the bisection finishes the volumes that launch round - 1
+// left as partials for kOcTrials multipliers, in heap order (node t: midpoint
+// of its interval, 2t + 1 and 2t + 2: its left and right halves), and takes up
+// to kOcLevels steps along the path that the decisions take.  Every workgroup
+// does so for itself, in the same order, so no launch is needed in between;
+// workgroup 0 also stores the state.  States and partials alternate between
+// two buffers, so a launch reads only what the launch before it wrote.
+// 16 lanes sum each trial's partials.
+__device__ inline OcState oc_walk(int round, double* __restrict__ state,
+                                  const double* __restrict__ partial, double target,
+                                  double* vol) {
+  OcState st{0.0, 1e9, 0.5e9, 0.0, 0.0};
+  if (round > 0) {
+    const double* from = state + ((round - 1) & 1) * kOcState;
+    st = {from[0], from[1], from[2], from[3], from[4]};
+    if (st.done == 0.0) {  // workgroup-uniform
+      const double* p = partial + (int64_t)((round - 1) & 1) * kOcTrials * kOcParts;
+      const int t = threadIdx.x >> 4, part = threadIdx.x & 15;
+      if (t < kOcTrials) {
+        double acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < kOcParts / 16; ++q) acc += p[t * kOcParts + q * 16 + part];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        if (part == 0) vol[t] = acc;
+      }
+      __syncthreads();
+      int h = 0;
+#pragma unroll
+      for (int level = 0; level < kOcLevels; ++level) {
+        if (st.done != 0.0) break;
+        st.lmid = 0.5 * (st.l1 + st.l2);
+        const bool right = vol[h] > target;
+        (right ? st.l1 : st.l2) = st.lmid;
+        h = 2 * h + (right ? 2 : 1);
+        st.steps += 1.0;
+        if ((st.l2 - st.l1) / (st.l1 + st.l2) <= 1e-3 || st.steps >= 200.0) st.done = 1.0;
+      }
     }
-    lam[4] += 1.0;
-    if ((lam[1] - lam[0]) / (lam[0] + lam[1]) <= 1e-3 || lam[4] >= 200.0) lam[3] = 1.0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    double* to = state + (round & 1) * kOcState;
+    to[0] = st.l1;
+    to[1] = st.l2;
+    to[2] = st.lmid;
+    to[3] = st.done;
+    to[4] = st.steps;
+  }
+  return st;
+}
+
+// One launch of the bisection: the steps that the previous launch's volumes
+// decide, then partials of sum_j c_j x_new_j, the volume of the filtered x_new
+// (c = H^T (1 / Hs), the column weights of the normalised filter), for the
+// kOcTrials multipliers that the next kOcLevels steps can visit.  The update's
+// root splits, x (B / l)^eta = (x B^eta) l^-eta, so an element costs one root
+// and a product and two clamps per trial.  The launches are a serial chain of
+// a few microseconds each, so what counts is their number: five levels here
+// (31 trials, 62 accumulator registers) against three per pair of launches
+// (96x48x48: 15 pairs of 11.8 us before, 9 launches of 8 us now).  The trial
+// sums of a wavefront are added by halving: 32 values in 32 exchanges.
+template <bool HALF>
+__global__ void __launch_bounds__(kOcThreads) k_oc_round(
+    int64_t ne, const double* __restrict__ x, const double* __restrict__ dc,
+    const double* __restrict__ dv, const double* __restrict__ cw, double move, double eta,
+    double target, int round, double* __restrict__ state, double* __restrict__ partial) {
+  __shared__ double vol[kOcTrials + 1], rl[kOcTrials + 1], red[kOcTrials + 1][kOcThreads / 64];
+  const int64_t stride = (int64_t)kOcParts * kOcThreads;
+  int64_t e = (int64_t)blockIdx.x * kOcThreads + threadIdx.x;
+  // the first element's values arrive while the state is walked
+  const bool any = e < ne;
+  double xe = any ? x[e] : 0.0, ge = any ? dc[e] : 0.0, ve = any ? dv[e] : 1.0,
+         c = any ? cw[e] : 0.0;
+  const OcState st = oc_walk(round, state, partial, target, vol);
+  if (st.done != 0.0) return;  // workgroup-uniform
+  if (threadIdx.x < kOcTrials) {  // the trial multipliers: walk down to node t
+    const int n = threadIdx.x + 1;  // heap index from 1: its bits below the top one are the path
+    double l1 = st.l1, l2 = st.l2;
+    for (int bit = 30 - __clz(n); bit >= 0; --bit) {
+      const double lm = 0.5 * (l1 + l2);
+      if ((n >> bit) & 1)
+        l1 = lm;
+      else
+        l2 = lm;
+    }
+    const double lm = 0.5 * (l1 + l2);
+    rl[threadIdx.x] = HALF ? 1.0 / sqrt(lm) : pow(lm, -eta);
+  }
+  __syncthreads();
+  double acc[kOcTrials + 1];
+#pragma unroll
+  for (int t = 0; t <= kOcTrials; ++t) acc[t] = 0.0;
+  while (e < ne) {
+    const double B = fmax(0.0, -ge) / ve;
+    const double xb = xe * (HALF ? sqrt(B) : pow(B, eta));
+    const double hi = fmin(1.0, xe + move), lo = fmax(0.0, xe - move);
+#pragma unroll
+    for (int t = 0; t < kOcTrials; ++t) acc[t] = fma(c, fmax(fmin(xb * rl[t], hi), lo), acc[t]);
+    e += stride;
+    if (e < ne) {
+      xe = x[e];
+      ge = dc[e];
+      ve = dv[e];
+      c = cw[e];
+    }
+  }
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int half = (kOcTrials + 1) / 2; half > 0; half >>= 1) {
+    const bool up = lane & (2 * half);
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const double send = up ? acc[i] : acc[i + half], keep = up ? acc[i + half] : acc[i];
+      acc[i] = keep + __shfl_xor(send, 2 * half, 64);
+    }
+  }
+  acc[0] += __shfl_xor(acc[0], 1, 64);
+  if (!(lane & 1)) red[lane >> 1][threadIdx.x >> 6] = acc[0];  // lane bits 5..1 are the trial's
+  __syncthreads();
+  if (threadIdx.x < kOcTrials) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kOcThreads / 64; ++w) s += red[threadIdx.x][w];
+    partial[(int64_t)(round & 1) * kOcTrials * kOcParts + threadIdx.x * kOcParts + blockIdx.x] = s;
   }
 }
 
-// x_new at the last multiplier the bisection evaluated.
-__global__ void k_oc_final(int64_t ne, const double* __restrict__ x, const double* __restrict__ dc,
-                           const double* __restrict__ dv, double move, double eta,
-                           const double* __restrict__ lam, double* __restrict__ xnew) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= ne) return;
-  xnew[e] = oc_x(x[e], fmax(0.0, -dc[e]) / dv[e], lam[2], move, eta);
+// The last launch's volumes decided, then, if they end the bisection, x_new
+// at the last multiplier it evaluated.
+__global__ void __launch_bounds__(kOcThreads) k_oc_final(
+    int64_t ne, const double* __restrict__ x, const double* __restrict__ dc,
+    const double* __restrict__ dv, double move, double eta, double target, int round,
+    double* __restrict__ state, const double* __restrict__ partial, double* __restrict__ xnew) {
+  __shared__ double vol[kOcTrials + 1];
+  const OcState st = oc_walk(round, state, partial, target, vol);
+  if (st.done == 0.0) return;
+  const int64_t stride = (int64_t)gridDim.x * kOcThreads;
+  for (int64_t e = (int64_t)blockIdx.x * kOcThreads + threadIdx.x; e < ne; e += stride)
+    xnew[e] = oc_x(x[e], fmax(0.0, -dc[e]) / dv[e], st.lmid, move, eta);
 }
 
 template <typename T>
@@ -238,22 +289,24 @@ void launch_fill_f32(int64_t n, float v, float* out, hipStream_t s) {
   k_fill<float><<<nblk(n, 256), 256, 0, s>>>(n, v, out);
 }
 
-void launch_oc_init(double* lam, hipStream_t s) { k_oc_init<<<1, 64, 0, s>>>(lam); }
-
-void launch_oc_step3(int64_t ne, const double* x, const double* dc, const double* dv,
-                     const double* cw, double move, double eta, const double* lam,
-                     double* partial, int nparts, hipStream_t s) {
-  k_oc_step3<<<nparts, 256, 0, s>>>(ne, x, dc, dv, cw, move, eta, lam, partial);
-}
-
-void launch_oc_bisect3(double* lam, const double* partial, int nparts, double target,
-                       hipStream_t s) {
-  k_oc_bisect3<<<1, 512, 0, s>>>(lam, partial, nparts, target);
+void launch_oc_round(int64_t ne, const double* x, const double* dc, const double* dv,
+                     const double* cw, double move, double eta, double target, int round,
+                     double* scratch, hipStream_t s) {
+  double* partial = scratch + 2 * kOcState;
+  if (eta == 0.5)
+    k_oc_round<true><<<kOcParts, kOcThreads, 0, s>>>(ne, x, dc, dv, cw, move, eta, target, round,
+                                                     scratch, partial);
+  else
+    k_oc_round<false><<<kOcParts, kOcThreads, 0, s>>>(ne, x, dc, dv, cw, move, eta, target, round,
+                                                      scratch, partial);
 }
 
 void launch_oc_final(int64_t ne, const double* x, const double* dc, const double* dv, double move,
-                     double eta, const double* lam, double* xnew, hipStream_t s) {
-  k_oc_final<<<nblk(ne, 256), 256, 0, s>>>(ne, x, dc, dv, move, eta, lam, xnew);
+                     double eta, double target, int round, double* scratch, double* xnew,
+                     hipStream_t s) {
+  const unsigned nb = std::min(nblk(ne, kOcThreads), 1024u);
+  k_oc_final<<<nb, kOcThreads, 0, s>>>(ne, x, dc, dv, move, eta, target, round, scratch,
+                                       scratch + 2 * kOcState, xnew);
 }
 
 }  // namespace aarmr
