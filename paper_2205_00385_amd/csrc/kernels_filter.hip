@@ -37,16 +37,12 @@ __global__ void k_filter_rowsum(int nx, int ny, int nz, double r, int R, double*
 
 // mode 0: out_e = sum_j w_ej in_j / Hs_e;  mode 1: out_e = sum_i w_ie in_i / Hs_i.
 // W holds the cone weights max(0, r - |d|) of the (2R+1)^3 offsets
-// (dk, dj, di), di fastest; zero weights are summed too (adding +0 changes
-// nothing).  RC > 0 fixes R at compile time; elements whose neighbourhood
-// lies inside the grid take an unrolled path without bounds checks.
-template <int RC>
-__global__ void __launch_bounds__(256) k_filter(int nx, int ny, int nz, int Rrt, int mode,
+// (dk, dj, di), di fastest.  Any reach; thread per element.
+__global__ void __launch_bounds__(256) k_filter(int nx, int ny, int nz, int R, int mode,
                                                 const double* __restrict__ W,
                                                 const double* __restrict__ Hs,
                                                 const double* __restrict__ in,
                                                 double* __restrict__ out) {
-  const int R = RC > 0 ? RC : Rrt;
   const int D = 2 * R + 1;
   const int64_t ne = (int64_t)nx * ny * nz;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -56,33 +52,87 @@ __global__ void __launch_bounds__(256) k_filter(int nx, int ny, int nz, int Rrt,
   const int j = (int)(rest % ny), k = (int)(rest / ny);
   const int64_t sy = nx, sz = (int64_t)nx * ny;
   double s = 0.0;
-  const bool inside = i >= R && i < nx - R && j >= R && j < ny - R && k >= R && k < nz - R;
-  if (RC > 0 && inside && mode == 0) {
-#pragma unroll
-    for (int dk = -RC; dk <= RC; ++dk)
-#pragma unroll
-      for (int dj = -RC; dj <= RC; ++dj)
-#pragma unroll
-        for (int di = -RC; di <= RC; ++di)
-          s = fma(W[((dk + RC) * D + (dj + RC)) * D + (di + RC)], in[e + di + sy * dj + sz * dk], s);
-  } else {
-    for (int dk = -R; dk <= R; ++dk) {
-      const int kk = k + dk;
-      if (kk < 0 || kk >= nz) continue;
-      for (int dj = -R; dj <= R; ++dj) {
-        const int jj = j + dj;
-        if (jj < 0 || jj >= ny) continue;
-        for (int di = -R; di <= R; ++di) {
-          const int ii = i + di;
-          if (ii < 0 || ii >= nx) continue;
-          const double w = W[((dk + R) * D + (dj + R)) * D + (di + R)];
-          const int64_t nb = e + di + sy * dj + sz * dk;
-          s = mode == 0 ? fma(w, in[nb], s) : fma(w, in[nb] / Hs[nb], s);
-        }
+  for (int dk = -R; dk <= R; ++dk) {
+    const int kk = k + dk;
+    if (kk < 0 || kk >= nz) continue;
+    for (int dj = -R; dj <= R; ++dj) {
+      const int jj = j + dj;
+      if (jj < 0 || jj >= ny) continue;
+      for (int di = -R; di <= R; ++di) {
+        const int ii = i + di;
+        if (ii < 0 || ii >= nx) continue;
+        const double w = W[((dk + R) * D + (dj + R)) * D + (di + R)];
+        const int64_t nb = e + di + sy * dj + sz * dk;
+        s = mode == 0 ? fma(w, in[nb], s) : fma(w, in[nb] / Hs[nb], s);
       }
     }
   }
   out[e] = mode == 0 ? s / Hs[e] : s;
+}
+
+// The same sums for a small reach, from LDS: a workgroup takes a tile of
+// kFtX x kFtY x TZ elements and stages it with its halo (0 outside the grid:
+// a term of 0 leaves the sum's bits), in mode 1 already divided by Hs, so an
+// element is divided two to four times and not once per tap.  Read directly,
+// the taps cost a pass of bounds checks in every wavefront that holds an
+// element on a side of the grid, which on rows of 96 is nearly all of them.
+// PLANE: one layer, whose sums have no z offsets.  Per call, both modes,
+// R = 1: 96x48x48 12.9 -> 4.9 us, 24x12x12 7.7 -> 4.1 us; R = 2: plane
+// 320x160 8.8 -> 3.8 us.
+constexpr int kFtX = 32, kFtY = 8;
+template <int R, int TZ, bool PLANE>
+__global__ void __launch_bounds__(kFtX * kFtY) k_filter_tile(int nx, int ny, int nz, int gx, int gy,
+                                                             int mode,
+                                                             const double* __restrict__ W,
+                                                             const double* __restrict__ Hs,
+                                                             const double* __restrict__ in,
+                                                             double* __restrict__ out) {
+  constexpr int D = 2 * R + 1, RZ = PLANE ? 0 : R;
+  constexpr int SX = kFtX + 2 * R, SY = kFtY + 2 * R, SZ = TZ + 2 * RZ, N = SX * SY * SZ;
+  constexpr int kPer = (N + kFtX * kFtY - 1) / (kFtX * kFtY);
+  __shared__ double tile[N];
+  const int b = blockIdx.x, by = b / gx, bz = by / gy;
+  const int i0 = (b - by * gx) * kFtX, j0 = (by - bz * gy) * kFtY, k0 = bz * TZ;
+  double v[kPer], h[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int t = threadIdx.x + q * kFtX * kFtY;
+    const int i = i0 + t % SX - R, j = j0 + t / SX % SY - R, k = k0 + t / (SX * SY) - RZ;
+    const bool ok = t < N && i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz;
+    const int64_t e = ok ? i + (int64_t)nx * (j + (int64_t)ny * k) : 0;
+    v[q] = in[e];
+    h[q] = mode ? Hs[e] : 1.0;
+    if (!ok) v[q] = 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int t = threadIdx.x + q * kFtX * kFtY;
+    if (t < N) tile[t] = mode ? v[q] / h[q] : v[q];
+  }
+  const int li = threadIdx.x % kFtX, lj = threadIdx.x / kFtX;
+  const int i = i0 + li, j = j0 + lj;
+  const bool col = i < nx && j < ny;
+  double hs[TZ];
+#pragma unroll
+  for (int z = 0; z < TZ; ++z)
+    hs[z] = (!mode && col && k0 + z < nz) ? Hs[i + (int64_t)nx * (j + (int64_t)ny * (k0 + z))]
+                                          : 1.0;
+  __syncthreads();
+  if (!col) return;
+#pragma unroll
+  for (int z = 0; z < TZ; ++z) {
+    if (k0 + z >= nz) break;
+    double s = 0.0;
+#pragma unroll
+    for (int dk = -RZ; dk <= RZ; ++dk)
+#pragma unroll
+      for (int dj = -R; dj <= R; ++dj)
+#pragma unroll
+        for (int di = -R; di <= R; ++di)
+          s = fma(W[((dk + R) * D + (dj + R)) * D + (di + R)],
+                  tile[((z + dk + RZ) * SY + lj + dj + R) * SX + li + di + R], s);
+    out[i + (int64_t)nx * (j + (int64_t)ny * (k0 + z))] = mode ? s : s / hs[z];
+  }
 }
 
 // The OC update of one element at multiplier lmid.
@@ -270,15 +320,29 @@ void launch_filter_rowsum(const Grid& g, double r, double* Hs, hipStream_t s) {
   k_filter_rowsum<<<nblk(g.ne, 256), 256, 0, s>>>(g.nx, g.ny, g.nz, r, filter_reach(r), Hs);
 }
 
+template <int R, int TZ, bool PLANE>
+static void filter_tile(const Grid& g, const double* W, int mode, const double* Hs,
+                        const double* in, double* out, hipStream_t s) {
+  const int gx = (g.nx + kFtX - 1) / kFtX, gy = (g.ny + kFtY - 1) / kFtY, gz = (g.nz + TZ - 1) / TZ;
+  k_filter_tile<R, TZ, PLANE><<<(unsigned)((int64_t)gx * gy * gz), kFtX * kFtY, 0, s>>>(
+      g.nx, g.ny, g.nz, gx, gy, mode, W, Hs, in, out);
+}
+
+// Tiles for the reaches 1 and 2 (radii up to 3), whose halo is a small
+// multiple of the tile; larger ones per element.
 void launch_filter(const Grid& g, double r, const double* W, int mode, const double* Hs,
                    const double* in, double* out, hipStream_t s) {
   const int R = filter_reach(r);
-  const unsigned nb = nblk(g.ne, 256);
-  switch (R) {
-    case 1: k_filter<1><<<nb, 256, 0, s>>>(g.nx, g.ny, g.nz, R, mode, W, Hs, in, out); break;
-    case 2: k_filter<2><<<nb, 256, 0, s>>>(g.nx, g.ny, g.nz, R, mode, W, Hs, in, out); break;
-    default: k_filter<0><<<nb, 256, 0, s>>>(g.nx, g.ny, g.nz, R, mode, W, Hs, in, out); break;
-  }
+  if (R == 1 && g.nz == 1)
+    filter_tile<1, 1, true>(g, W, mode, Hs, in, out, s);
+  else if (R == 2 && g.nz == 1)
+    filter_tile<2, 1, true>(g, W, mode, Hs, in, out, s);
+  else if (R == 1)
+    filter_tile<1, 2, false>(g, W, mode, Hs, in, out, s);
+  else if (R == 2)
+    filter_tile<2, 4, false>(g, W, mode, Hs, in, out, s);
+  else
+    k_filter<<<nblk(g.ne, 256), 256, 0, s>>>(g.nx, g.ny, g.nz, R, mode, W, Hs, in, out);
 }
 
 void launch_fill(int64_t n, double v, double* out, hipStream_t s) {
