@@ -602,8 +602,8 @@ int64_t layout(aarmr_mesh* m, char* base) {
   m->scal = (double*)take(R * SC_TOTAL * d8);  // one block of scalars per load case
   // reduction partials; the OC bisection's scratch between solves
   m->partial = (double*)take(std::max(kRedSlots * kRedBlocks, kOcScratchDoubles) * d8);
-  if (m->dim == 3) {  // CG's p^T A p and r^T z partials from the fine-grid products
-    const int64_t cap = ebe_partials_max(m->lg[0]);
+  {  // CG's p^T A p and r^T z partials from the fine-grid products
+    const int64_t cap = m->dim == 3 ? ebe_partials_max(m->lg[0]) : q4_partials_max(m->lg[0]);
     m->part_cap = (int)cap;
     m->part_pq = (double*)take(R * cap * d8);
     m->part_rz = (double*)take(R * cap * d8);
@@ -750,9 +750,15 @@ LevelArgs level_args(const aarmr_mesh* m, int l) {
                    T.mom[l],   T.special[l], T.nlist[l], T.corner[l], T.Kst[l]};
 }
 
-// Product of coarse level l (3D), by launch_level_product's modes.
+// Product of coarse level l: mode 0 y = A v, 1 a damped-Jacobi sweep, 2 the
+// residual b - A v.
 int level_product(aarmr_mesh* m, int l, int mode, const double* v, double* y, const double* b,
                   hipStream_t s) {
+  if (m->dim == 2) {
+    launch_q4_coarse(m->lg[l], m->lv[l].Ke, mode, v, y, b, m->lv[l].dinv, m->p.omega, s);
+    KCHECK();
+    return AARMR_OK;
+  }
   TRY(level_counts(m, s));
   launch_level_product(level_args(m, l), m->wk, m->E, mode, v, y, b, m->lv[l].dinv, m->p.omega, s);
   KCHECK();
@@ -784,8 +790,8 @@ int level_product32(aarmr_mesh* m, int l, int mode, const float* v, float* y, co
 int fine_product(aarmr_mesh* m, const double* E, const double* v, double* y, hipStream_t s,
                  bool with_springs = true) {
   if (m->dim == 2) {
-    launch_q4_apply(m->lg[0], m->KEd, E, m->mask, v, y, 2, s);
-    if (with_springs) launch_springs_add(m->springs, m->lg[0], m->mask, v, y, s);
+    launch_q4_fine(m->lg[0], m->KEd, E, m->mask, with_springs ? m->springs : SpringSet{}, 0, 2, v,
+                   y, nullptr, nullptr, 0.0, nullptr, s);
   } else
     launch_ebe(m->lg[0], m->wk, E, m->mask, v, y, 2, s);
   ++m->sweeps;
@@ -795,14 +801,10 @@ int fine_product(aarmr_mesh* m, const double* E, const double* v, double* y, hip
 
 int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
           bool any_input = false) {
-  if (m->dim == 2) {
-    if (l == 0) {
-      launch_q4_apply(m->lg[0], m->KEd, m->E, m->mask, v, y, any_input ? 0 : 2, s);
-      launch_springs_add(m->springs, m->lg[0], m->mask, v, y, s);
-      ++m->sweeps;
-    } else {
-      launch_q4_apply_elemmat(m->lg[l], m->lv[l].Ke, v, y, s);
-    }
+  if (l == 0 && m->dim == 2) {
+    launch_q4_fine(m->lg[0], m->KEd, m->E, m->mask, m->springs, 0, any_input ? 0 : 2, v, y, nullptr,
+                   nullptr, 0.0, nullptr, s);
+    ++m->sweeps;
     KCHECK();
     return AARMR_OK;
   }
@@ -818,14 +820,14 @@ int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
 
 // One V-cycle (Algorithm 2) on level l from a zero initial guess: x = M_l^-1 b.
 // x_init: x already holds the first pre-smoothing sweep omega D^-1 b (formed
-// by the kernel that produced b).  On the 3D hierarchy the sweeps are fused
-// into neighbouring kernels: the restriction forms the coarse level's first
-// sweep, and below the finest level the last post-smoothing sweep is the
-// epilogue of its operator product, which writes into L.t, and the level's x
-// and t buffers swap roles, so there x must be L.x; on the finest level this is
-// done only for the solver's own z (m->z, which swaps with t0), a caller's
-// buffer gets the separate sweep.  The coarse levels' product before the
-// restriction forms the residual itself.
+// by the kernel that produced b).  The sweeps are fused into neighbouring
+// kernels: the restriction forms the coarse level's first sweep, and below the
+// finest level the last post-smoothing sweep is the epilogue of its operator
+// product, which writes into L.t, and the level's x and t buffers swap roles,
+// so there x must be L.x; on the finest level this is done only for the
+// solver's own z (m->z, which swaps with t0), a caller's buffer gets the
+// separate sweep.  The product before the restriction forms the residual
+// itself, except that of the finest 3D level.
 int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
            bool x_init = false) {
   if (l == m->nlev - 1) {
@@ -839,8 +841,8 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
   LevelBuf& C = m->lv[l + 1];
   const uint8_t* mask = (l == 0) ? m->mask : nullptr;
   const double om = m->p.omega;
-  const bool fuse = m->dim == 3;
-  const bool child_first = fuse && m->p.nu_pre >= 1 && l + 1 < m->nlev - 1;
+  const bool plane = m->dim == 2;
+  const bool child_first = m->p.nu_pre >= 1 && l + 1 < m->nlev - 1;
   const CoarseOrder* co = l + 1 == m->nlev - 1 ? &m->corder : nullptr;
   if (m->p.nu_pre >= 1) {
     if (!x_init) {
@@ -853,15 +855,19 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
       KCHECK();
     }
     // line 2: residual, restricted
-    const bool res = fuse && l >= 1;  // L.t holds b - A x, not A x
-    if (res)
+    const bool res = plane || l >= 1;  // L.t holds b - A x, not A x
+    if (l >= 1) {
       TRY(level_product(m, l, 2, x, L.t, b, s));
-    else
+    } else if (plane) {
+      launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 2, 2, x, L.t, b, nullptr, 0.0, nullptr,
+                     s);
+      ++m->sweeps;
+    } else
       TRY(apply(m, l, x, L.t, s));
     const double* rb = res ? L.t : b;
     const double* rt = res ? nullptr : L.t;
     if (child_first)
-      launch_restrict_jacobi(m->lg[l + 1], rb, rt, mask, C.b, C.dinv, om, C.x, s);
+      launch_restrict_jacobi(m->lg[l + 1], rb, rt, mask, C.b, C.dinv, om, C.x, s, m->dim);
     else
       launch_restrict(m->lg[l + 1], rb, rt, mask, C.b, s, m->dim, co);
   } else {
@@ -874,9 +880,13 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
   launch_prolong_add(G, C.x, mask, x, s, m->dim, co);  // line 4
   KCHECK();
   for (int it = 0; it < m->p.nu_post; ++it) {        // line 5
-    if (fuse && l == 0 && x == m->z && it == m->p.nu_post - 1) {
+    if (l == 0 && x == m->z && it == m->p.nu_post - 1) {
       // the solver's own z: the sweep writes into t0 and the two swap roles
-      if (m->want_rz)
+      if (plane) {
+        const int nb = launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 1, 2, x, m->t0, b,
+                                      L.dinv, om, m->want_rz ? m->part_rz : nullptr, s);
+        if (m->want_rz) m->rz_nb = nb;
+      } else if (m->want_rz)
         m->rz_nb = launch_ebe_jacobi_dot(G, m->wk, m->E, m->mask, x, b, L.dinv, om, m->t0,
                                          m->part_rz, s, m->tz64);
       else
@@ -887,7 +897,7 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
       L.t = m->t0;
       continue;
     }
-    if (fuse && l >= 1 && it == m->p.nu_post - 1) {
+    if (l >= 1 && it == m->p.nu_post - 1) {
       if (x != L.x) return fail(AARMR_E_STATE, "V-cycle iterate is not the level's buffer");
       TRY(level_product(m, l, 1, x, L.t, b, s));
       std::swap(L.x, L.t);
@@ -1583,34 +1593,28 @@ int pcg64(aarmr_mesh* m, double* x, int* iters, double* relres, int maxit_in, hi
     // direction update: they read r and write only z and p, so when the
     // iteration turns out to be the last, x and r are final and that work is
     // simply unused.
-    double* part_pq = m->partial;
-    double* part_rz = m->partial + kRedBlocks;
+    double* part_rz = m->partial;  // when the V-cycle leaves none (nu_post = 0)
     double* part_rr = m->hrr_dev;  // fused_blocks(n3) + 1 entries, in host memory
     const int nb = fused_blocks(n3);
     const bool z0 = m->p.nu_pre >= 1;
     const double* hrr = m->hrr;
-    // 3D: p^T A p comes with the product and r^T z with the V-cycle's last
-    // fine sweep (workgroup partials of the EbE kernel)
-    const bool ebe_dots = m->dim == 3;
+    // p^T A p comes with the product and r^T z with the V-cycle's last fine
+    // sweep (workgroup partials of those kernels)
     for (int it = 0; it < maxit; ++it) {
-      int n_pq = 0;
-      if (ebe_dots) {
-        n_pq = launch_ebe_dot(g, m->wk, m->E, m->mask, m->pv, m->q, m->part_pq, s, m->tz64);
-        ++m->sweeps;
-        KCHECK();
-      } else {
-        TRY(apply(m, 0, m->pv, m->q, s));
-        launch_dot_partials(n3, m->pv, m->q, part_pq, s);
-      }
-      launch_cg_xr_fused(n3, sc + SC_RZ + it, ebe_dots ? m->part_pq : part_pq, n_pq,
-                         sc + SC_PQ + it, x, m->r, m->pv, m->q, part_rr, m->lv[0].dinv,
-                         m->p.omega, z0 ? m->z : nullptr, s);
+      const int n_pq =
+          m->dim == 2 ? launch_q4_fine(g, m->KEd, m->E, m->mask, m->springs, 0, 2, m->pv, m->q,
+                                       nullptr, nullptr, 0.0, m->part_pq, s)
+                      : launch_ebe_dot(g, m->wk, m->E, m->mask, m->pv, m->q, m->part_pq, s, m->tz64);
+      ++m->sweeps;
+      KCHECK();
+      launch_cg_xr_fused(n3, sc + SC_RZ + it, m->part_pq, n_pq, sc + SC_PQ + it, x, m->r, m->pv,
+                         m->q, part_rr, m->lv[0].dinv, m->p.omega, z0 ? m->z : nullptr, s);
       KCHECK();
       // the update stored the r^T r partials and the finished p^T q (after
       // them) into host memory: the event marks them complete
       HIP_TRY(hipEventRecord(m->ev_cg, s));
       if (it + 1 < maxit) {
-        m->want_rz = ebe_dots;
+        m->want_rz = true;
         m->rz_nb = 0;
         const int rc = vcycle(m, 0, m->r, m->z, s, z0);
         m->want_rz = false;

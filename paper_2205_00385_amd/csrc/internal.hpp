@@ -197,7 +197,7 @@ void launch_jacobi_first(int64_t n3, const double* b, const double* dinv, double
 // xc = omega dinv_c bc.
 void launch_restrict_jacobi(const Grid& coarse, const double* bf, const double* tf,
                             const uint8_t* mask, double* bc, const double* dinv_c, double omega,
-                            double* xc, hipStream_t s);
+                            double* xc, hipStream_t s, int ncomp);
 void launch_jacobi_update(int64_t n3, const double* b, const double* t, const double* dinv,
                           double omega, double* x, hipStream_t s);
 // The dense coarsest operator with its unknowns in the order o, and its
@@ -296,9 +296,6 @@ constexpr int kSymEntries2 = 36;
 __host__ __device__ constexpr int sym_index2(int r, int c) {
   return r <= c ? r * 8 - (r * (r - 1)) / 2 + (c - r) : c * 8 - (c * (c - 1)) / 2 + (r - c);
 }
-// mode as for launch_ebe
-void launch_q4_apply(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
-                     const double* v, double* y, int mode, hipStream_t s);
 // energy_e = u_e^T KE w_e (w = u: strain energy)
 void launch_q4_energy(const Grid& g, const double* KE, const uint8_t* mask, const double* u,
                       const double* w, double* energy, hipStream_t s);
@@ -308,8 +305,19 @@ struct SpringSet {
   int64_t dof[AARMR_MAX_SPRINGS];
   double k[AARMR_MAX_SPRINGS];
 };
-void launch_springs_add(const SpringSet& S, const Grid& g, const uint8_t* mask, const double* v,
-                        double* y, hipStream_t s);
+// Product of the fine operator.  mode 0: y = A v; 1: y = v + omega dinv (b -
+// A v), y distinct from v; 2: y = b - A v.  in: 0 any input, identity rows on
+// fixed DOFs; 1 any input, zero rows; 2 an input that is zero there.  part
+// (or null): partials of v . y (mode 0) or b . y (mode 1), at most
+// q4_partials_max(g); the return value is their number.
+int q4_partials_max(const Grid& g);
+int launch_q4_fine(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
+                   const SpringSet& S, int mode, int in, const double* v, double* y,
+                   const double* b, const double* dinv, double omega, double* part,
+                   hipStream_t s);
+// The same modes for a coarse level's element matrices.
+void launch_q4_coarse(const Grid& g, const double* Ke, int mode, const double* v, double* y,
+                      const double* b, const double* dinv, double omega, hipStream_t s);
 void launch_springs_diag(const SpringSet& S, const Grid& g, const uint8_t* mask, double* dinv,
                          hipStream_t s);
 // level-1 contribution (Df P)^T S (Df P); coarse = the level-1 grid
@@ -322,8 +330,6 @@ void launch_q4_galerkin_from_fine(const Grid& coarse, const double* KE, const do
                                   const uint8_t* mask, double* Kc, hipStream_t s);
 void launch_q4_galerkin_from_coarse(const Grid& coarse, const double* Kf, double* Kc,
                                     hipStream_t s);
-void launch_q4_apply_elemmat(const Grid& g, const double* Ke, const double* v, double* y,
-                             hipStream_t s);
 void launch_q4_diag_elemmat(const Grid& g, const double* Ke, double* dinv, hipStream_t s);
 void launch_q4_assemble_dense(const Grid& g, const CoarseOrder& o, const double* Ke, double* A,
                               hipStream_t s);

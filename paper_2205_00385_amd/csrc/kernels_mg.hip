@@ -591,12 +591,12 @@ void launch_restrict(const Grid& coarse, const double* bf, const double* tf, con
 
 void launch_restrict_jacobi(const Grid& coarse, const double* bf, const double* tf,
                             const uint8_t* mask, double* bc, const double* dinv_c, double omega,
-                            double* xc, hipStream_t s) {
+                            double* xc, hipStream_t s, int ncomp) {
   if (coarse.nz > 0 && coarse.nn >= kRsMinNodes) {
     restrict_z<double>(coarse, bf, tf, mask, bc, dinv_c, omega, xc, s, 1, 0, 0);
     return;
   }
-  k_restrict<double><<<dim3(nblk(coarse.nn, 64), 3), 192, 0, s>>>(coarse.nx, coarse.ny, coarse.nz,
+  k_restrict<double><<<dim3(nblk(coarse.nn, 64), ncomp), 192, 0, s>>>(coarse.nx, coarse.ny, coarse.nz,
                                                                   bf, tf, mask, bc, dinv_c, omega,
                                                                   xc, natural(coarse));
 }

@@ -3,6 +3,8 @@
 // diagonal, and the 2D Galerkin hierarchy (Algorithm 2) with 8x8 coarse
 // element matrices.  Grids are nx x ny unit squares, nodes x-fastest
 // (i + (nx+1) j), local corner a = dx + 2 dy, DOF vectors SoA [2][n_node].
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace aarmr {
@@ -14,48 +16,104 @@ inline unsigned nblk(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); 
 __host__ __device__ constexpr int s2(int r, int c) { return sym_index2(r, c); }
 
 // Weight of parent corner A (0/1) at refined position pos (0, 1, 2) along an axis.
-__device__ inline double phi1q(int pos, int A) {
+__host__ __device__ constexpr double phi1q(int pos, int A) {
   return pos == 1 ? 0.5 : ((pos >> 1) == A ? 1.0 : 0.0);
 }
 
-// y = A v (mode 0), Df K Df v (mode 1) or Df K v for a v zero on fixed DOFs
-// (mode 2): thread per node, the (up to) 4 adjacent elements in corner order.
-__global__ void __launch_bounds__(256) k_q4_apply(int nx, int ny, const double* __restrict__ KE,
-                                                  const double* __restrict__ E,
-                                                  const uint8_t* __restrict__ mask,
-                                                  const double* __restrict__ v,
-                                                  double* __restrict__ y, int mode) {
-  const int64_t nn = (int64_t)(nx + 1) * (ny + 1);
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nn) return;
-  const int i = (int)(n % (nx + 1)), j = (int)(n / (nx + 1));
-  double acc0 = 0.0, acc1 = 0.0;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
+// Product of the fine operator (FINE: moduli E, masks, springs) or of a coarse
+// level's packed element matrices Ke.  MODE 0: y = A v; 1: a damped-Jacobi
+// sweep, y = v + omega dinv (b - A v), y distinct from v; 2: the residual
+// y = b - A v.  On fixed DOFs A v is v with identity rows (in = 0), else 0; in:
+// 0 any input with identity rows, 1 any input, 2 an input that is zero there.
+// With part non-null each workgroup also writes part[blockIdx.x], its sum of
+// v . y (MODE 0) or b . y (MODE 1): the partials of CG's dot products.
+//
+// These launches are bound by their chain of loads, not by bytes: wavefront a
+// of a workgroup takes the elements of which its 64 nodes are corner a, so a
+// thread has one element's loads, all in flight, and row pairs of the fine KE
+// are wave-uniform; the four sums meet in LDS, where wavefront c finishes
+// component c with operands it loaded at the start.  At 320x160 a thread per
+// node took 6.5 us for the fine product, 5.4 us for a coarse one and 2.8 us
+// each for the sweep and the dot products; 4.0 to 4.8 us (fine) and 3.7 us
+// (coarse) for all of it now.
+constexpr int kQ4Nodes = 64, kQ4Blocks = 1024;
+template <bool FINE, int MODE>
+__global__ void __launch_bounds__(4 * kQ4Nodes) k_q4_product(
+    int nx, int ny, const double* __restrict__ Kmat, const double* __restrict__ E,
+    const uint8_t* __restrict__ mask, int in, const double* __restrict__ v,
+    double* __restrict__ y, const double* __restrict__ b, const double* __restrict__ dinv,
+    double omega, double* __restrict__ part, SpringSet S) {
+  __shared__ double sums[4][2][kQ4Nodes], dots[2];
+  const uint32_t nxp = nx + 1, nn = nxp * (ny + 1), ne = (uint32_t)nx * ny;
+  const int lane = threadIdx.x & 63, a = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double dacc = 0.0;
+  for (uint32_t base = blockIdx.x * kQ4Nodes; base < nn; base += gridDim.x * kQ4Nodes) {
+    const uint32_t n = base + lane, nc = n < nn ? n : nn - 1;
+    const int j = (int)(nc / nxp), i = (int)(nc - (uint32_t)j * nxp);
     const int ex = i - (a & 1), ey = j - (a >> 1);
-    if (ex < 0 || ex >= nx || ey < 0 || ey >= ny) continue;
-    const double w = E[(int64_t)ex + (int64_t)nx * ey];
-    double t0 = 0.0, t1 = 0.0;
+    const bool eok = ex >= 0 && ex < nx && ey >= 0 && ey < ny;
+    const uint32_t cx = min(max(ex, 0), nx - 1), cy = min(max(ey, 0), ny - 1);
+    const uint32_t e = cx + (uint32_t)nx * cy;
+    // what finishes component a of node nc
+    double vn = 0.0, bn = 0.0, dn = 0.0;
+    uint32_t mn = 0;
+    if (a < 2) {
+      const int64_t d = (int64_t)a * nn + nc;
+      vn = v[d];
+      if (MODE) bn = b[d];
+      if (MODE == 1) dn = dinv[d];
+      if (FINE) mn = mask[nc];
+    }
+    double ve[8], k0[8], k1[8];
+    uint32_t me[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int64_t nb = (int64_t)(ex + (b & 1)) + (int64_t)(nx + 1) * (ey + (b >> 1));
-      const uint8_t mb = (mode != 2) ? mask[nb] : 0;
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t nb = cx + (c & 1) + nxp * (cy + (c >> 1));
+      ve[2 * c] = v[nb];
+      ve[2 * c + 1] = v[(int64_t)nn + nb];
+      if (FINE && in != 2) me[c] = mask[nb];
+    }
+    const double w = FINE ? E[e] : 1.0;
 #pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        const double vb = ((mb >> d) & 1) ? 0.0 : v[d * nn + nb];
-        t0 = fma(KE[(2 * a) * 8 + 2 * b + d], vb, t0);
-        t1 = fma(KE[(2 * a + 1) * 8 + 2 * b + d], vb, t1);
+    for (int q = 0; q < 8; ++q) {
+      if (FINE) {
+        k0[q] = Kmat[16 * a + q];
+        k1[q] = Kmat[16 * a + 8 + q];
+      } else {
+        k0[q] = Kmat[(int64_t)s2(2 * a, q) * ne + e];
+        k1[q] = Kmat[(int64_t)s2(2 * a + 1, q) * ne + e];
       }
     }
-    acc0 = fma(w, t0, acc0);
-    acc1 = fma(w, t1, acc1);
-  }
-  const uint8_t m = mask[n];
-  const double r[2] = {acc0, acc1};
+    double t0 = 0.0, t1 = 0.0;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const bool fx = (m >> c) & 1;
-    y[c * nn + n] = fx ? (mode == 0 ? v[c * nn + n] : 0.0) : r[c];
+    for (int q = 0; q < 8; ++q) {
+      const double x = ((me[q >> 1] >> (q & 1)) & 1u) ? 0.0 : ve[q];
+      t0 = fma(k0[q], x, t0);
+      t1 = fma(k1[q], x, t1);
+    }
+    sums[a][0][lane] = eok ? w * t0 : 0.0;
+    sums[a][1][lane] = eok ? w * t1 : 0.0;
+    __syncthreads();
+    if (a < 2 && n < nn) {
+      const int64_t d = (int64_t)a * nn + n;
+      double Av = (sums[0][a][lane] + sums[1][a][lane]) + (sums[2][a][lane] + sums[3][a][lane]);
+      if (FINE) {
+        for (int t = 0; t < S.n; ++t)
+          if (S.dof[t] == d) Av = fma(S.k[t], vn, Av);
+        if ((mn >> a) & 1u) Av = in == 0 ? vn : 0.0;
+      }
+      const double out = MODE == 0 ? Av : MODE == 1 ? fma(omega * dn, bn - Av, vn) : bn - Av;
+      y[d] = out;
+      dacc = fma(MODE ? bn : vn, out, dacc);
+    }
+    __syncthreads();  // the sums are read before the next nodes' are written
+  }
+  if (part) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) dacc += __shfl_down(dacc, off, 64);
+    if (a < 2 && lane == 0) dots[a] = dacc;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = dots[0] + dots[1];
   }
 }
 
@@ -108,86 +166,83 @@ __global__ void k_q4_diag(int nx, int ny, const double* __restrict__ KE,
   for (int c = 0; c < 2; ++c) dinv[c * nn + n] = (((m >> c) & 1) || d[c] == 0.0) ? 1.0 : 1.0 / d[c];
 }
 
+// acc += P_c^T K P_c for child c of a parent (upper triangles, packed), P_c
+// the child's bilinear interpolation from the parent's corners.
+template <int C>
+__device__ __forceinline__ void galerkin_child(const double (&K)[kSymEntries2],
+                                               double (&acc)[kSymEntries2]) {
+  constexpr int dx = C & 1, dy = C >> 1;
+#pragma unroll
+  for (int I = 0; I < 8; ++I)
+#pragma unroll
+    for (int J = I; J < 8; ++J)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const double pa = phi1q(dx + (a & 1), (I >> 1) & 1) * phi1q(dy + (a >> 1), I >> 2);
+        if (pa == 0.0) continue;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const double pb = phi1q(dx + (b & 1), (J >> 1) & 1) * phi1q(dy + (b >> 1), J >> 2);
+          if (pb != 0.0)
+            acc[s2(I, J)] = fma(pa * pb, K[s2(2 * a + (I & 1), 2 * b + (J & 1))], acc[s2(I, J)]);
+        }
+      }
+}
+
 // Galerkin matrix of every parent of the coarse grid (cnx x cny), one thread
-// per parent: Kc[I][J] = sum over children c and their corners a, b of
-// P_c[a][I/2] P_c[b][J/2] K_c[2a + I%2][2b + J%2].  FROM_FINE: K_c = E_c KE
-// with the rows and columns of fixed fine DOFs removed (masked P);
-// otherwise K_c is the previous level's packed matrix.
+// per parent: Kc = sum over the four children c of P_c^T K_c P_c.  FROM_FINE:
+// K_c = E_c KE with the rows and columns of fixed fine DOFs removed (masked
+// P); otherwise K_c is the previous level's packed matrix.  A child's 36
+// entries are loaded at once and its share of all 36 sums formed in
+// registers; small workgroups spread a level over the device (parents of
+// 320x160, 160x80 and 80x40 children: 70, 122 and 122 us with a loop over
+// entries that loaded operand by operand, 13.4, 6.2 and 6.2 us now).
+template <bool FROM_FINE, int C>
+__device__ __forceinline__ void galerkin_add(int cx, int cy, int cnx, int64_t fne,
+                                             const double* __restrict__ KE,
+                                             const double* __restrict__ E,
+                                             const uint8_t* __restrict__ mask,
+                                             const double* __restrict__ Kf,
+                                             double (&acc)[kSymEntries2]) {
+  const int fx = 2 * cx + (C & 1), fy = 2 * cy + (C >> 1);
+  const int64_t fe = fx + (int64_t)(2 * cnx) * fy;
+  double K[kSymEntries2];
+  if (FROM_FINE) {
+    const double w = E[fe];
+    uint32_t fixed = 0;  // bit 2 a + c: DOF c of corner a
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      fixed |= (mask[fx + (a & 1) + (int64_t)(2 * cnx + 1) * (fy + (a >> 1))] & 3u) << (2 * a);
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+      for (int q = r; q < 8; ++q)
+        K[s2(r, q)] = (((fixed >> r) | (fixed >> q)) & 1u) ? 0.0 : w * KE[r * 8 + q];
+  } else {
+#pragma unroll
+    for (int t = 0; t < kSymEntries2; ++t) K[t] = Kf[(int64_t)t * fne + fe];
+  }
+  galerkin_child<C>(K, acc);
+}
 template <bool FROM_FINE>
-__global__ void __launch_bounds__(256) k_q4_galerkin(int cnx, int cny, const double* __restrict__ KE,
-                                                     const double* __restrict__ E,
-                                                     const uint8_t* __restrict__ mask,
-                                                     const double* __restrict__ Kf,
-                                                     double* __restrict__ Kc) {
+__global__ void __launch_bounds__(64) k_q4_galerkin(int cnx, int cny, const double* __restrict__ KE,
+                                                    const double* __restrict__ E,
+                                                    const uint8_t* __restrict__ mask,
+                                                    const double* __restrict__ Kf,
+                                                    double* __restrict__ Kc) {
   const int64_t cne = (int64_t)cnx * cny;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= cne) return;
-  const int cx = (int)(e % cnx), cy = (int)(e / cnx);
-  const int fnx = 2 * cnx;
-  const int64_t fne = cne * 4;
-  double w[4];
-  int64_t fe[4];
-  uint8_t fm[9];
+  const int cy = (int)(e / cnx), cx = (int)(e - (int64_t)cy * cnx);
+  double acc[kSymEntries2];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    fe[c] = (int64_t)(2 * cx + (c & 1)) + (int64_t)fnx * (2 * cy + (c >> 1));
-    w[c] = FROM_FINE ? E[fe[c]] : 0.0;
-  }
-  if (FROM_FINE)
-    for (int t = 0; t < 9; ++t)
-      fm[t] = mask[(int64_t)(2 * cx + t % 3) + (int64_t)(fnx + 1) * (2 * cy + t / 3)];
-  for (int I = 0; I < 8; ++I)
-    for (int J = I; J < 8; ++J) {
-      const int A = I >> 1, ci = I & 1, B = J >> 1, cj = J & 1;
-      double acc = 0.0;
-      for (int c = 0; c < 4; ++c) {
-        const int dx = c & 1, dy = c >> 1;
-        for (int a = 0; a < 4; ++a) {
-          const double pa = phi1q(dx + (a & 1), A & 1) * phi1q(dy + (a >> 1), A >> 1);
-          if (pa == 0.0) continue;
-          if (FROM_FINE && ((fm[(dx + (a & 1)) + 3 * (dy + (a >> 1))] >> ci) & 1)) continue;
-          for (int b = 0; b < 4; ++b) {
-            const double pb = phi1q(dx + (b & 1), B & 1) * phi1q(dy + (b >> 1), B >> 1);
-            if (pb == 0.0) continue;
-            if (FROM_FINE && ((fm[(dx + (b & 1)) + 3 * (dy + (b >> 1))] >> cj) & 1)) continue;
-            const int r = 2 * a + ci, q = 2 * b + cj;
-            const double k = FROM_FINE ? w[c] * KE[r * 8 + q] : Kf[(int64_t)s2(r, q) * fne + fe[c]];
-            acc = fma(pa * pb, k, acc);
-          }
-        }
-      }
-      Kc[(int64_t)s2(I, J) * cne + e] = acc;
-    }
-}
-
-// y = sum_e L_e^T Ke_e L_e v for packed 8x8 element matrices; thread per node.
-template <typename T>
-__global__ void __launch_bounds__(256) k_q4_apply_elemmat(int nx, int ny, const double* __restrict__ Ke,
-                                                          const T* __restrict__ v, T* __restrict__ y) {
-  const int64_t nn = (int64_t)(nx + 1) * (ny + 1);
-  const int64_t ne = (int64_t)nx * ny;
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nn) return;
-  const int i = (int)(n % (nx + 1)), j = (int)(n / (nx + 1));
-  T acc0 = 0, acc1 = 0;
+  for (int t = 0; t < kSymEntries2; ++t) acc[t] = 0.0;
+  galerkin_add<FROM_FINE, 0>(cx, cy, cnx, 4 * cne, KE, E, mask, Kf, acc);
+  galerkin_add<FROM_FINE, 1>(cx, cy, cnx, 4 * cne, KE, E, mask, Kf, acc);
+  galerkin_add<FROM_FINE, 2>(cx, cy, cnx, 4 * cne, KE, E, mask, Kf, acc);
+  galerkin_add<FROM_FINE, 3>(cx, cy, cnx, 4 * cne, KE, E, mask, Kf, acc);
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int ex = i - (a & 1), ey = j - (a >> 1);
-    if (ex < 0 || ex >= nx || ey < 0 || ey >= ny) continue;
-    const int64_t e = (int64_t)ex + (int64_t)nx * ey;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int64_t nb = (int64_t)(ex + (b & 1)) + (int64_t)(nx + 1) * (ey + (b >> 1));
-#pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        const T vb = v[d * nn + nb];
-        acc0 = fma((T)Ke[(int64_t)s2(2 * a, 2 * b + d) * ne + e], vb, acc0);
-        acc1 = fma((T)Ke[(int64_t)s2(2 * a + 1, 2 * b + d) * ne + e], vb, acc1);
-      }
-    }
-  }
-  y[n] = acc0;
-  y[nn + n] = acc1;
+  for (int t = 0; t < kSymEntries2; ++t) Kc[(int64_t)t * cne + e] = acc[t];
 }
 
 __global__ void k_q4_diag_elemmat(int nx, int ny, const double* __restrict__ Ke,
@@ -208,17 +263,7 @@ __global__ void k_q4_diag_elemmat(int nx, int ny, const double* __restrict__ Ke,
 }
 
 // Grounded springs (one thread each; the host merges repeated DOFs, so no
-// two threads touch one DOF).  y += k v on free spring DOFs.
-__global__ void k_springs_add(SpringSet S, int64_t nn, const uint8_t* __restrict__ mask,
-                              const double* __restrict__ v, double* __restrict__ y) {
-  const int t = threadIdx.x;
-  if (t >= S.n) return;
-  const int64_t d = S.dof[t];
-  const int64_t node = d % nn;
-  if ((mask[node] >> (int)(d / nn)) & 1) return;
-  y[d] = fma(S.k[t], v[d], y[d]);
-}
-
+// two threads touch one DOF).
 // The inverse Jacobi diagonal with the spring stiffness added.
 __global__ void k_springs_diag(SpringSet S, int64_t nn, const uint8_t* __restrict__ mask,
                                double* __restrict__ dinv) {
@@ -298,19 +343,34 @@ __global__ void __launch_bounds__(256) k_q4_assemble_dense(int nx, int ny, Coars
 
 }  // namespace
 
-void launch_q4_apply(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
-                     const double* v, double* y, int mode, hipStream_t s) {
-  k_q4_apply<<<nblk(g.nn, 256), 256, 0, s>>>(g.nx, g.ny, KE, E, mask, v, y, mode);
+int q4_partials_max(const Grid& g) {
+  return (int)std::min<int64_t>((g.nn + kQ4Nodes - 1) / kQ4Nodes, kQ4Blocks);
+}
+
+int launch_q4_fine(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
+                   const SpringSet& S, int mode, int in, const double* v, double* y,
+                   const double* b, const double* dinv, double omega, double* part,
+                   hipStream_t s) {
+  const int nb = q4_partials_max(g);
+  auto k = mode == 1   ? k_q4_product<true, 1>
+           : mode == 2 ? k_q4_product<true, 2>
+                       : k_q4_product<true, 0>;
+  k<<<nb, 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, KE, E, mask, in, v, y, b, dinv, omega, part, S);
+  return nb;
+}
+
+void launch_q4_coarse(const Grid& g, const double* Ke, int mode, const double* v, double* y,
+                      const double* b, const double* dinv, double omega, hipStream_t s) {
+  auto k = mode == 1   ? k_q4_product<false, 1>
+           : mode == 2 ? k_q4_product<false, 2>
+                       : k_q4_product<false, 0>;
+  k<<<q4_partials_max(g), 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, Ke, nullptr, nullptr, 2, v, y, b, dinv,
+                                                omega, nullptr, SpringSet{});
 }
 
 void launch_q4_energy(const Grid& g, const double* KE, const uint8_t* mask, const double* u,
                       const double* w, double* energy, hipStream_t s) {
   k_q4_energy<<<nblk(g.ne, 256), 256, 0, s>>>(g.nx, g.ny, KE, mask, u, w, energy);
-}
-
-void launch_springs_add(const SpringSet& S, const Grid& g, const uint8_t* mask, const double* v,
-                        double* y, hipStream_t s) {
-  if (S.n > 0) k_springs_add<<<1, 64, 0, s>>>(S, g.nn, mask, v, y);
 }
 
 void launch_springs_diag(const SpringSet& S, const Grid& g, const uint8_t* mask, double* dinv,
@@ -330,19 +390,14 @@ void launch_q4_diag(const Grid& g, const double* KE, const double* E, const uint
 
 void launch_q4_galerkin_from_fine(const Grid& coarse, const double* KE, const double* E,
                                   const uint8_t* mask, double* Kc, hipStream_t s) {
-  k_q4_galerkin<true><<<nblk(coarse.ne, 256), 256, 0, s>>>(coarse.nx, coarse.ny, KE, E, mask,
+  k_q4_galerkin<true><<<nblk(coarse.ne, 64), 64, 0, s>>>(coarse.nx, coarse.ny, KE, E, mask,
                                                            nullptr, Kc);
 }
 
 void launch_q4_galerkin_from_coarse(const Grid& coarse, const double* Kf, double* Kc,
                                     hipStream_t s) {
-  k_q4_galerkin<false><<<nblk(coarse.ne, 256), 256, 0, s>>>(coarse.nx, coarse.ny, nullptr,
+  k_q4_galerkin<false><<<nblk(coarse.ne, 64), 64, 0, s>>>(coarse.nx, coarse.ny, nullptr,
                                                             nullptr, nullptr, Kf, Kc);
-}
-
-void launch_q4_apply_elemmat(const Grid& g, const double* Ke, const double* v, double* y,
-                             hipStream_t s) {
-  k_q4_apply_elemmat<double><<<nblk(g.nn, 256), 256, 0, s>>>(g.nx, g.ny, Ke, v, y);
 }
 
 void launch_q4_diag_elemmat(const Grid& g, const double* Ke, double* dinv, hipStream_t s) {
