@@ -783,7 +783,7 @@ int level_product32(aarmr_mesh* m, int l, int mode, const float* v, float* y, co
 // y = A v on level l.  Inside the solvers every vector is zero on fixed
 // DOFs (loads and initial guesses are masked, and A, the smoother and the
 // masked transfer operators preserve that), so the fine product skips input
-// masking (mode 2); `any_input` selects the general form.
+// masking; `any_input` selects the general form.
 // Fine product with moduli E (the current design's, the reference design's
 // or their difference): y = Df K(E) v for a v zero on fixed DOFs, plus the
 // springs unless the product is the change K - K0 (with_springs false).
@@ -793,7 +793,7 @@ int fine_product(aarmr_mesh* m, const double* E, const double* v, double* y, hip
     launch_q4_fine(m->lg[0], m->KEd, E, m->mask, with_springs ? m->springs : SpringSet{}, 0, 2, v,
                    y, nullptr, nullptr, 0.0, nullptr, s);
   } else
-    launch_ebe(m->lg[0], m->wk, E, m->mask, v, y, 2, s);
+    launch_ebe(m->lg[0], m->wk, E, m->mask, v, y, false, s);
   ++m->sweeps;
   KCHECK();
   return AARMR_OK;
@@ -809,7 +809,7 @@ int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
     return AARMR_OK;
   }
   if (l == 0) {
-    launch_ebe(m->lg[0], m->wk, m->E, m->mask, v, y, any_input ? 0 : 2, s, m->tz64);
+    launch_ebe(m->lg[0], m->wk, m->E, m->mask, v, y, any_input, s, m->tz64);
     ++m->sweeps;
   } else {
     return level_product(m, l, 0, v, y, nullptr, s);
@@ -1040,7 +1040,7 @@ int setup(aarmr_mesh* m, const double* rho, const int64_t* fixed, int64_t nfixed
 // y = A v on level l with FP32 vectors (v zero on fixed DOFs).
 int apply32(aarmr_mesh* m, int l, const float* v, float* y, hipStream_t s, int nr = 1) {
   if (l == 0) {
-    launch_ebe_f32(m->lg[0], m->wk, m->E32, m->mask, v, y, 2, s, m->tz32, nr);
+    launch_ebe_f32(m->lg[0], m->wk, m->E32, m->mask, v, y, s, m->tz32, nr);
     ++m->sweeps;
   } else {
     return level_product32(m, l, 0, v, y, nullptr, s, nr);
@@ -2484,7 +2484,7 @@ int aarmr_autotune(aarmr_mesh* m, int32_t* tz_out, void* stream) {
   int best_tz = 0;
   for (int sh : shapes) {
     const float ms = time_one([&] {
-      launch_ebe(g, m->wk, m->ework, m->mask, m->q, m->t0, 2, s, sh);
+      launch_ebe(g, m->wk, m->ework, m->mask, m->q, m->t0, false, s, sh);
     });
     if (ms < best) { best = ms; best_tz = sh; }
   }
@@ -2498,7 +2498,7 @@ int aarmr_autotune(aarmr_mesh* m, int32_t* tz_out, void* stream) {
     best_tz = 0;
     for (int sh : shapes) {
       const float ms = time_one([&] {
-        launch_ebe_f32(g, m->wk, m->d32, m->mask, m->q32, m->p32, 2, s, sh);
+        launch_ebe_f32(g, m->wk, m->d32, m->mask, m->q32, m->p32, s, sh);
       });
       if (ms < best) { best = ms; best_tz = sh; }
     }

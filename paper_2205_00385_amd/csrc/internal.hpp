@@ -66,24 +66,22 @@ struct DotSetT {
 using DotSet = DotSetT<double>;
 
 // ---- fine-level operator (element-by-element, reflection-blocked) --------
-// mode 0: y = A v = Df K Df v + (I - Df) v for any v; mode 1: y = Df K Df v;
-// mode 2: y = Df K v for a v that is zero on fixed DOFs (then equal to both
-// A v and Df K Df v), the form every solver-internal product uses.
-// tz: z-chunk length (node planes per workgroup); <= 0 takes the default
-// sized from the kernel's residency (one round of workgroups fills the GPU).
+// y = A v = Df K Df v + (I - Df) v for any v (any_input), or y = Df K v for a v
+// that is zero on fixed DOFs (then equal to both A v and Df K Df v), the form
+// every solver-internal product uses.
+// tz: launch shape word, 0 the grid's default shape (kernels_ebe.hip).
 void launch_ebe(const Grid& g, const WalshConsts& K, const double* E, const uint8_t* mask,
-                const double* v, double* y, int mode, hipStream_t s, int tz = 0);
+                const double* v, double* y, bool any_input, hipStream_t s, int tz = 0);
 void launch_ebe_f32(const Grid& g, const WalshConsts& K, const float* E, const uint8_t* mask,
-                    const float* v, float* y, int mode, hipStream_t s, int tz = 0,
-                    int nr = 1);
-// The mode-2 product feeding a damped-Jacobi sweep: out = v + omega dinv
+                    const float* v, float* y, hipStream_t s, int tz = 0, int nr = 1);
+// The solver's product feeding a damped-Jacobi sweep: out = v + omega dinv
 // (b - A v), out distinct from v.
 void launch_ebe_jacobi(const Grid& g, const WalshConsts& K, const double* E, const uint8_t* mask,
                        const double* v, const double* b, const double* dinv, double omega,
                        double* out, hipStream_t s, int tz = 0);
 // The same two products with CG's dot product folded in: each workgroup w
 // writes part[w], the sum over the nodes it owns of v . y (launch_ebe_dot,
-// mode 2: p^T A p) or b . out (launch_ebe_jacobi_dot: r^T z); the return
+// p^T A p) or b . out (launch_ebe_jacobi_dot: r^T z); the return
 // value is the number of partials.  part holds ebe_partials_max(g) entries.
 int ebe_partials_max(const Grid& g);
 int launch_ebe_dot(const Grid& g, const WalshConsts& K, const double* E, const uint8_t* mask,

@@ -121,9 +121,11 @@ struct PlaneRaw {
   uint32_t m0, m2;
 };
 
-// y = Df K Df v (zero on fixed DOFs).  MASK_IN: zero the fixed DOFs of v on
-// load; without it the caller guarantees that v is already zero there (true
-// of every vector inside the solvers), which saves the loads and selects.
+// y = Df K Df v.  MASK_IN: any v; its fixed DOFs are zeroed on load and y is v
+// there (the identity rows of A; as a launch of their own they took 2.6 us of
+// 104x56x40's 12.4 us).  Without it the caller guarantees that v is already
+// zero there (true of every vector inside the solvers), which saves the loads
+// and selects, and y is zero there.
 // PF: prefetch distance in node planes (1 or 2).  JAC: the product feeds a
 // damped-Jacobi sweep, y = v + omega jd (jb - A v) (y distinct from v); the
 // node's own v, jb and jd are fetched one plane ahead like the moduli.
@@ -142,7 +144,7 @@ __global__ void __launch_bounds__(kLanes * ROWS, AARMR_EBE_MINB) k_ebe_z(int nx,
                                                     const T* __restrict__ jd, T omega,
                                                     double* __restrict__ part, int64_t rs,
                                                     int pst) {
-  constexpr bool OWNV = JAC || DOT;  // keep the node's own v of the plane written next
+  constexpr bool OWNV = JAC || DOT || MASK_IN;  // keep the node's own v of the plane written next
   {  // load case blockIdx.z of a lock-step multi-vector (the moduli, mask and
      // Jacobi diagonal are shared)
     const int64_t ro = (int64_t)blockIdx.z * rs;
@@ -313,7 +315,7 @@ __global__ void __launch_bounds__(kLanes * ROWS, AARMR_EBE_MINB) k_ebe_z(int nx,
     for (int c = 0; c < 3; ++c) {
       T out = X0[c] + xs[buf][c][ty > 0 ? ty - 1 : 0][tx];
       if (JAC) out = own_v[c] + omega * own_d[c] * (own_b[c] - out);
-      if ((own_m >> c) & 1u) out = (T)0;
+      if ((own_m >> c) & 1u) out = MASK_IN ? own_v[c] : (T)0;
       st(ry, oy, out, (uint32_t)c * cstride);
       if (DOT) dacc += wr ? (double)(JAC ? own_b[c] : own_v[c]) * (double)out : 0.0;
     }
@@ -401,19 +403,6 @@ __global__ void __launch_bounds__(256) k_energy_walsh(int nx, int ny, int nz, Wa
 }
 
 }  // namespace
-
-// y[fixed] = v[fixed]: the identity rows of A on fixed DOFs.
-template <typename T>
-__global__ void k_identity_rows(int64_t nn, const uint8_t* __restrict__ mask,
-                                const T* __restrict__ v, T* __restrict__ y) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nn) return;
-  const uint32_t m = mask[n];
-  if (!m) return;
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-    if ((m >> c) & 1u) y[c * nn + n] = v[c * nn + n];
-}
 
 // Prefetch distance: two node planes in flight for the 16-row tile (a
 // 512-thread workgroup leaves registers to spare at its occupancy of two
@@ -565,13 +554,11 @@ int launch_ebe_jacobi_f32_dot(const Grid& g, const WalshConsts& K, const float* 
 }
 
 void launch_ebe(const Grid& g, const WalshConsts& K, const double* E, const uint8_t* mask,
-                const double* v, double* y, int mode, hipStream_t s, int tz) {
-  if (mode == 2) {
+                const double* v, double* y, bool any_input, hipStream_t s, int tz) {
+  if (any_input)
+    launch_ebe_t<double, true>(g, K, E, mask, v, y, tz, s);
+  else
     launch_ebe_t<double, false>(g, K, E, mask, v, y, tz, s);
-    return;
-  }
-  launch_ebe_t<double, true>(g, K, E, mask, v, y, tz, s);
-  if (mode == 0) k_identity_rows<double><<<nblk(g.nn, 256), 256, 0, s>>>(g.nn, mask, v, y);
 }
 
 void launch_ebe_jacobi(const Grid& g, const WalshConsts& K, const double* E, const uint8_t* mask,
@@ -581,13 +568,8 @@ void launch_ebe_jacobi(const Grid& g, const WalshConsts& K, const double* E, con
 }
 
 void launch_ebe_f32(const Grid& g, const WalshConsts& K, const float* E, const uint8_t* mask,
-                    const float* v, float* y, int mode, hipStream_t s, int tz, int nr) {
-  if (mode == 2) {
-    launch_ebe_t<float, false>(g, K, E, mask, v, y, tz, s, nullptr, nullptr, 0.0f, nullptr, nr);
-    return;
-  }
-  launch_ebe_t<float, true>(g, K, E, mask, v, y, tz, s);
-  if (mode == 0) k_identity_rows<float><<<nblk(g.nn, 256), 256, 0, s>>>(g.nn, mask, v, y);
+                    const float* v, float* y, hipStream_t s, int tz, int nr) {
+  launch_ebe_t<float, false>(g, K, E, mask, v, y, tz, s, nullptr, nullptr, 0.0f, nullptr, nr);
 }
 
 void launch_energy_walsh(const Grid& g, const WalshConsts& K, const uint8_t* mask,
