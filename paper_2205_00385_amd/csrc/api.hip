@@ -743,11 +743,27 @@ int level_counts(aarmr_mesh* m, hipStream_t s) {
   return AARMR_OK;
 }
 
-// What the product of coarse level l reads (3D).
-LevelArgs level_args(const aarmr_mesh* m, int l) {
+// What the product of coarse level l reads (3D).  Under stream capture the
+// launch is sized for every node and takes the count of special nodes from the
+// device: the host can't wait for it there, and a replay after another setup
+// has to follow that setup's fixed DOFs.
+int level_args(aarmr_mesh* m, int l, hipStream_t s, LevelArgs* out) {
   const LevelTable& T = m->lt;
-  return LevelArgs{l,          T.nx[l],      T.ny[l],    T.nz[l],    m->nspecial[l], 1.0 / (1 << l),
-                   T.mom[l],   T.special[l], T.nlist[l], T.corner[l], T.Kst[l]};
+  const int* count = nullptr;
+  int n = T.nn[l];  // the coarsest level is special as a whole
+  if (l < m->nlev - 1) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap == hipStreamCaptureStatusActive) {
+      count = T.counts + 2 * l + 1;
+    } else {
+      TRY(level_counts(m, s));
+      n = m->nspecial[l];
+    }
+  }
+  *out = LevelArgs{l,        T.nx[l],      T.ny[l],    T.nz[l],     n,       count, 1.0 / (1 << l),
+                   T.mom[l], T.special[l], T.nlist[l], T.corner[l], T.Kst[l]};
+  return AARMR_OK;
 }
 
 // Product of coarse level l: mode 0 y = A v, 1 a damped-Jacobi sweep, 2 the
@@ -759,8 +775,9 @@ int level_product(aarmr_mesh* m, int l, int mode, const double* v, double* y, co
     KCHECK();
     return AARMR_OK;
   }
-  TRY(level_counts(m, s));
-  launch_level_product(level_args(m, l), m->wk, m->E, mode, v, y, b, m->lv[l].dinv, m->p.omega, s);
+  LevelArgs L;
+  TRY(level_args(m, l, s, &L));
+  launch_level_product(L, m->wk, m->E, mode, v, y, b, m->lv[l].dinv, m->p.omega, s);
   KCHECK();
   return AARMR_OK;
 }

@@ -137,9 +137,11 @@ struct LevelTable {
   int* part = nullptr;                      // level_list_blocks() counts
   int* counts = nullptr;                    // [2 level]: stored elements, [2 level + 1]: special nodes
 };
-// What one level's product reads; nspecial as read back by the host.
+// What one level's product reads; nspecial as read back by the host, or, with
+// count (the number on the device), the most there can be.
 struct LevelArgs {
   int level, nx, ny, nz, nspecial;
+  const int* count;
   double gam;  // 2^-level
   const double* mom;
   const uint8_t* special;

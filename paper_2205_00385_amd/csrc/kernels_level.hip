@@ -565,7 +565,7 @@ __device__ __forceinline__ void special_nodes(const LevelArgs& L, const double* 
   const int nx = L.nx, ny = L.ny, nz = L.nz, nxp = nx + 1, nyp = ny + 1, nn = nxp * nyp * (nz + 1);
   const int64_t ne = (int64_t)nx * ny * nz;
   const int idx = blk * NODES + lane;
-  const bool live = idx < L.nspecial;
+  const bool live = idx < (L.count ? *L.count : L.nspecial);
   const int n = live ? L.nlist[idx] : 0;
   const int64_t w = live ? L.corner[(int64_t)a * nn + idx] : -1;
   double acc[3] = {0.0, 0.0, 0.0};
@@ -812,7 +812,7 @@ void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, con
     }
   }
   // the coarsest level is special as a whole and has no moments: nothing to march
-  const bool whole = L.nspecial == (L.nx + 1) * (L.ny + 1) * (L.nz + 1);
+  const bool whole = !L.count && L.nspecial == (L.nx + 1) * (L.ny + 1) * (L.nz + 1);
   const int nmarch = whole ? 0 : gx * gy * ((planes + tz - 1) / tz);
   const int nsp = (L.nspecial + 4 * kRows - 1) / (4 * kRows);
   k_level_z<LV1, MODE><<<(unsigned)(nmarch + nsp), kLanes * kRows, 0, s>>>(
