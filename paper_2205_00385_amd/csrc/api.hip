@@ -841,12 +841,12 @@ int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
 // kernels: the restriction forms the coarse level's first sweep, and below the
 // finest level the last post-smoothing sweep is the epilogue of its operator
 // product, which writes into L.t, and the level's x and t buffers swap roles,
-// so there x must be L.x; on the finest level this is done only for the
-// solver's own z (m->z, which swaps with t0), a caller's buffer gets the
-// separate sweep.  The product before the restriction forms the residual
-// itself, except that of the finest 3D level.
+// so there x must be L.x; on the finest level x is m->z, and the sweep writes
+// into a caller's buffer `dest`, or into t0, which swaps with m->z.  The
+// product before the restriction forms the residual itself, except that of
+// the finest 3D level.
 int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
-           bool x_init = false) {
+           bool x_init = false, double* dest = nullptr) {
   if (l == m->nlev - 1) {
     launch_gemv(m->nc, m->Ainv, b, x, s);
     KCHECK();
@@ -897,21 +897,24 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
   launch_prolong_add(G, C.x, mask, x, s, m->dim, co);  // line 4
   KCHECK();
   for (int it = 0; it < m->p.nu_post; ++it) {        // line 5
-    if (l == 0 && x == m->z && it == m->p.nu_post - 1) {
-      // the solver's own z: the sweep writes into t0 and the two swap roles
+    if (l == 0 && it == m->p.nu_post - 1) {
+      if (x != m->z) return fail(AARMR_E_STATE, "V-cycle iterate is not the solver's z");
+      double* y = dest ? dest : m->t0;
       if (plane) {
-        const int nb = launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 1, 2, x, m->t0, b,
-                                      L.dinv, om, m->want_rz ? m->part_rz : nullptr, s);
+        const int nb = launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 1, 2, x, y, b, L.dinv,
+                                      om, m->want_rz ? m->part_rz : nullptr, s);
         if (m->want_rz) m->rz_nb = nb;
       } else if (m->want_rz)
-        m->rz_nb = launch_ebe_jacobi_dot(G, m->wk, m->E, m->mask, x, b, L.dinv, om, m->t0,
-                                         m->part_rz, s, m->tz64);
+        m->rz_nb = launch_ebe_jacobi_dot(G, m->wk, m->E, m->mask, x, b, L.dinv, om, y, m->part_rz,
+                                         s, m->tz64);
       else
-        launch_ebe_jacobi(G, m->wk, m->E, m->mask, x, b, L.dinv, om, m->t0, s, m->tz64);
+        launch_ebe_jacobi(G, m->wk, m->E, m->mask, x, b, L.dinv, om, y, s, m->tz64);
       ++m->sweeps;
       KCHECK();
-      std::swap(m->z, m->t0);
-      L.t = m->t0;
+      if (!dest) {
+        std::swap(m->z, m->t0);
+        L.t = m->t0;
+      }
       continue;
     }
     if (l >= 1 && it == m->p.nu_post - 1) {
@@ -924,6 +927,8 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
     launch_jacobi_update(n3, b, L.t, L.dinv, om, x, s);
     KCHECK();
   }
+  if (dest && m->p.nu_post == 0)
+    HIP_TRY(hipMemcpyAsync(dest, x, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
   return AARMR_OK;
 }
 
@@ -2002,7 +2007,7 @@ int aarmr_vcycle(aarmr_mesh* m, const double* r, double* z, void* stream) {
   TRY(need_ws(m));
   if (!r || !z || r == z) return fail(AARMR_E_INVALID, "r, z must be distinct non-null");
   if (!m->mg_ready) return fail(AARMR_E_STATE, "no hierarchy: call aarmr_setup");
-  return vcycle(m, 0, r, z, S(stream));
+  return vcycle(m, 0, r, m->z, S(stream), false, z);
 }
 
 int aarmr_element_energy(aarmr_mesh* m, const double* u, double* energy, void* stream) {

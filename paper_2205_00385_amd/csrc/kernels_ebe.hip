@@ -127,7 +127,8 @@ struct PlaneRaw {
 // zero there (true of every vector inside the solvers), which saves the loads
 // and selects, and y is zero there.
 // PF: prefetch distance in node planes (1 or 2).  JAC: the product feeds a
-// damped-Jacobi sweep, y = v + omega jd (jb - A v) (y distinct from v); the
+// damped-Jacobi sweep, y = v + omega jd (jb - A v) (y distinct from v, A v zero
+// on fixed DOFs); the
 // node's own v, jb and jd are fetched one plane ahead like the moduli.
 // DOT: the workgroup also writes part[blockIdx.x], the sum over the nodes it
 // owns of d . y with d = jb (JAC) or d = v: the partials of CG's r^T z or
@@ -314,8 +315,8 @@ __global__ void __launch_bounds__(kLanes * ROWS, AARMR_EBE_MINB) k_ebe_z(int nx,
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       T out = X0[c] + xs[buf][c][ty > 0 ? ty - 1 : 0][tx];
-      if (JAC) out = own_v[c] + omega * own_d[c] * (own_b[c] - out);
       if ((own_m >> c) & 1u) out = MASK_IN ? own_v[c] : (T)0;
+      if (JAC) out = own_v[c] + omega * own_d[c] * (own_b[c] - out);
       st(ry, oy, out, (uint32_t)c * cstride);
       if (DOT) dacc += wr ? (double)(JAC ? own_b[c] : own_v[c]) * (double)out : 0.0;
     }
