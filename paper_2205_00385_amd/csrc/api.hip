@@ -102,7 +102,6 @@ constexpr int M_KR = 180;      // reduced matrix (up to 10x10, slots 180..279)
 constexpr int M_SVC = 300;     // SVD basis coefficients (up to 10x10, slots 300..399)
 constexpr int M_SVK = 400;     // SVD: number of kept singular vectors
 constexpr int M_N0 = 410;      // GS: squared column norms before the projections (Nm)
-constexpr int M_N1 = 420;      // GS: and after them (Nm)
 constexpr int M_KEEP = 430;    // GS: 1 for a kept column, 0 for a dropped one (Nm)
 
 constexpr int64_t kAlign = 256;
@@ -622,9 +621,9 @@ int need_ws(const aarmr_mesh* m) {
 
 RedScratch red(aarmr_mesh* m) { return RedScratch{m->partial}; }
 
-// Launch one multi-dot with up to kRedSlots products.
+// k dot products, kRedSlots a launch; the last one also solves `solve`.
 int dots(aarmr_mesh* m, int k, const double* const* a, const double* const* b, double* const* out,
-         int64_t n, hipStream_t s) {
+         int64_t n, hipStream_t s, const SmallSolve& solve = SmallSolve{}) {
   for (int base = 0; base < k; base += kRedSlots) {
     DotSet d{};
     d.k = std::min(kRedSlots, k - base);
@@ -634,7 +633,7 @@ int dots(aarmr_mesh* m, int k, const double* const* a, const double* const* b, d
       d.b[i] = b ? b[base + i] : nullptr;
       d.out[i] = out[base + i];
     }
-    launch_multidot(d, red(m), s);
+    launch_multidot(d, red(m), s, base + kRedSlots >= k ? solve : SmallSolve{});
     KCHECK();
   }
   return AARMR_OK;
@@ -2202,17 +2201,21 @@ int aarmr_ca_update(aarmr_mesh* m, const double* rho, const double* f, int32_t n
     KCHECK();
     launch_copy_masked(g, ul, m->mask, ul, s, m->dim);
     KCHECK();
-    // eq. (15): K_Phi = Phi^T K0 Phi, K0 = K(previous design)
-    for (int j = 0; j < Ns; ++j) {
-      TRY(fine_product(m, m->E_prev, PhiL + j * n3, m->t0, s));
-      std::vector<const double*> a(Ns), b(Ns);
-      std::vector<double*> o(Ns);
-      for (int i = 0; i < Ns; ++i) {
-        a[i] = PhiL + i * n3;
-        b[i] = m->t0;
-        o[i] = misc + M_KPHI + i * Ns + j;
+    // eq. (15): K_Phi = Phi^T K0 Phi, K0 = K(previous design); the products
+    // of t0 and the still unused KR columns share one reduction
+    for (int j0 = 0; j0 < Ns; j0 += Nm + 1) {
+      std::vector<const double*> a, b;
+      std::vector<double*> o;
+      for (int j = j0; j < std::min(Ns, j0 + Nm + 1); ++j) {
+        double* y = j == j0 ? m->t0 : m->KR + (j - j0 - 1) * n3;
+        TRY(fine_product(m, m->E_prev, PhiL + j * n3, y, s));
+        for (int i = 0; i < Ns; ++i) {
+          a.push_back(PhiL + i * n3);
+          b.push_back(y);
+          o.push_back(misc + M_KPHI + i * Ns + j);
+        }
       }
-      TRY(dots(m, Ns, a.data(), b.data(), o.data(), n3, s));
+      TRY(dots(m, (int)a.size(), a.data(), b.data(), o.data(), n3, s));
     }
     // eq. (20)/(26): r_1 = u_last, r_i = -Phi K_Phi^-1 Phi^T dK r_(i-1)
     HIP_TRY(hipMemcpyAsync(m->R, ul, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -2226,9 +2229,8 @@ int aarmr_ca_update(aarmr_mesh* m, const double* rho, const double* f, int32_t n
         b[j] = m->t0;
         o[j] = misc + M_G + j;
       }
-      TRY(dots(m, Ns, a.data(), b.data(), o.data(), n3, s));
-      launch_small_spd_solve(Ns, Ns, misc + M_KPHI, misc + M_G, misc + M_C2, m->flags, s);
-      KCHECK();
+      TRY(dots(m, Ns, a.data(), b.data(), o.data(), n3, s,
+               SmallSolve{Ns, Ns, misc + M_KPHI, misc + M_G, misc + M_C2, m->flags}));
       std::vector<const double*> V(Ns);
       for (int j = 0; j < Ns; ++j) V[j] = PhiL + j * n3;
       launch_lincomb(n3, Ns, V.data(), misc + M_C2, -1.0, nullptr, m->R + i * n3, s);
@@ -2249,24 +2251,38 @@ int aarmr_ca_update(aarmr_mesh* m, const double* rho, const double* f, int32_t n
       if (ca_ok) TRY(orth_svd(m, Nm, &kept_svd, s));
       for (int j = 0; j < kept_svd; ++j) slot.push_back(j);
     } else {
+      {
+        std::vector<const double*> a(Nm);
+        std::vector<double*> o(Nm);
+        for (int i = 0; i < Nm; ++i) {
+          a[i] = m->R + i * n3;
+          o[i] = misc + M_N0 + i;
+        }
+        TRY(dots(m, Nm, a.data(), a.data(), o.data(), n3, s));
+      }
+      // partials of a column's products with those before it, before the
+      // first and the second pass, and of its last squared norm
+      double* part[3] = {m->partial, m->partial + AARMR_MAX_BASIS * kRedBlocks,
+                         m->partial + 2 * AARMR_MAX_BASIS * kRedBlocks};
+      static_assert(2 * AARMR_MAX_BASIS + 1 <= kRedSlots, "slots of the three sets");
       for (int i = 0; i < Nm; ++i) {
         double* v = m->R + i * n3;
-        TRY(dot1(m, v, v, misc + M_N0 + i, n3, s));
-        for (int pass = 0; pass < 2 && i > 0; ++pass) {
-          std::vector<const double*> a(i), b(i);
-          std::vector<double*> o(i);
+        if (i > 0) {
+          DotSet d{};
+          const double* self = nullptr;
+          d.k = i;
+          d.n = n3;
           for (int j = 0; j < i; ++j) {
-            a[j] = m->R + j * n3;
-            b[j] = v;
-            o[j] = misc + M_H + j;
+            d.a[j] = m->R + j * n3;
+            d.b[j] = v;
           }
-          TRY(dots(m, i, a.data(), b.data(), o.data(), n3, s));
-          launch_lincomb(n3, i, a.data(), misc + M_H, -1.0, v, v, s);
-          KCHECK();
+          launch_multidot_partials(d, part[0], s);
+          launch_lincomb_dots(n3, i, d.a, nullptr, part[0], -1.0, v, v, i, d.a, part[1], s);
+          launch_lincomb_dots(n3, i, d.a, nullptr, part[1], -1.0, v, v, 1, &self, part[2], s);
         }
-        TRY(dot1(m, v, v, misc + M_N1 + i, n3, s));
-        launch_gs_keep(n3, v, misc + M_N0 + i, misc + M_N1 + i, m->p.gs_tau, v,
-                       misc + M_KEEP + i, s);
+        // the first column keeps its norm
+        launch_gs_keep(n3, v, misc + M_N0 + i, i == 0 ? misc + M_N0 : nullptr, part[2],
+                       m->p.gs_tau, v, misc + M_KEEP + i, s);
         KCHECK();
       }
       unsigned* hfl = reinterpret_cast<unsigned*>(m->hpin + 64);
@@ -2306,15 +2322,16 @@ int aarmr_ca_update(aarmr_mesh* m, const double* rho, const double* f, int32_t n
       a.push_back(m->fm);
       b.push_back(m->fm);
       o.push_back(misc + M_FF);
-      TRY(dots(m, (int)a.size(), a.data(), b.data(), o.data(), n3, s));
-      launch_small_spd_solve(kept, kept, misc + M_KR, misc + M_FR, misc + M_Y, m->flags, s);
-      KCHECK();
+      TRY(dots(m, (int)a.size(), a.data(), b.data(), o.data(), n3, s,
+               SmallSolve{kept, kept, misc + M_KR, misc + M_FR, misc + M_Y, m->flags}));
       launch_lincomb(n3, kept, Q.data(), misc + M_Y, 1.0, nullptr, ul, s);
       KCHECK();
       // eq. (29) from the stored K R~ columns: f - sum_j y_j K r~_j
-      launch_lincomb(n3, kept, KQ.data(), misc + M_Y, -1.0, m->fm, m->t0, s);
+      const double* self = nullptr;
+      launch_lincomb_dots(n3, kept, KQ.data(), misc + M_Y, nullptr, -1.0, m->fm, m->t0, 1, &self,
+                          m->partial, s);
+      launch_dot_finish(n3, m->partial, misc + M_EPS, s);
       KCHECK();
-      TRY(dot1(m, m->t0, m->t0, misc + M_EPS, n3, s));
       // one read-back: eps^2, f^T f and the flags (bit 4: K_R~ not positive definite)
       unsigned* hfl = reinterpret_cast<unsigned*>(m->hpin + 64);
       HIP_TRY(hipMemcpyAsync(hfl, m->flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));

@@ -41,6 +41,16 @@ struct RedScratch {
   double* partial;     // [kRedSlots][kRedBlocks]
 };
 
+// A small SPD system A x = b (n x n, row stride lda, entries averaged with
+// their transpose) that is solved when its entries are finished (n = 0: none);
+// not positive definite: bit 4 of *bad and x = 0.
+struct SmallSolve {
+  int n, lda;
+  const double *A, *b;
+  double* x;
+  unsigned* bad;
+};
+
 // k dot products a_i . b_i (b_i == nullptr: plain sum of a_i) of vectors of
 // element type T, accumulated and returned in FP64.
 // Load cases solved in lock step by one set of launches: case l's vectors
@@ -223,7 +233,11 @@ void launch_jacobi_update_f32(int64_t n3, const float* b, const float* t, const 
 void launch_gemv_f32(int n, const double* A, const float* x, float* y, hipStream_t s, int nr = 1);
 
 // ---- vector kernels and reductions ----------------------------------------
-void launch_multidot(const DotSet& d, const RedScratch& rs, hipStream_t s);
+void launch_multidot(const DotSet& d, const RedScratch& rs, hipStream_t s,
+                     const SmallSolve& S = SmallSolve{});
+// The partials alone, product k's in slot k; and the finish of slot 0.
+void launch_multidot_partials(const DotSet& d, double* partial, hipStream_t s);
+void launch_dot_finish(int64_t n, const double* partial, double* out, hipStream_t s);
 void launch_multidot_f32(const DotSetT<float>& d, const RedScratch& rs, hipStream_t s);
 // FP32 direction update after a separate r^T z; the scalars stay FP64 in
 // device memory and the update is formed in FP64 before rounding to FP32.
@@ -273,15 +287,18 @@ void launch_scale_by_inv_sqrt(int64_t n, const double* src, const double* nrm2, 
 // out = sum_j coef[j] * V_j (+ add) with coefficients read from device memory
 void launch_lincomb(int64_t n, int k, const double* const* V, const double* coef, double sign,
                     const double* add, double* out, hipStream_t s);
-// Cholesky solve of A x = b (n x n, row stride lda, entries averaged with
-// their transpose); not positive definite: bit 4 of *bad and x = 0.
-void launch_small_spd_solve(int n, int lda, const double* A, const double* b, double* x,
-                            unsigned* bad, hipStream_t s);
+// launch_lincomb whose coefficients are coef or, with coef null, the sums of
+// slots 0..k - 1 of `from`; partials of out . W_j (null: out . out) to slot j
+// of `partial`, j < nw.  out may be add.
+void launch_lincomb_dots(int64_t n, int k, const double* const* V, const double* coef,
+                         const double* from, double sign, const double* add, double* out, int nw,
+                         const double* const* W, double* partial, hipStream_t s);
 // Gram-Schmidt keep test on a projected column (n0, n1: squared norms before
-// and after the projections): dst = src / sqrt(n1) and *keep = 1 when
-// sqrt(n1) > tau sqrt(n0), else dst = 0 and *keep = 0.
-void launch_gs_keep(int64_t n, const double* src, const double* n0, const double* n1, double tau,
-                    double* dst, double* keep, hipStream_t s);
+// and after the projections, n1 null: the sum of the partials part): dst = src
+// / sqrt(n1) and *keep = 1 when sqrt(n1) > tau sqrt(n0), else dst = 0 and
+// *keep = 0.
+void launch_gs_keep(int64_t n, const double* src, const double* n0, const double* n1,
+                    const double* part, double tau, double* dst, double* keep, hipStream_t s);
 // Thin SVD of the small n x n matrix T (row-major): left singular vectors of
 // sigma > tau sigma_1, decreasing, column by column into coef[j * n + i];
 // their count (as a double) into *kept.

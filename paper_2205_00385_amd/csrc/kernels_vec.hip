@@ -55,9 +55,45 @@ __global__ void __launch_bounds__(256) k_multidot(DotSetT<T> d, double* __restri
   }
 }
 
-template <typename T>
+// Cholesky solve of the small SPD system A x = b (row-major, leading dimension
+// lda, entries averaged with their transpose) by one thread; one that is not
+// positive definite sets bit 4 of *bad and gives x = 0.
+__device__ inline void small_spd_solve(int n, int lda, const double* A, const double* b, double* x,
+                                       unsigned* bad) {
+  double L[2 * AARMR_MAX_BASIS][2 * AARMR_MAX_BASIS];
+  double y[2 * AARMR_MAX_BASIS];
+  for (int i = 0; i < n; ++i) {
+    for (int j = 0; j <= i; ++j) {
+      double s = 0.5 * (A[i * lda + j] + A[j * lda + i]);
+      for (int k = 0; k < j; ++k) s -= L[i][k] * L[j][k];
+      if (i == j) {
+        if (!(s > 0.0)) {
+          atomicOr(bad, 4u);
+          for (int t = 0; t < n; ++t) x[t] = 0.0;
+          return;
+        }
+        L[i][i] = sqrt(s);
+      } else {
+        L[i][j] = s / L[j][j];
+      }
+    }
+  }
+  for (int i = 0; i < n; ++i) {
+    double s = b[i];
+    for (int k = 0; k < i; ++k) s -= L[i][k] * y[k];
+    y[i] = s / L[i][i];
+  }
+  for (int i = n - 1; i >= 0; --i) {
+    double s = y[i];
+    for (int k = i + 1; k < n; ++k) s -= L[k][i] * x[k];
+    x[i] = s / L[i][i];
+  }
+}
+
+template <typename T, bool SOLVE>
 __global__ void __launch_bounds__(256) k_multidot_finish(DotSetT<T> d, int nb,
-                                                         const double* __restrict__ partial) {
+                                                         const double* __restrict__ partial,
+                                                         SmallSolve S) {
   __shared__ double sh[4];
   for (int k = 0; k < d.k; ++k) {
     double s = 0.0;
@@ -65,6 +101,8 @@ __global__ void __launch_bounds__(256) k_multidot_finish(DotSetT<T> d, int nb,
     s = block_sum(s, sh);
     if (threadIdx.x == 0) *d.out[k] = s;
   }
+  // thread 0 wrote the sums itself
+  if (SOLVE && threadIdx.x == 0) small_spd_solve(S.n, S.lda, S.A, S.b, S.x, S.bad);
 }
 
 // The finished sum of nb block partials, in the order of k_multidot_finish
@@ -425,53 +463,80 @@ __global__ void k_lincomb(int64_t n, int k, VecList V, const double* __restrict_
   out[i] = add ? fma(sign, s, add[i]) : sign * s;
 }
 
-// Solve A x = b for a small SPD matrix (row-major, leading dimension lda) by
-// Cholesky in one thread; flags a non-positive pivot.
-// Cholesky solve of the small SPD system A x = b (entries averaged with
-// their transpose); one that is not positive definite sets bit 4 of *bad
-// and gives x = 0.  One thread.
-__global__ void k_small_spd_solve(int n, int lda, const double* __restrict__ A,
-                                  const double* __restrict__ b, double* __restrict__ x,
-                                  unsigned* bad) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double L[2 * AARMR_MAX_BASIS][2 * AARMR_MAX_BASIS];
-  double y[2 * AARMR_MAX_BASIS];
-  for (int i = 0; i < n; ++i) {
-    for (int j = 0; j <= i; ++j) {
-      double s = 0.5 * (A[i * lda + j] + A[j * lda + i]);
-      for (int k = 0; k < j; ++k) s -= L[i][k] * L[j][k];
-      if (i == j) {
-        if (!(s > 0.0)) {
-          atomicOr(bad, 4u);
-          for (int t = 0; t < n; ++t) x[t] = 0.0;
-          return;
-        }
-        L[i][i] = sqrt(s);
-      } else {
-        L[i][j] = s / L[j][j];
-      }
+// k_lincomb with the dot products of its result folded in: for j < nw block
+// partials of out . W_j (W_j null: out . out) go to slot j of `partial`, in
+// k_multidot's pattern.  coef null: the coefficients are finished here from
+// slots 0..k - 1 of `from`, one wavefront per coefficient.  A Gram-Schmidt
+// pass is then one launch where the combination, the next products and their
+// finish were three of 2.6 to 4.2 us (72x24x48).
+struct CombineDots {
+  const double* W[AARMR_MAX_BASIS];
+  const double* from;
+  double* partial;
+  int nw, nb;
+};
+__global__ void __launch_bounds__(256) k_lincomb_dots(int64_t n, int k, VecList V,
+                                                      const double* __restrict__ coef, double sign,
+                                                      const double* add, double* out,
+                                                      CombineDots D) {
+  __shared__ double sh[4], c[2 * AARMR_MAX_BASIS];
+  const int lane = threadIdx.x & 63;
+  for (int j = threadIdx.x >> 6; j < k; j += 4) {
+    double s = 0.0;
+    if (coef) {
+      s = coef[j];
+    } else {
+      for (int b = lane; b < D.nb; b += 64) s += D.from[j * kRedBlocks + b];
+      s = wave_sum(s);
     }
+    if (lane == 0) c[j] = s;
   }
-  for (int i = 0; i < n; ++i) {
-    double s = b[i];
-    for (int k = 0; k < i; ++k) s -= L[i][k] * y[k];
-    y[i] = s / L[i][i];
+  __syncthreads();
+  double acc[AARMR_MAX_BASIS] = {};
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  // four entries at a time, their loads together
+  for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += 4 * stride) {
+    int64_t i[4];
+    double s[4] = {}, o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      i[q] = min(i0 + q * stride, n - 1);
+      o[q] = add ? add[i[q]] : 0.0;
+    }
+    for (int j = 0; j < k; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] = fma(c[j], V.v[j][i[q]], s[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      o[q] = i0 + q * stride < n ? fma(sign, s[q], o[q]) : 0.0;  // 0: past the end
+      if (i0 + q * stride < n) out[i[q]] = o[q];
+    }
+#pragma unroll
+    for (int j = 0; j < AARMR_MAX_BASIS; ++j)
+      if (j < D.nw)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[j] = fma(D.W[j] ? D.W[j][i[q]] : o[q], o[q], acc[j]);
   }
-  for (int i = n - 1; i >= 0; --i) {
-    double s = y[i];
-    for (int k = i + 1; k < n; ++k) s -= L[k][i] * x[k];
-    x[i] = s / L[i][i];
-  }
+#pragma unroll
+  for (int j = 0; j < AARMR_MAX_BASIS; ++j)
+    if (j < D.nw) {
+      const double t = block_sum(acc[j], sh);
+      if (threadIdx.x == 0) D.partial[j * kRedBlocks + blockIdx.x] = t;
+    }
 }
 
 // Gram-Schmidt keep test: with n0 = ||v||^2 before and n1 after the
-// projections, a column with sqrt(n1) > tau sqrt(n0) is scaled to unit norm
+// projections (n1 null: finished here from nb partials), a column with sqrt(n1) > tau sqrt(n0) is scaled to unit norm
 // (dst = src / sqrt(n1)) and *keep = 1; any other becomes zero, *keep = 0.
-__global__ void k_gs_keep(int64_t n, const double* __restrict__ src,
-                          const double* __restrict__ n0, const double* __restrict__ n1,
-                          double tau, double* __restrict__ dst, double* __restrict__ keep) {
+__global__ void __launch_bounds__(256) k_gs_keep(int64_t n, const double* src,
+                                                 const double* __restrict__ n0,
+                                                 const double* __restrict__ n1,
+                                                 const double* __restrict__ part, int nb,
+                                                 double tau, double* dst,
+                                                 double* __restrict__ keep) {
+  __shared__ double sh[5];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const double a = *n0, b = *n1;
+  const double a = *n0, b = n1 ? *n1 : finish_partials(part, nb, sh);
   const bool k = sqrt(b) > tau * sqrt(a);
   const double sc = 1.0 / sqrt(b);
   if (i < n) dst[i] = k ? src[i] * sc : 0.0;  // exact zeros, also for a non-finite column
@@ -481,15 +546,30 @@ __global__ void k_gs_keep(int64_t n, const double* __restrict__ src,
 }  // namespace
 
 template <typename T>
-void multidot_t(const DotSetT<T>& d, const RedScratch& rs, hipStream_t s) {
+void multidot_t(const DotSetT<T>& d, const RedScratch& rs, hipStream_t s, const SmallSolve& S) {
   int64_t want = (d.n + 255) / 256;
   int nb = (int)(want < kRedBlocks ? (want < 1 ? 1 : want) : kRedBlocks);
   k_multidot<T><<<nb, 256, 0, s>>>(d, rs.partial);
-  k_multidot_finish<T><<<1, 256, 0, s>>>(d, nb, rs.partial);
+  if (S.n > 0)
+    k_multidot_finish<T, true><<<1, 256, 0, s>>>(d, nb, rs.partial, S);
+  else
+    k_multidot_finish<T, false><<<1, 256, 0, s>>>(d, nb, rs.partial, S);
 }
 
-void launch_multidot(const DotSet& d, const RedScratch& rs, hipStream_t s) {
-  multidot_t<double>(d, rs, s);
+void launch_multidot(const DotSet& d, const RedScratch& rs, hipStream_t s, const SmallSolve& S) {
+  multidot_t<double>(d, rs, s, S);
+}
+
+void launch_multidot_partials(const DotSet& d, double* partial, hipStream_t s) {
+  k_multidot<double><<<dot_blocks(d.n), 256, 0, s>>>(d, partial);
+}
+
+void launch_dot_finish(int64_t n, const double* partial, double* out, hipStream_t s) {
+  DotSet d{};
+  d.k = 1;
+  d.n = n;
+  d.out[0] = out;
+  k_multidot_finish<double, false><<<1, 256, 0, s>>>(d, dot_blocks(n), partial, SmallSolve{});
 }
 
 int dot_blocks(int64_t n) {
@@ -527,7 +607,7 @@ void launch_cg_p_fused(int64_t n, const double* rz_part, int n_part, double* rz_
 }
 
 void launch_multidot_f32(const DotSetT<float>& d, const RedScratch& rs, hipStream_t s) {
-  multidot_t<float>(d, rs, s);
+  multidot_t<float>(d, rs, s, SmallSolve{});
 }
 
 void launch_cg_xr_fused_f32(int64_t n, const double* rz, const double* pq_part, int n_part,
@@ -592,14 +672,23 @@ void launch_small_svd(int n, const double* T, double tau, double* coef, double* 
   k_small_svd<<<1, 64, 0, s>>>(n, T, tau, coef, kept);
 }
 
-void launch_small_spd_solve(int n, int lda, const double* A, const double* b, double* x,
-                            unsigned* bad, hipStream_t s) {
-  k_small_spd_solve<<<1, 64, 0, s>>>(n, lda, A, b, x, bad);
+void launch_lincomb_dots(int64_t n, int k, const double* const* V, const double* coef,
+                         const double* from, double sign, const double* add, double* out, int nw,
+                         const double* const* W, double* partial, hipStream_t s) {
+  VecList L;
+  for (int j = 0; j < 2 * AARMR_MAX_BASIS; ++j) L.v[j] = j < k ? V[j] : nullptr;
+  CombineDots D;
+  for (int j = 0; j < AARMR_MAX_BASIS; ++j) D.W[j] = j < nw ? W[j] : nullptr;
+  D.from = from;
+  D.partial = partial;
+  D.nw = nw;
+  D.nb = dot_blocks(n);
+  k_lincomb_dots<<<D.nb, 256, 0, s>>>(n, k, L, coef, sign, add, out, D);
 }
 
-void launch_gs_keep(int64_t n, const double* src, const double* n0, const double* n1, double tau,
-                    double* dst, double* keep, hipStream_t s) {
-  k_gs_keep<<<nblk(n, 256), 256, 0, s>>>(n, src, n0, n1, tau, dst, keep);
+void launch_gs_keep(int64_t n, const double* src, const double* n0, const double* n1,
+                    const double* part, double tau, double* dst, double* keep, hipStream_t s) {
+  k_gs_keep<<<nblk(n, 256), 256, 0, s>>>(n, src, n0, n1, part, dot_blocks(n), tau, dst, keep);
 }
 
 }  // namespace aarmr
