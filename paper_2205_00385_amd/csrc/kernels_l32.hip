@@ -237,54 +237,61 @@ __device__ __forceinline__ void l1_elem(int nx, int ny, int nz,
 }
 
 // Level-1 element products of the flagged parents from their stored Galerkin
-// matrices (elist[0..cnt), of which only the flagged ones are written).  Row r
-// is uniform per wavefront; its lanes take 16 list entries w (from chunk * 16
-// in steps of nchunk * 16), four lanes per entry, each lane two corners (six
-// columns q = 3b + c), so that all of a lane's loads are in flight at once; the
-// four sums are then added in a fixed order.
+// matrices (elist[0..cnt), of which only the flagged ones are written): rows
+// r0..r0 + 2.  r0 is uniform per wavefront; its lanes take 16 list entries w
+// (from chunk * 16 in steps of nchunk * 16), four lanes per entry, each lane two
+// corners (six columns q = 3b + c); the four sums are then added in a fixed
+// order.  The matrix entries need only w, so the chain is the element's number
+// and then everything else at once, the flag included.  Three rows a wavefront
+// and not one, with a third of the workgroups, and the flag no longer ahead of
+// the operands: 56x40x64's level 1 with 4 cases 11.9 -> 10.7 us for the launch.
 __device__ __forceinline__ void l1_masked_rows(int nx, int ny, int nz,
                                                const double* __restrict__ Kst,
                                                const uint8_t* __restrict__ eflag,
                                                const int* __restrict__ list, int cnt,
                                                const T* __restrict__ v, T* __restrict__ Y,
-                                               int chunk, int nchunk, int r) {
+                                               int chunk, int nchunk, int r0) {
   const int nn = (nx + 1) * (ny + 1) * (nz + 1);
   const int64_t ne = (int64_t)nx * ny * nz;
   const int lane = threadIdx.x & 63, quarter = lane >> 4;
   // the loop bound is uniform per wavefront, so every lane reaches the shuffles
   for (int base = chunk * 16; base < cnt; base += nchunk * 16) {
-    const int w = base + (lane & 15);
-    T acc = 0;
-    int e = 0;
-    bool live = w < cnt;
-    if (live) {
-      e = list[w];
-      live = eflag[e] != 0;
-    }
-    if (live) {
-      const int ex = e % nx, rest = e / nx, ey = rest % ny, ez = rest / ny;
+    const int w = base + (lane & 15), wc = min(w, cnt - 1);
+    const int e = list[wc];
+    double K[3][6];
+    T x[6];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int b = 2 * quarter + h;
-        const int nb = ex + (b & 1) + (nx + 1) * (ey + ((b >> 1) & 1) + (ny + 1) * (ez + (b >> 2)));
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const int q = 3 * b + c;
-          const double k = Kst[(int64_t)sidx(r, q) * ne + w];
-          acc = fma((T)k, v[c * nn + nb], acc);
-        }
-      }
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          K[t][3 * h + c] = Kst[(int64_t)sidx(r0 + t, 3 * (2 * quarter + h) + c) * ne + wc];
+    const bool live = eflag[e] != 0 && w < cnt;
+    const int ex = e % nx, rest = e / nx, ey = rest % ny, ez = rest / ny;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int b = 2 * quarter + h;
+      const int nb = ex + (b & 1) + (nx + 1) * (ey + ((b >> 1) & 1) + (ny + 1) * (ez + (b >> 2)));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) x[3 * h + c] = v[c * nn + nb];
     }
-    acc += __shfl_down(acc, 32, 64);  // corners 0-3 + 4-7
-    acc += __shfl_down(acc, 16, 64);
-    if (quarter == 0 && live) Y[(int64_t)r * ne + e] = acc;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      T acc = 0;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) acc = fma((T)K[t][q], x[q], acc);
+      acc += __shfl_down(acc, 32, 64);  // corners 0-3 + 4-7
+      acc += __shfl_down(acc, 16, 64);
+      if (quarter == 0 && live) Y[(int64_t)(r0 + t) * ne + e] = acc;
+    }
   }
 }
 
 // Pass 1 in one launch: workgroups x < nbe run the element path (grid.y:
-// output component, or with all3 a third of the elements each); the rest
-// run the flagged parents, two per grid.y, each with four rows (one per
-// wavefront) of a 16-entry chunk of the list.
+// output component, or with all3 a third of the elements each); the rest,
+// counted over grid.y, run the flagged parents: two workgroups per 16-entry
+// chunk of the list, twelve rows each.  (Those first: 11.2 against 10.7 us.)
 __global__ void __launch_bounds__(256) k_l1_elem(int nx, int ny, int nz,
                                                  const double* __restrict__ Kst,
                                                  const T* __restrict__ Bw,
@@ -296,10 +303,10 @@ __global__ void __launch_bounds__(256) k_l1_elem(int nx, int ny, int nz,
   v += (int64_t)blockIdx.z * rs;  // load case blockIdx.z
   Y += (int64_t)blockIdx.z * Ys;
   if ((int)blockIdx.x >= nbe) {  // workgroup-uniform
-    const int mb = (int)blockIdx.x - nbe;
-    const int r = (int)(blockIdx.y * 2 + (mb & 1)) * 4 + (int)(threadIdx.x >> 6);
-    l1_masked_rows(nx, ny, nz, Kst, eflag, list, cnt, v, Y, mb >> 1,
-                      ((int)gridDim.x - nbe) >> 1, r);
+    const int per = (int)gridDim.x - nbe, mb = (int)blockIdx.x - nbe + per * (int)blockIdx.y;
+    if (mb >= 3 * per / 2 * 2) return;  // an odd one out has no partner
+    l1_masked_rows(nx, ny, nz, Kst, eflag, list, cnt, v, Y, mb >> 1, 3 * per >> 1,
+                   12 * (mb & 1) + 3 * __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
     return;
   }
   if (all3) {
@@ -316,7 +323,10 @@ __global__ void __launch_bounds__(256) k_l1_elem(int nx, int ny, int nz,
 // Pass 2: y[c][n] = sum over the (up to 8) elements around node n, taken in
 // corner order a = 0..7, of Y[3a + c][e(n, a)].
 // mode 1: y = v + omega jd (jb - A v), the damped-Jacobi sweep; mode 2: y =
-// jb - A v, the residual.
+// jb - A v, the residual.  All 24 entries and the epilogue's operands are
+// loaded at once, at clamped elements whose terms a select leaves out (with a
+// branch per corner 6.4 us on 56x40x64's level 1 with 4 cases and 16.8 us on
+// 256x128x128's, 4.1 and 13.8 us so).
 __global__ void __launch_bounds__(256) k_l1_gather(int nx, int ny, int nz, int mode,
                                                    const T* __restrict__ Y,
                                                    const T* __restrict__ v, T* __restrict__ y,
@@ -331,23 +341,39 @@ __global__ void __launch_bounds__(256) k_l1_gather(int nx, int ny, int nz, int m
   y += (int64_t)blockIdx.z * rs;
   if (mode) jb += (int64_t)blockIdx.z * rs;
   if (n >= nn) return;
+  T vn[3] = {}, bn[3] = {}, dn[3] = {};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int64_t d = (int64_t)c * nn + n;
+    if (mode) bn[c] = jb[d];
+    if (mode == 1) {
+      vn[c] = v[d];
+      dn[c] = jd[d];
+    }
+  }
   const int i = n % (nx + 1), rest = n / (nx + 1), j = rest % (ny + 1), k = rest / (ny + 1);
+  T t[8][3];
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    const int ex = min(max(i - (a & 1), 0), nx - 1), ey = min(max(j - ((a >> 1) & 1), 0), ny - 1);
+    const int ez = min(max(k - (a >> 2), 0), nz - 1), e = ex + nx * (ey + ny * ez);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) t[a][c] = Y[(int64_t)(3 * a + c) * ne + e];
+  }
   T acc[3] = {0, 0, 0};
 #pragma unroll
   for (int a = 0; a < 8; ++a) {
     const int ex = i - (a & 1), ey = j - ((a >> 1) & 1), ez = k - (a >> 2);
-    if (ex < 0 || ex >= nx || ey < 0 || ey >= ny || ez < 0 || ez >= nz) continue;
-    const int e = ex + nx * (ey + ny * ez);
+    const bool in = ex >= 0 && ex < nx && ey >= 0 && ey < ny && ez >= 0 && ez < nz;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) acc[c] += Y[(int64_t)(3 * a + c) * ne + e];
+    for (int c = 0; c < 3; ++c) acc[c] = in ? acc[c] + t[a][c] : acc[c];
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const int64_t d = (int64_t)c * nn + n;
-    y[d] = mode == 0 ? acc[c] : mode == 1 ? v[d] + omega * jd[d] * (jb[d] - acc[c]) : jb[d] - acc[c];
-  }
+  for (int c = 0; c < 3; ++c)
+    y[(int64_t)c * nn + n] = mode == 0 ? acc[c]
+                             : mode == 1 ? vn[c] + omega * dn[c] * (bn[c] - acc[c])
+                                         : bn[c] - acc[c];
 }
-
 
 constexpr int64_t kL1All3 = 200000;
 
@@ -376,7 +402,7 @@ void launch_apply_l1_f32(const Grid& g, const double* Kst, const float* Bw, cons
   const int all3 = g.ne >= kL1All3 ? 1 : 0;
   const int nbe = (int)nblk(g.ne, all3 ? 3 * 256 : 256);
   const int chunks = (int)nblk(nlist, 16);
-  const int nbm = nlist > 0 ? 2 * (chunks < 1024 ? chunks : 1024) : 0;
+  const int nbm = nlist > 0 ? (2 * (chunks < 1024 ? chunks : 1024) + 2) / 3 : 0;  // per grid.y
   const int64_t rs = 3 * g.nn, Ys = 24 * g.ne;
   k_l1_elem<<<dim3(nbe + nbm, 3, nr), 256, 0, s>>>(g.nx, g.ny, g.nz, Kst, Bw, Ef, eflag, v, Y, nbe,
                                                    list, nlist, all3, rs, Ys);
