@@ -32,12 +32,23 @@ __device__ inline double phi1(int pos, int A) {
   return pos == 1 ? 0.5 : ((pos >> 1) == A ? 1.0 : 0.0);
 }
 
-__device__ inline bool flagged_near(const uint8_t* f, int nx, int ny, int nz, int x0, int x1, int y0,
-                                    int y1, int z0, int z1) {
+// Whether one of the elements x - 1 .. x + N - 2 (and so in y and z) is flagged.
+// Outside the grid the index is clamped to an element of the set, which leaves
+// the answer, so all N^3 loads are independent (in a loop over the elements
+// inside the grid each waited for the one before: 14 us a list pass on 96x48x48,
+// 7.3 to 8.2 us so).
+template <int N>
+__device__ __forceinline__ bool flagged_near(const uint8_t* f, int nx, int ny, int nz, int x, int y,
+                                             int z) {
   unsigned any = 0;
-  for (int z = max(z0, 0); z <= min(z1, nz - 1); ++z)
-    for (int y = max(y0, 0); y <= min(y1, ny - 1); ++y)
-      for (int x = max(x0, 0); x <= min(x1, nx - 1); ++x) any |= f[x + nx * (y + ny * z)];
+#pragma unroll
+  for (int dz = -1; dz < N - 1; ++dz)
+#pragma unroll
+    for (int dy = -1; dy < N - 1; ++dy)
+#pragma unroll
+      for (int dx = -1; dx < N - 1; ++dx)
+        any |= f[min(max(x + dx, 0), nx - 1) +
+                 nx * (min(max(y + dy, 0), ny - 1) + ny * min(max(z + dz, 0), nz - 1))];
   return any != 0;
 }
 
@@ -107,12 +118,12 @@ __global__ void __launch_bounds__(256) k_lists(LevelTable T) {
   const int i0 = (blk - first) * kChunk + 4 * (int)threadIdx.x;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int i = i0 + q;
-    if (i >= n) break;
+    const int i = min(i0 + q, n - 1);
     const int wx = nodes ? nx + 1 : nx, wy = nodes ? ny + 1 : ny;
     const int x = i % wx, r = i / wx, y = r % wy, z = r / wy;
-    const int hi = nodes ? 0 : 1;
-    if (all || flagged_near(f, nx, ny, nz, x - 1, x + hi, y - 1, y + hi, z - 1, z + hi)) hit |= 1u << q;
+    const bool near = all || (nodes ? flagged_near<2>(f, nx, ny, nz, x, y, z)
+                                    : flagged_near<3>(f, nx, ny, nz, x, y, z));
+    if (near && i0 + q < n) hit |= 1u << q;
   }
   int cnt = __popc(hit);
   sh[threadIdx.x] = cnt;
