@@ -11,7 +11,7 @@
 // transforms per component plus ~40 multiply-adds instead of 576.
 //
 // Data flow.  A workgroup of 32 x ROWS threads (two 32-lane x-rows per
-// wavefront; ROWS = 16 unless a tuned shape says otherwise) owns
+// wavefront; ROWS by ebe_shape or a tuned shape) owns
 // 30 x (ROWS - 1) node columns; thread (tx, ty) handles the element column
 // (i, j) = (30 bx - 1 + tx, (ROWS - 1) by - 1 + ty) (the last lane of a row
 // only supplies node values) and marches along z over a chunk of node
