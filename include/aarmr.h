@@ -278,7 +278,10 @@ int aarmr_filter(aarmr_mesh* m, int32_t mode, const double* in, double* out, voi
  * SIMP moduli from rho~ (device [n_elem]), the fixed-DOF mask, and the
  * multigrid hierarchy (Jacobi diagonals, Galerkin coarse operators
  * P^T A P per level, inverse of the coarsest operator).  Stream-ordered;
- * rho~ is range-checked on the next synchronising call. */
+ * rho~ is range-checked on the next synchronising call.  It may be captured
+ * into a graph (after an eager call): replays read the buffers' contents of
+ * then, the fixed DOFs among them, and later calls of aarmr_apply_operator and
+ * aarmr_vcycle use the hierarchy of the last replay or call. */
 int aarmr_setup(aarmr_mesh* m, const double* rho_phys, const int64_t* fixed_dofs,
                 int64_t n_fixed, void* stream);
 

@@ -135,6 +135,8 @@ struct aarmr_mesh {
   int nspecial[AARMR_MAX_LEVELS] = {};  // special nodes per level of the current hierarchy
   int nstored1 = 0;                     // stored elements of level 1
   bool counts_ready = false;            // read back since the last hierarchy build
+  bool setup_captured = false;          // a graph that holds a hierarchy build may be replayed
+  bool device_counts = false;           // the products take the counts on the device
   float* E32 = nullptr;       // FP32 moduli (refinement form)
   float *r32 = nullptr, *z32 = nullptr, *p32 = nullptr, *q32 = nullptr, *d32 = nullptr;
   double* E = nullptr;
@@ -742,18 +744,23 @@ int level_counts(aarmr_mesh* m, hipStream_t s) {
   return AARMR_OK;
 }
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  return cap == hipStreamCaptureStatusActive;
+}
+
 // What the product of coarse level l reads (3D).  Under stream capture the
 // launch is sized for every node and takes the count of special nodes from the
 // device: the host can't wait for it there, and a replay after another setup
-// has to follow that setup's fixed DOFs.
+// has to follow that setup's fixed DOFs.  So do a caller's products once a
+// setup was captured: a replay changes the device's lists unseen by the host.
 int level_args(aarmr_mesh* m, int l, hipStream_t s, LevelArgs* out) {
   const LevelTable& T = m->lt;
   const int* count = nullptr;
   int n = T.nn[l];  // the coarsest level is special as a whole
   if (l < m->nlev - 1) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap == hipStreamCaptureStatusActive) {
+    if (m->device_counts || capturing(s)) {
       count = T.counts + 2 * l + 1;
     } else {
       TRY(level_counts(m, s));
@@ -1003,6 +1010,8 @@ int build_mg(aarmr_mesh* m, hipStream_t s) {
   HIP_TRY(hipMemcpyAsync(m->hpin + 72, m->lt.counts, 2 * m->nlev * sizeof(int),
                          hipMemcpyDeviceToHost, s));
   m->counts_ready = false;
+  m->device_counts = false;  // a solve's products read the counts of its own build
+  if (capturing(s)) m->setup_captured = true;
   for (int l = 1; l < m->nlev; ++l) {
     if (l >= 2 && l < m->nlev - 1) launch_level_moments(m->lg[l], l, m->E, m->lt.mom[l - 1], m->lt.mom[l], s);
     launch_level_store(m->lt, l, m->wk, m->E, m->mask, s);
@@ -1999,6 +2008,7 @@ int aarmr_apply_operator(aarmr_mesh* m, int32_t level, const double* v, double* 
   if (!v || !y || v == y) return fail(AARMR_E_INVALID, "v, y must be distinct non-null");
   if (level < 0 || level >= m->nlev) return fail(AARMR_E_INVALID, "level out of range");
   if (level > 0 && !m->mg_ready) return fail(AARMR_E_STATE, "no hierarchy: call aarmr_setup");
+  m->device_counts = m->setup_captured;
   return apply(m, level, v, y, S(stream), !(flags & AARMR_INPUT_MASKED));
 }
 
@@ -2006,6 +2016,7 @@ int aarmr_vcycle(aarmr_mesh* m, const double* r, double* z, void* stream) {
   TRY(need_ws(m));
   if (!r || !z || r == z) return fail(AARMR_E_INVALID, "r, z must be distinct non-null");
   if (!m->mg_ready) return fail(AARMR_E_STATE, "no hierarchy: call aarmr_setup");
+  m->device_counts = m->setup_captured;
   return vcycle(m, 0, r, m->z, S(stream), false, z);
 }
 
