@@ -26,6 +26,7 @@
 // written once by its owner, so results are deterministic.
 #include <algorithm>
 
+#include "chunks.hpp"
 #include "internal.hpp"
 #include "walsh.hpp"
 
@@ -464,9 +465,7 @@ static EbeShape ebe_shape(const Grid& g, int shape, bool f32) {
     for (const Cost& c : kCost[f32]) {
       if (rows_req ? c.rows != best.rows : c.rows == 12) continue;
       const int64_t tiles = (int64_t)((g.nx + kTileX) / kTileX) * ((g.ny + c.rows - 1) / (c.rows - 1));
-      for (int n = 1; n <= planes; ++n) {
-        const int t = (planes + n - 1) / n;
-        if (t < (f32 ? 4 : 2)) break;
+      for_chunk_lengths(planes, f32 ? 4 : 2, [&](int t) {
         const int64_t k = (tiles * ((planes + t - 1) / t) + cus - 1) / cus;
         // a step of one small workgroup is bound by its own chain
         const double step = std::max(f32 && c.rows == 8 ? 0.62 : 0.0, c.step0 + c.step * k);
@@ -475,7 +474,7 @@ static EbeShape ebe_shape(const Grid& g, int shape, bool f32) {
           least = cost;
           best = {c.rows, t};
         }
-      }
+      });
     }
   }
   best.tz = std::max(best.tz, 2);

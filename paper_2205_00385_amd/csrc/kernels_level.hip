@@ -16,6 +16,7 @@
 // 14.8 -> 7.5, level 2 9.9 -> 7.5; 24x12x12 level 1 10 -> 6 us.
 #include <type_traits>
 
+#include "chunks.hpp"
 #include "internal.hpp"
 #include "moment.hpp"
 
@@ -819,15 +820,14 @@ void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, con
   const int64_t tiles = (int64_t)gx * gy;
   int tz = planes;
   int64_t best = -1;
-  for (int n = 1; n <= planes; ++n) {
-    const int t = (planes + n - 1) / n;
+  for_chunk_lengths(planes, 1, [&](int t) {
     const int64_t chunks = (planes + t - 1) / t;
     const int64_t cost = (tiles * chunks + slots - 1) / slots * (t + 1);
     if (best < 0 || cost < best) {
       best = cost;
       tz = t;
     }
-  }
+  });
   // the coarsest level is special as a whole and has no moments: nothing to march
   const bool whole = !L.count && L.nspecial == (L.nx + 1) * (L.ny + 1) * (L.nz + 1);
   const int nmarch = whole ? 0 : gx * gy * ((planes + tz - 1) / tz);

@@ -4,6 +4,7 @@
 // (kernels_inv.hip).
 #include <algorithm>
 
+#include "chunks.hpp"
 #include "internal.hpp"
 
 namespace aarmr {
@@ -480,15 +481,14 @@ static void restrict_z(const Grid& coarse, const T* bf, const T* tf, const uint8
   const int planes = coarse.nz + 1, tiles = gx * gy;
   int tk = planes;
   int64_t best = -1;
-  for (int n = 1; n <= planes; ++n) {
-    const int t = (planes + n - 1) / n;
+  for_chunk_lengths(planes, 1, [&](int t) {
     const int64_t chunks = (planes + t - 1) / t;
     const int64_t cost = ((int64_t)tiles * chunks + slots - 1) / slots * (2 * t + 1);
     if (best < 0 || cost < best) {
       best = cost;
       tk = t;
     }
-  }
+  });
   const int gz = (planes + tk - 1) / tk;
   k_restrict_zm<T><<<dim3((unsigned)(tiles * gz), 1, (unsigned)nr), 64 * kRmWaves, 0, s>>>(
       coarse.nx, coarse.ny, coarse.nz, gx, gy, tk, bf, tf, mask, bc, dc, omega, xc, fs, cs);
