@@ -568,6 +568,12 @@ constexpr int kLanes = 32;
 // to 12 against 8.
 constexpr int kRows = 8;
 
+// Slot of workgroup w of `total` in XCD-contiguous order (see kernels_mg.hip).
+__device__ __forceinline__ int xcd_slot(int w, int total) {
+  const int xcd = w & 7, pos = w >> 3, q = total >> 3, r = total & 7;
+  return (xcd < r) ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
+}
+
 // Special nodes from the stored matrices, eight threads per node: thread
 // (corner a, node) takes the node as corner a of its element and forms the
 // node's three rows; the eight partial rows are summed in LDS in a fixed order.
@@ -582,8 +588,10 @@ __device__ __forceinline__ void special_nodes(const LevelArgs& L, const double* 
   const int lane = threadIdx.x % NODES, a = threadIdx.x / NODES;
   const int nx = L.nx, ny = L.ny, nz = L.nz, nxp = nx + 1, nyp = ny + 1, nn = nxp * nyp * (nz + 1);
   const int64_t ne = (int64_t)nx * ny * nz;
-  const int idx = blk * NODES + lane;
-  const bool live = idx < (L.count ? *L.count : L.nspecial);
+  const int total = L.count ? *L.count : L.nspecial, nb = (total + NODES - 1) / NODES;
+  if (blk >= nb) return;  // workgroup-uniform
+  const int idx = xcd_slot(blk, nb) * NODES + lane;
+  const bool live = idx < total;
   const int n = live ? L.nlist[idx] : 0;
   const int64_t w = live ? L.corner[(int64_t)a * nn + idx] : -1;
   double acc[3] = {0.0, 0.0, 0.0};
@@ -642,8 +650,7 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
   const int tx = threadIdx.x & (kLanes - 1), ty = threadIdx.x / kLanes;
   int bx, by, bz;
   {  // XCD-contiguous tile order
-    const int w = (int)blockIdx.x - nsp, xcd = w & 7, pos = w >> 3, q = nmarch >> 3, r = nmarch & 7;
-    const int t = (xcd < r) ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
+    const int t = xcd_slot((int)blockIdx.x - nsp, nmarch);
     bx = t % gx;
     by = (t / gx) % gy;
     bz = t / (gx * gy);
