@@ -74,7 +74,39 @@ __global__ void __launch_bounds__(256) k_flags1(int nx, int ny, int nz,
 }
 
 // Levels >= 2 in one launch, one wavefront per element: flagged if one of its
-// level-1 descendants is.
+// level-1 descendants is.  A row of descendants along x is n = 2^(l - 1) bytes
+// at an offset that is a multiple of n, so rows are read in words of up to 16
+// bytes, eight a lane in flight (byte by byte the few elements of the deepest
+// levels set the launch's time: setup of 128x128x128 in eight levels 807 -> 368 us).
+template <typename W>
+__device__ __forceinline__ bool any_in(const W& w) {
+  if constexpr (sizeof(W) == 16)
+    return (w.x | w.y | w.z | w.w) != 0;
+  else if constexpr (sizeof(W) == 8)
+    return (w.x | w.y) != 0;
+  else
+    return w != 0;
+}
+template <typename W>
+__device__ __forceinline__ bool flagged_below(const uint8_t* f, int nx1, int ny1, int s, int x, int y,
+                                              int z, int lane) {
+  const int n = 1 << s, lw = s - (31 - __builtin_clz((unsigned)sizeof(W)));  // words of a row: 2^lw
+  const int words = n << (s + lw);
+  const uint8_t* p = f + x * n + (int64_t)nx1 * (y * n + (int64_t)ny1 * (z * n));
+  bool any = false;
+  for (int d0 = lane; d0 < words; d0 += 8 * 64) {
+    W w[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int d = min(d0 + 64 * q, words - 1);  // a word of the element again past its end
+      const int dx = d & ((1 << lw) - 1), dy = (d >> lw) & (n - 1), dz = d >> (lw + s);
+      w[q] = *reinterpret_cast<const W*>(p + dx * (int)sizeof(W) + (int64_t)nx1 * (dy + (int64_t)ny1 * dz));
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) any |= any_in(w[q]);
+  }
+  return any;
+}
 __global__ void __launch_bounds__(256) k_flags_deep(LevelTable T) {
   int item = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -83,15 +115,14 @@ __global__ void __launch_bounds__(256) k_flags_deep(LevelTable T) {
   if (l >= T.nlev) return;
   const int nx = T.nx[l], ny = T.ny[l];
   const int x = item % nx, r = item / nx, y = r % ny, z = r / ny;
-  const int s = l - 1, n = 1 << s;  // descendants per axis
-  const int nx1 = T.nx[1], ny1 = T.ny[1];
-  unsigned any = 0;
-  for (int d = lane; d < n * n * n; d += 64) {
-    const int dx = d & (n - 1), dy = (d >> s) & (n - 1), dz = d >> (2 * s);
-    any |= T.eflag[1][x * n + dx + (int64_t)nx1 * (y * n + dy + (int64_t)ny1 * (z * n + dz))];
-  }
-  const bool f = __any(any != 0);
-  if (lane == 0) T.eflag[l][item] = f ? 1 : 0;
+  const int s = l - 1, nx1 = T.nx[1], ny1 = T.ny[1];
+  const uint8_t* f = T.eflag[1];
+  const bool any = s == 1   ? flagged_below<uint16_t>(f, nx1, ny1, s, x, y, z, lane)
+                   : s == 2 ? flagged_below<uint32_t>(f, nx1, ny1, s, x, y, z, lane)
+                   : s == 3 ? flagged_below<uint2>(f, nx1, ny1, s, x, y, z, lane)
+                            : flagged_below<uint4>(f, nx1, ny1, s, x, y, z, lane);
+  const bool flag = __any(any);
+  if (lane == 0) T.eflag[l][item] = flag ? 1 : 0;
 }
 
 // The stored elements and the special nodes of every level, in index order
