@@ -36,6 +36,13 @@ __host__ __device__ constexpr double phi1q(int pos, int A) {
 // node took 6.5 us for the fine product, 5.4 us for a coarse one and 2.8 us
 // each for the sweep and the dot products; 4.0 to 4.8 us (fine) and 3.7 us
 // (coarse) for all of it now.
+//
+// With part a workgroup takes several groups of 64 nodes above kQ4Blocks, since
+// every workgroup of the CG updates reads all the partials (16384 of them: the
+// 1024x1024 solve 5.7 -> 6.4 ms).  Without it there is one group a workgroup: at
+// four workgroups a CU the loads were not hidden (1024x1024 25.6 -> 21.2 us,
+// 2048x2048 91.0 -> 73.3 us, 4096x4096 450 -> 391 us; two groups a workgroup 21.8,
+// 74.6 and 391 us).  A thread per node took 27.1, 83.5 and 372 us.
 constexpr int kQ4Nodes = 64, kQ4Blocks = 1024;
 template <bool FINE, int MODE>
 __global__ void __launch_bounds__(4 * kQ4Nodes) k_q4_product(
@@ -347,11 +354,16 @@ int q4_partials_max(const Grid& g) {
   return (int)std::min<int64_t>((g.nn + kQ4Nodes - 1) / kQ4Nodes, kQ4Blocks);
 }
 
+// Workgroups of a product without partials (a launch holds below 2^32 threads).
+static int q4_blocks(const Grid& g) {
+  return (int)std::min<int64_t>((g.nn + kQ4Nodes - 1) / kQ4Nodes, 1 << 22);
+}
+
 int launch_q4_fine(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
                    const SpringSet& S, int mode, int in, const double* v, double* y,
                    const double* b, const double* dinv, double omega, double* part,
                    hipStream_t s) {
-  const int nb = q4_partials_max(g);
+  const int nb = part ? q4_partials_max(g) : q4_blocks(g);
   auto k = mode == 1   ? k_q4_product<true, 1>
            : mode == 2 ? k_q4_product<true, 2>
                        : k_q4_product<true, 0>;
@@ -364,8 +376,8 @@ void launch_q4_coarse(const Grid& g, const double* Ke, int mode, const double* v
   auto k = mode == 1   ? k_q4_product<false, 1>
            : mode == 2 ? k_q4_product<false, 2>
                        : k_q4_product<false, 0>;
-  k<<<q4_partials_max(g), 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, Ke, nullptr, nullptr, 2, v, y, b, dinv,
-                                                omega, nullptr, SpringSet{});
+  k<<<q4_blocks(g), 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, Ke, nullptr, nullptr, 2, v, y, b, dinv, omega,
+                                          nullptr, SpringSet{});
 }
 
 void launch_q4_energy(const Grid& g, const double* KE, const uint8_t* mask, const double* u,
