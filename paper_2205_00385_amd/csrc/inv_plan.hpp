@@ -72,6 +72,7 @@ struct InvPlan {
   std::vector<InvTask> tasks;
   std::vector<InvStep> steps;  // steps[0] only prepares the first pivots
   int max_pivots = 0;          // most pivots of one step
+  int max_rows = 0;            // most rows of a block
 };
 
 // n rows in planes of m rows each.
@@ -130,6 +131,7 @@ inline InvPlan make_inv_plan(int n, int m) {
     nd.hi = it.right < nu ? row_of(it.right + 1) : n;
     for (int k = nd.r0; k < nd.r1; k += kInvBlock)
       nd.blk.push_back({k, std::min(kInvBlock, nd.r1 - k)});
+    plan.max_rows = std::max(plan.max_rows, std::min(kInvBlock, nd.r1 - nd.r0));
     nd.start = it.end - (int)nd.blk.size();
     first = std::min(first, nd.start);
     if (split) {

@@ -112,7 +112,7 @@ __device__ __forceinline__ void invert4(const double (&D)[4][4], double (&P)[4][
 // the 64 KB a workgroup may hold).
 __device__ __forceinline__ int swz(int p, int i) { return p * 64 + (i ^ ((p & 3) << 3)); }
 
-constexpr int kP = kInvBlock * kInvBlock;  // doubles of one pivot inverse
+constexpr int kP = kInvBlock * kInvBlock;  // doubles of a tile
 
 // Invert the ni x ni block x (each wavefront a strip of 16 rows in four 16x16
 // MFMA tiles, tile element v of lane (lk, li) = row 16 w + lk + 4 v, column
@@ -215,14 +215,14 @@ __device__ __forceinline__ void product(const double* X, const double* Y, int nk
 }
 
 // One step of the plan, one workgroup per task.  It reads the step's pivot
-// inverses Pc (slot q at q * 4096) and panels Cc[q & 1][p][i] = c_i[p] (row
-// stride n) and writes the next step's into Pn and Cn, so no workgroup reads
-// what another writes; every tile of A has one writer.  Entries of a tile that
+// inverses Pc (slot q at q * 64 mr, mr the most rows of a block) and panels
+// Cc[q & 1][p][i] = c_i[p] (mr rows of stride n) and writes the next step's into
+// Pn and Cn, so no workgroup reads what another writes; every tile of A has one writer.  Entries of a tile that
 // lie in a next pivot's row or column are also its panel's.  All products on
 // FP64 MFMA.  The code is kept short (buffer accesses, rolled loops): it runs
 // once per workgroup, and an early version of 77 KB spent its time fetching
 // instructions.
-__global__ void __launch_bounds__(256, 2) k_inv_step(int n, double* __restrict__ A,
+__global__ void __launch_bounds__(256, 2) k_inv_step(int n, int mr, double* __restrict__ A,
                                                      const InvTask* __restrict__ tasks,
                                                      const double* __restrict__ Pc,
                                                      double* __restrict__ Pn,
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(256, 2) k_inv_step(int n, double* __restrict__
   const InvTask t = tasks[blockIdx.x];
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int li = lane & 15, lk = lane >> 4;
-  const int64_t cs = (int64_t)kInvBlock * n;  // panel stride
+  const int64_t cs = (int64_t)mr * n, ps = (int64_t)mr * kInvBlock;  // strides of panels, pivots
   const uint32_t rs = (uint32_t)n * 8;        // row stride in bytes
   const int I0 = t.i0, J0 = t.j0, ni = t.ni, nj = t.nj;
   const bool inverts = t.nrow >= 0 && I0 == J0;
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(256, 2) k_inv_step(int n, double* __restrict__
     return;
   }
   if (t.kind == kInvDiag) {
-    const double* P = Pc + (int64_t)t.p0 * kP;
+    const double* P = Pc + t.p0 * ps;
 #pragma unroll 4
     for (int r = 0; r < 16; ++r) {
       const int p = w + 4 * r;
@@ -284,7 +284,7 @@ __global__ void __launch_bounds__(256, 2) k_inv_step(int n, double* __restrict__
     const int kb = h == 0 ? t.kb0 : t.kb1, k0 = h == 0 ? t.k00 : t.k01;
     const int nk = (kb + 3) / 4;
     const double* C = Cc + (q & 1) * cs;
-    const auto rP = rsrc(Pc + (int64_t)q * kP, kb * kInvBlock * 8);
+    const auto rP = rsrc(Pc + q * ps, kb * kInvBlock * 8);
     const auto rO = rsrc(C + O0, (int64_t)(kb - 1) * rs + 8 * no);
     const auto rJ = rsrc(C + J0, (int64_t)(kb - 1) * rs + 8 * nj);
     // every global load in flight before the first LDS store; zero beyond the blocks
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(256, 2) k_inv_step(int n, double* __restrict__
       if (16 * w + lk + 4 * v >= ni || 16 * jb + li >= ni)
         acc[jb][v] = 16 * w + lk + 4 * v == 16 * jb + li ? 1.0 : 0.0;
   __syncthreads();  // sP and sX are read
-  store_pivot(sm, ni, acc, Pn + (int64_t)t.nrow * kP);
+  store_pivot(sm, ni, acc, Pn + t.nrow * ps);
 }
 
 // After the last step: A = -A on and above the diagonal, mirrored below it.
@@ -402,18 +402,19 @@ void launch_assemble_dense(const Grid& g, const CoarseOrder& o, const double* Ke
 }
 
 int64_t inv_scratch_doubles(const InvPlan& plan) {
-  return 2 * (int64_t)plan.max_pivots * kP + 4 * (int64_t)kInvBlock * plan.n;
+  return (2 * (int64_t)plan.max_pivots * kInvBlock + 4 * (int64_t)plan.n) * plan.max_rows;
 }
 
 void launch_invert(const InvPlan& plan, const InvTask* tasks, double* A, double* scratch, hipStream_t s) {
   // pivot inverses and panels alternate between two buffers each
-  const int64_t ps = (int64_t)plan.max_pivots * kP, cs = 2 * (int64_t)kInvBlock * plan.n;
+  const int64_t ps = (int64_t)plan.max_pivots * plan.max_rows * kInvBlock;
+  const int64_t cs = 2 * (int64_t)plan.max_rows * plan.n;
   double* P[2] = {scratch, scratch + ps};
   double* C[2] = {scratch + 2 * ps, scratch + 2 * ps + cs};
   for (int st = 0; st < (int)plan.steps.size(); ++st) {
     const InvStep& S = plan.steps[st];
     const int b = st & 1;
-    k_inv_step<<<S.ntask, 256, 0, s>>>(plan.n, A, tasks + S.task0, P[b], P[b ^ 1], C[b],
+    k_inv_step<<<S.ntask, 256, 0, s>>>(plan.n, plan.max_rows, A, tasks + S.task0, P[b], P[b ^ 1], C[b],
                                        C[b ^ 1]);
   }
   const unsigned nb = (unsigned)((plan.n + kInvBlock - 1) / kInvBlock);
