@@ -598,6 +598,14 @@ constexpr int kLanes = 32;
 // 18 / 15 against 19 / 17 but level 3 14 / 11 against 9 / 7; 96x48x48 level 1 11
 // to 12 against 8.
 constexpr int kRows = 8;
+// Lanes of an x-row on levels of up to kNarrow elements along x, where 32-lane
+// rows would hold at most 12 nodes: a tile is then one wavefront of eight 8-lane
+// rows, and the four wavefronts of a workgroup take four tiles (or chunks), each
+// for itself.  Thin grids have many planes for few columns: wide tiles left nearly
+// all lanes idle and, with one chunk a workgroup, gave a chunk several layers
+// (16x16x8192 with a single support, levels 1 to 3: 49.2, 21.8 and 15.6 us with
+// wide tiles, 28.1, 12.2 and 8.9 us so; 64x64x64's 8x8x8 level the same either way).
+constexpr int kNarrowLanes = 8, kNarrow = 11;
 
 // Slot of workgroup w of `total` in XCD-contiguous order (see kernels_mg.hip).
 __device__ __forceinline__ int xcd_slot(int w, int total) {
@@ -664,12 +672,13 @@ __device__ __forceinline__ void special_nodes(const LevelArgs& L, const double* 
 // FP32 would cost the softest corner of an element of high contrast more than
 // rounding its matrix entry by entry did).  The first gridDim.x - nmarch
 // workgroups take special nodes instead.  blockIdx.z: load case.
-template <bool LV1, int MODE>
+template <bool LV1, int MODE, int LANES>
 __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
-    LevelArgs L, int gx, int gy, int TZ, int nmarch, WalshConsts K, const double* __restrict__ E,
+    LevelArgs L, int gx, int gy, int ntile, int TZ, int nmarch, WalshConsts K, const double* __restrict__ E,
     const double* __restrict__ v, double* __restrict__ y, const double* __restrict__ jb,
     const double* __restrict__ jd, double omega) {
-  constexpr int kTileX = kLanes - 2, kTileY = kRows - 1;
+  constexpr int kTileX = LANES - 2, kTileY = kRows - 1;
+  constexpr int kSub = kLanes / LANES, kTile = LANES * kRows;  // tiles of a workgroup, their threads
   __shared__ double xs[2 * 3 * kRows * kLanes];  // special nodes: 8 x 3 x 4 kRows of it
   const int nsp = (int)gridDim.x - nmarch;
   if ((int)blockIdx.x < nsp) {
@@ -678,10 +687,12 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
   }
   const int nx = L.nx, ny = L.ny, nz = L.nz;
   const double gam = L.gam;
-  const int tx = threadIdx.x & (kLanes - 1), ty = threadIdx.x / kLanes;
+  const int sub = kSub > 1 ? (int)threadIdx.x / kTile : 0;
+  const int tx = threadIdx.x & (LANES - 1), ty = (int)threadIdx.x % kTile / LANES;
   int bx, by, bz;
   {  // XCD-contiguous tile order
-    const int t = xcd_slot((int)blockIdx.x - nsp, nmarch);
+    const int t = kSub * xcd_slot((int)blockIdx.x - nsp, nmarch) + sub;
+    if (kSub > 1 && t >= ntile) return;  // a whole wavefront: no barrier below waits for it
     bx = t % gx;
     by = (t / gx) % gy;
     bz = t / (gx * gy);
@@ -697,9 +708,9 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
   const auto rsp = make_rsrc(L.special, (uint32_t)nn);
   const auto rE = make_rsrc(E, LV1 ? 8u * ne * TS : 0u);
   const auto rM = make_rsrc(L.mom, LV1 || !L.mom ? 0u : 27u * ne * 8u);
-  const bool col_ok = tx < kLanes - 1 && i >= 0 && i < nx && j >= 0 && j < ny;
+  const bool col_ok = tx < LANES - 1 && i >= 0 && i < nx && j >= 0 && j < ny;
   const bool xi_ok = i >= 0 && i <= nx, yj_ok = j >= 0 && j <= ny, yj1_ok = j + 1 >= 0 && j + 1 <= ny;
-  const bool own = tx >= 1 && tx < kLanes - 1 && ty >= 1 && i <= nx && j <= ny;
+  const bool own = tx >= 1 && tx < LANES - 1 && ty >= 1 && i <= nx && j <= ny;
   const int off00 = i + nxp * j;
 
   double q0[3], q2[3];
@@ -805,7 +816,8 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
     }
     // as in the fine-grid product, with the outputs' scaling by gam per axis
     double X0[3];
-    double (*xb)[kRows][kLanes] = reinterpret_cast<double (*)[kRows][kLanes]>(xs + buf * 3 * kRows * kLanes);
+    double (*xb)[kRows][LANES] =
+        reinterpret_cast<double (*)[kRows][LANES]>(xs + (2 * sub + buf) * 3 * kTile);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       using std::fma;
@@ -822,7 +834,13 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
       X0[c] = u + w;
       xb[c][ty][tx] = u - w;
     }
-    __syncthreads();
+    if constexpr (kSub == 1) {
+      __syncthreads();
+    } else {  // one wavefront writes and reads: its LDS accesses stay in this order
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
     const uint32_t oy = wr && !sp ? on * TS : kOutside;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -839,7 +857,7 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
   }
 }
 
-template <bool LV1, int MODE>
+template <bool LV1, int MODE, int LANES>
 void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, const double* v,
                   double* y, const double* jb, const double* jd, double omega, hipStream_t s) {
   // resident workgroups of this kernel on the device (thread-safe one-time init)
@@ -847,11 +865,12 @@ void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, con
     int dev = 0, cus = 0, per_cu = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_level_z<LV1, MODE>,
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_level_z<LV1, MODE, LANES>,
                                                         kLanes * kRows, 0);
     return (cus > 0 && per_cu > 0) ? cus * per_cu : 256;
   }();
-  const int gx = (L.nx + 1 + kLanes - 3) / (kLanes - 2), gy = (L.ny + 1 + kRows - 2) / (kRows - 1);
+  constexpr int kSub = kLanes / LANES;
+  const int gx = (L.nx + 1 + LANES - 3) / (LANES - 2), gy = (L.ny + 1 + kRows - 2) / (kRows - 1);
   const int planes = L.nz + 1;
   // a chunk of t planes is t + 1 layers, and the launch takes about
   // ceil(workgroups / slots) rounds of them
@@ -859,8 +878,8 @@ void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, con
   int tz = planes;
   int64_t best = -1;
   for_chunk_lengths(planes, 1, [&](int t) {
-    const int64_t chunks = (planes + t - 1) / t;
-    const int64_t cost = (tiles * chunks + slots - 1) / slots * (t + 1);
+    const int64_t groups = (tiles * ((planes + t - 1) / t) + kSub - 1) / kSub;
+    const int64_t cost = (groups + slots - 1) / slots * (t + 1);
     if (best < 0 || cost < best) {
       best = cost;
       tz = t;
@@ -868,10 +887,20 @@ void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, con
   });
   // the coarsest level is special as a whole and has no moments: nothing to march
   const bool whole = !L.count && L.nspecial == (L.nx + 1) * (L.ny + 1) * (L.nz + 1);
-  const int nmarch = whole ? 0 : gx * gy * ((planes + tz - 1) / tz);
+  const int ntile = whole ? 0 : gx * gy * ((planes + tz - 1) / tz);
+  const int nmarch = (ntile + kSub - 1) / kSub;
   const int nsp = (L.nspecial + 4 * kRows - 1) / (4 * kRows);
-  k_level_z<LV1, MODE><<<(unsigned)(nmarch + nsp), kLanes * kRows, 0, s>>>(
-      L, gx, gy, tz, nmarch, K, E, v, y, jb, jd, omega);
+  k_level_z<LV1, MODE, LANES><<<(unsigned)(nmarch + nsp), kLanes * kRows, 0, s>>>(
+      L, gx, gy, ntile, tz, nmarch, K, E, v, y, jb, jd, omega);
+}
+
+template <bool LV1, int MODE>
+void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, const double* v,
+                  double* y, const double* jb, const double* jd, double omega, hipStream_t s) {
+  if (L.nx <= kNarrow)
+    level_launch<LV1, MODE, kNarrowLanes>(L, K, E, v, y, jb, jd, omega, s);
+  else
+    level_launch<LV1, MODE, kLanes>(L, K, E, v, y, jb, jd, omega, s);
 }
 
 }  // namespace
