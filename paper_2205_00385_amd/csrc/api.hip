@@ -133,6 +133,7 @@ struct aarmr_mesh {
   double* Cmd[AARMR_MAX_LEVELS] = {};         // on the device
   LevelTable lt;              // 3D: flags, lists, moments and stored matrices per coarse level
   int nspecial[AARMR_MAX_LEVELS] = {};  // special nodes per level of the current hierarchy
+  bool split[AARMR_MAX_LEVELS] = {};    // levels that store the flagged elements alone
   int nstored1 = 0;                     // stored elements of level 1
   bool counts_ready = false;            // read back since the last hierarchy build
   bool setup_captured = false;          // a graph that holds a hierarchy build may be replayed
@@ -531,8 +532,10 @@ int64_t layout(aarmr_mesh* m, char* base) {
       T.corner[l] = (int*)take(8 * G.nn * 4);
       if (l >= 2 && l < m->nlev - 1) T.mom[l] = (double*)take(27 * G.ne * d8);
     }
+    const Grid& G1 = m->lg[1];
+    if (m->nlev > 2 && level_may_split(G1.nx, G1.ny, G1.nz)) T.Esplit = (double*)take(m->lg[0].ne * d8);
     T.part = (int*)take(level_list_blocks(m->lg, m->nlev) * 4);
-    T.counts = (int*)take(2 * AARMR_MAX_LEVELS * 4);
+    T.counts = (int*)take(kCounts * 4);
   }
   m->E = (double*)take(g.ne * d8);
   m->E_prev = (double*)take(g.ne * d8);
@@ -738,7 +741,10 @@ int level_counts(aarmr_mesh* m, hipStream_t s) {
   if (m->counts_ready) return AARMR_OK;
   HIP_TRY(hipStreamSynchronize(s));
   const int* h = reinterpret_cast<const int*>(m->hpin + 72);
-  for (int l = 1; l < m->nlev; ++l) m->nspecial[l] = h[2 * l + 1];
+  for (int l = 1; l < m->nlev; ++l) {
+    m->nspecial[l] = h[2 * l + 1];
+    m->split[l] = h[kCountSplit + l] != 0;
+  }
   m->nstored1 = h[2];
   m->counts_ready = true;
   return AARMR_OK;
@@ -759,16 +765,21 @@ int level_args(aarmr_mesh* m, int l, hipStream_t s, LevelArgs* out) {
   const LevelTable& T = m->lt;
   const int* count = nullptr;
   int n = T.nn[l];  // the coarsest level is special as a whole
+  bool split = false;
   if (l < m->nlev - 1) {
     if (m->device_counts || capturing(s)) {
       count = T.counts + 2 * l + 1;
     } else {
       TRY(level_counts(m, s));
       n = m->nspecial[l];
+      split = m->split[l];
     }
   }
-  *out = LevelArgs{l,        T.nx[l],      T.ny[l],    T.nz[l],     n,       count, 1.0 / (1 << l),
-                   T.mom[l], T.special[l], T.nlist[l], T.corner[l], T.Kst[l]};
+  const int* gate =
+      count && level_may_split(T.nx[l], T.ny[l], T.nz[l]) ? T.counts + kCountSplit + l : nullptr;
+  *out = LevelArgs{l,      T.nx[l],        T.ny[l],  T.nz[l],  n,            count,      gate,
+                   split,  1.0 / (1 << l), T.mom[l], T.Esplit, T.special[l], T.nlist[l], T.corner[l],
+                   T.Kst[l]};
   return AARMR_OK;
 }
 
@@ -1007,13 +1018,14 @@ int build_mg(aarmr_mesh* m, hipStream_t s) {
   KCHECK();
   // the special-node counts size the products' launches: fetched without a
   // stall, read at the first coarse product
-  HIP_TRY(hipMemcpyAsync(m->hpin + 72, m->lt.counts, 2 * m->nlev * sizeof(int),
+  HIP_TRY(hipMemcpyAsync(m->hpin + 72, m->lt.counts, kCounts * sizeof(int),
                          hipMemcpyDeviceToHost, s));
   m->counts_ready = false;
   m->device_counts = false;  // a solve's products read the counts of its own build
   if (capturing(s)) m->setup_captured = true;
   for (int l = 1; l < m->nlev; ++l) {
-    if (l >= 2 && l < m->nlev - 1) launch_level_moments(m->lg[l], l, m->E, m->lt.mom[l - 1], m->lt.mom[l], s);
+    if (l == 1) launch_level_moduli(m->lt, m->E, s);
+    if (l >= 2 && l < m->nlev - 1) launch_level_moments(m->lt, l, m->E, s);
     launch_level_store(m->lt, l, m->wk, m->E, m->mask, s);
     KCHECK();
     if (m->lv[l].Ke32) {

@@ -132,6 +132,7 @@ __host__ __device__ constexpr int sym_index(int r, int c) {
   return r <= c ? r * 24 - (r * (r - 1)) / 2 + (c - r) : c * 24 - (c * (c - 1)) / 2 + (r - c);
 }
 // The coarse levels' buffers (index 0 unused, null).
+constexpr int kCountSplit = 2 * AARMR_MAX_LEVELS, kCounts = 3 * AARMR_MAX_LEVELS;
 struct LevelTable {
   int nlev = 0;
   int nx[AARMR_MAX_LEVELS] = {}, ny[AARMR_MAX_LEVELS] = {}, nz[AARMR_MAX_LEVELS] = {};
@@ -139,32 +140,39 @@ struct LevelTable {
   uint8_t* eflag[AARMR_MAX_LEVELS] = {};    // [ne] 1: contains a fixed fine DOF
   uint8_t* special[AARMR_MAX_LEVELS] = {};  // [nn] 1: node of a flagged element
   int* eidx[AARMR_MAX_LEVELS] = {};         // [ne] place in the list of stored elements, or -1
-  int* elist[AARMR_MAX_LEVELS] = {};        // [ne] stored elements: those with a special node
+  int* elist[AARMR_MAX_LEVELS] = {};        // [ne] stored elements: those with a special node, or flagged
   int* nlist[AARMR_MAX_LEVELS] = {};        // [nn] special nodes
   int* corner[AARMR_MAX_LEVELS] = {};       // [8][nn] stored elements around the special nodes
   double* mom[AARMR_MAX_LEVELS] = {};       // levels >= 2: [27][ne] moments of the moduli
+  double* Esplit = nullptr;                 // split level 1: the fine moduli, 0 in flagged elements
   double* Kst[AARMR_MAX_LEVELS] = {};       // [300][ne] stored matrices
   int* part = nullptr;                      // level_list_blocks() counts
-  int* counts = nullptr;                    // [2 level]: stored elements, [2 level + 1]: special nodes
+  int* counts = nullptr;                    // [2 level]: stored elements, [2 level + 1]: special nodes,
+                                            // [kCountSplit + level]: 1 if the level is split
 };
-// What one level's product reads; nspecial as read back by the host, or, with
-// count (the number on the device), the most there can be.
+// What one level's product reads; nspecial and split as read back by the host,
+// or, with count (the number on the device), the most nodes there can be and, if
+// the level may be split, gate (on the device: 1 if it is).
 struct LevelArgs {
   int level, nx, ny, nz, nspecial;
-  const int* count;
+  const int *count, *gate;
+  bool split;
   double gam;  // 2^-level
   const double* mom;
+  const double* Esplit;
   const uint8_t* special;
   const int* nlist;
   const int* corner;
   const double* Kst;
 };
+bool level_may_split(int nx, int ny, int nz);
 int64_t level_list_blocks(const Grid* lg, int nlev);
 // Flags, lists and special nodes of every level >= 1 from the fine mask.
 void launch_level_lists(const LevelTable& T, const uint8_t* mask, hipStream_t s);
-// Moments of a level >= 2: from the fine moduli (2) or from the level above.
-void launch_level_moments(const Grid& g, int level, const double* E, const double* child, double* mom,
-                          hipStream_t s);
+// What a product marches on: moments of a level >= 2, from the fine moduli (2) or
+// from the level above; the moduli of a split level 1.  After the lists.
+void launch_level_moments(const LevelTable& T, int level, const double* E, hipStream_t s);
+void launch_level_moduli(const LevelTable& T, const double* E, hipStream_t s);
 // Matrices of the listed elements; level l - 1 done before level l.
 void launch_level_store(const LevelTable& T, int level, const WalshConsts& K, const double* E,
                         const uint8_t* mask, hipStream_t s);

@@ -130,13 +130,27 @@ __global__ void __launch_bounds__(256) k_flags_deep(LevelTable T) {
 // are the elements, then the nodes, of level 1, 2, ..; a block takes 1024 of
 // one segment.  Pass 0 counts a block's hits, pass 1 adds up the counts before
 // it and writes its part of the list.
+//
+// A level is split where kSplitElements elements or more have a special node but
+// no flag: its list then holds the flagged elements alone, the march takes what
+// they would add as 0 (moments, on level 1 moduli) and k_level_add adds it.  Below
+// that the stored rows of all elements around a special node, in the march's own
+// launch, are the faster form (256x128x128 with one clamped face, 4096 such
+// elements: level 1 30 against 35 us); above, supports spread over a grid had ten
+// stored elements to a flagged one (256x128x128 with 0.1% of the nodes fixed: setup
+// 2.93 -> 0.93 ms, level 1 126 -> 60 us, solve 21.2 -> 16.2 ms).  Levels of less
+// than kSplitLevel elements are left as they are, without a second launch.
+// A count of part[] is near elements (low half) and flagged ones.
 constexpr int kChunk = 1024;
+constexpr int kSplitElements = 16384, kSplitLevel = 32768;
 template <int PASS>
 __global__ void __launch_bounds__(256) k_lists(LevelTable T) {
-  __shared__ int sh[256], base_sh;
-  int blk = blockIdx.x, first = 0, l = 1, nodes = 0;
+  __shared__ int sh[256];
+  __shared__ int2 sb[256];
+  int blk = blockIdx.x, first = 0, l = 1, nodes = 0, nb;
   for (;;) {  // the segment of this block (uniform)
-    const int n = nodes ? T.nn[l] : T.ne[l], nb = (n + kChunk - 1) / kChunk;
+    const int n = nodes ? T.nn[l] : T.ne[l];
+    nb = (n + kChunk - 1) / kChunk;
     if (blk < first + nb) break;
     first += nb;
     l += nodes;
@@ -145,8 +159,9 @@ __global__ void __launch_bounds__(256) k_lists(LevelTable T) {
   const int n = nodes ? T.nn[l] : T.ne[l];
   const int nx = T.nx[l], ny = T.ny[l], nz = T.nz[l];
   const bool all = l == T.nlev - 1;  // the coarsest level is stored whole
+  const bool can = !nodes && !all && n >= kSplitLevel;
   const uint8_t* f = T.eflag[l];
-  unsigned hit = 0;
+  unsigned hit = 0, hitf = 0;
   const int i0 = (blk - first) * kChunk + 4 * (int)threadIdx.x;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -156,8 +171,38 @@ __global__ void __launch_bounds__(256) k_lists(LevelTable T) {
     const bool near = all || (nodes ? flagged_near<2>(f, nx, ny, nz, x, y, z)
                                     : flagged_near<3>(f, nx, ny, nz, x, y, z));
     if (near && i0 + q < n) hit |= 1u << q;
+    if (can && f[i] && i0 + q < n) hitf |= 1u << q;
   }
-  int cnt = __popc(hit);
+  int base = 0;
+  bool split = false;
+  if (PASS == 1) {  // near but unflagged elements of the level; both counts of the blocks before
+    int saved = 0;
+    int2 s = {0, 0};
+    for (int b = first + (int)threadIdx.x; b < (can ? first + nb : blk); b += 256) {
+      const int p = T.part[b];
+      saved += (p & 0xFFFF) - (p >> 16);
+      if (b < blk) {
+        s.x += p & 0xFFFF;
+        s.y += p >> 16;
+      }
+    }
+    sh[threadIdx.x] = saved;
+    sb[threadIdx.x] = s;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+      if ((int)threadIdx.x < off) {
+        sh[threadIdx.x] += sh[threadIdx.x + off];
+        sb[threadIdx.x].x += sb[threadIdx.x + off].x;
+        sb[threadIdx.x].y += sb[threadIdx.x + off].y;
+      }
+      __syncthreads();
+    }
+    split = can && sh[0] >= kSplitElements;
+    base = split ? sb[0].y : sb[0].x;
+    if (split) hit = hitf;
+    __syncthreads();
+  }
+  const int cnt = __popc(hit) | (PASS == 0 ? __popc(hitf) << 16 : 0);
   sh[threadIdx.x] = cnt;
   __syncthreads();
   for (int off = 1; off < 256; off <<= 1) {  // inclusive scan
@@ -170,19 +215,7 @@ __global__ void __launch_bounds__(256) k_lists(LevelTable T) {
     if (threadIdx.x == 255) T.part[blk] = sh[255];
     return;
   }
-  const int before = sh[threadIdx.x] - cnt, total = sh[255];
-  __syncthreads();
-  int s = 0;
-  for (int b = first + (int)threadIdx.x; b < blk; b += 256) s += T.part[b];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) base_sh = sh[0];
-  __syncthreads();
-  int w = base_sh + before;
+  int w = base + sh[threadIdx.x] - cnt;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int i = i0 + q;
@@ -196,7 +229,10 @@ __global__ void __launch_bounds__(256) k_lists(LevelTable T) {
       if (h) T.elist[l][w++] = i;
     }
   }
-  if (threadIdx.x == 0 && i0 + kChunk >= n) T.counts[2 * l + nodes] = base_sh + total;
+  if (threadIdx.x == 0 && i0 + kChunk >= n) {
+    T.counts[2 * l + nodes] = base + sh[255];
+    if (!nodes) T.counts[kCountSplit + l] = split ? 1 : 0;
+  }
 }
 
 // The place among the stored elements of the element that has a special node
@@ -219,6 +255,7 @@ __global__ void __launch_bounds__(256) k_corners(LevelTable T) {
 // Level 2 from the 64 fine moduli, axis by axis; descendant position p along
 // an axis has tau = 3 - 2 p.
 __global__ void __launch_bounds__(64) k_moments2(int nx, int ny, int nz, const double* __restrict__ E,
+                                                 const uint8_t* __restrict__ zero,
                                                  double* __restrict__ mom) {
   const int ne = nx * ny * nz;
   const int e = blockIdx.x * 64 + threadIdx.x;
@@ -261,8 +298,23 @@ __global__ void __launch_bounds__(64) k_moments2(int nx, int ny, int nz, const d
         m[a + 3 * b + 18] = fma(tz * tz, yz[a][b], m[a + 3 * b + 18]);
       }
   }
+  const bool none = zero && zero[e];  // a flagged element of a level that may be split
 #pragma unroll
-  for (int a = 0; a < 27; ++a) mom[(int64_t)a * ne + e] = m[a];
+  for (int a = 0; a < 27; ++a) mom[(int64_t)a * ne + e] = none ? 0.0 : m[a];
+}
+
+// The fine moduli with those of flagged level-1 elements 0, for a split level 1.
+__global__ void __launch_bounds__(256) k_split_moduli(int nx, int ny, int64_t ne,
+                                                      const double* __restrict__ E,
+                                                      const uint8_t* __restrict__ eflag,
+                                                      const int* __restrict__ split,
+                                                      double* __restrict__ Es) {
+  if (!*split) return;
+  const uint32_t e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= ne) return;
+  const uint32_t r = e / (2 * nx), x = e - r * (2 * nx), z = r / (2 * ny), y = r - z * (2 * ny);
+  const double v = E[e];
+  Es[e] = eflag[(x >> 1) + nx * ((y >> 1) + ny * (z >> 1))] ? 0.0 : v;
 }
 
 // Level l >= 3 from level l - 1, eight lanes per element, one per child: the
@@ -270,6 +322,7 @@ __global__ void __launch_bounds__(64) k_moments2(int nx, int ny, int nz, const d
 // over the children in a fixed order.
 __global__ void __launch_bounds__(256) k_moments_up(int nx, int ny, int nz, double shift,
                                                     const double* __restrict__ child,
+                                                    const uint8_t* __restrict__ zero,
                                                     double* __restrict__ mom) {
   const int ne = nx * ny * nz;
   const int t = blockIdx.x * 256 + threadIdx.x, e = t >> 3, c = t & 7;
@@ -302,13 +355,14 @@ __global__ void __launch_bounds__(256) k_moments_up(int nx, int ny, int nz, doub
       m[2][a][b] = fma(sz * sz, m[0][a][b], fma(2.0 * sz, m[1][a][b], m[2][a][b]));
       m[1][a][b] = fma(sz, m[0][a][b], m[1][a][b]);
     }
+  const bool none = live && zero && zero[e];  // as on level 2 (a parent of it is flagged too)
 #pragma unroll
   for (int a = 0; a < 27; ++a) {
     double s = m[a / 9][(a / 3) % 3][a % 3];
     s += __shfl_xor(s, 1, 64);
     s += __shfl_xor(s, 2, 64);
     s += __shfl_xor(s, 4, 64);
-    if (live && c == (a & 7)) mom[(int64_t)a * ne + e] = s;
+    if (live && c == (a & 7)) mom[(int64_t)a * ne + e] = none ? 0.0 : s;
   }
 }
 
@@ -619,7 +673,7 @@ __device__ __forceinline__ int xcd_slot(int w, int total) {
 // One corner a thread keeps the chain short (node and matrix index, then all
 // operands at once, 72 matrix entries in flight): it sets the time of the small
 // levels' launches.
-template <int MODE, int NODES>
+template <int MODE, int NODES, bool ADD>
 __device__ __forceinline__ void special_nodes(const LevelArgs& L, const double* v, double* y,
                                               const double* jb, const double* jd, double omega,
                                               int blk, double* lds) {
@@ -658,8 +712,21 @@ __device__ __forceinline__ void special_nodes(const LevelArgs& L, const double* 
 #pragma unroll
     for (int t = 1; t < 8; ++t) sum += red[t][q][lane];
     const int d = q * nn + n;
-    y[d] = MODE == 0 ? sum : MODE == 1 ? v[d] + omega * jd[d] * (jb[d] - sum) : jb[d] - sum;
+    if (ADD)
+      y[d] = MODE == 0 ? y[d] + sum : MODE == 1 ? fma(-omega * jd[d], sum, y[d]) : y[d] - sum;
+    else
+      y[d] = MODE == 0 ? sum : MODE == 1 ? v[d] + omega * jd[d] * (jb[d] - sum) : jb[d] - sum;
   }
+}
+
+// On a split level: what the flagged elements add to the marched product.
+template <int MODE>
+__global__ void __launch_bounds__(256) k_level_add(LevelArgs L, const double* __restrict__ v,
+                                                   double* __restrict__ y,
+                                                   const double* __restrict__ jd, double omega) {
+  __shared__ double red[8 * 3 * 32];
+  if (L.gate && !*L.gate) return;
+  special_nodes<MODE, 32, true>(L, v, y, nullptr, jd, omega, (int)blockIdx.x, red);
 }
 
 // y = A_l v (MODE 0), v + omega jd (jb - A_l v) (MODE 1, a damped-Jacobi sweep)
@@ -672,7 +739,7 @@ __device__ __forceinline__ void special_nodes(const LevelArgs& L, const double* 
 // FP32 would cost the softest corner of an element of high contrast more than
 // rounding its matrix entry by entry did).  The first gridDim.x - nmarch
 // workgroups take special nodes instead.  blockIdx.z: load case.
-template <bool LV1, int MODE, int LANES>
+template <bool LV1, int MODE, int LANES, bool SPLIT>
 __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
     LevelArgs L, int gx, int gy, int ntile, int TZ, int nmarch, WalshConsts K, const double* __restrict__ E,
     const double* __restrict__ v, double* __restrict__ y, const double* __restrict__ jb,
@@ -680,9 +747,10 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
   constexpr int kTileX = LANES - 2, kTileY = kRows - 1;
   constexpr int kSub = kLanes / LANES, kTile = LANES * kRows;  // tiles of a workgroup, their threads
   __shared__ double xs[2 * 3 * kRows * kLanes];  // special nodes: 8 x 3 x 4 kRows of it
-  const int nsp = (int)gridDim.x - nmarch;
-  if ((int)blockIdx.x < nsp) {
-    special_nodes<MODE, 4 * kRows>(L, v, y, jb, jd, omega, (int)blockIdx.x, xs);
+  if (L.gate && (*L.gate != 0) != SPLIT) return;  // the form that the device chose
+  const int nsp = SPLIT ? 0 : (int)gridDim.x - nmarch;
+  if (!SPLIT && (int)blockIdx.x < nsp) {
+    special_nodes<MODE, 4 * kRows, false>(L, v, y, jb, jd, omega, (int)blockIdx.x, xs);
     return;
   }
   const int nx = L.nx, ny = L.ny, nz = L.nz;
@@ -778,7 +846,7 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
     // plane k's own values; the first layer of a chunk only primes the carry
     const bool wr = own && k >= kz0;
     const uint32_t on = wr ? (uint32_t)(k * plane + off00) : kOutside;
-    const uint32_t sp = __builtin_amdgcn_raw_buffer_load_b8(rsp, (int)on, 0, 0);
+    const uint32_t sp = SPLIT ? 0 : __builtin_amdgcn_raw_buffer_load_b8(rsp, (int)on, 0, 0);
     double ob[3], od[3];
     if (MODE != 0) {
 #pragma unroll
@@ -857,15 +925,15 @@ __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
   }
 }
 
-template <bool LV1, int MODE, int LANES>
-void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, const double* v,
-                  double* y, const double* jb, const double* jd, double omega, hipStream_t s) {
+template <bool LV1, int MODE, int LANES, bool SPLIT>
+void level_march(const LevelArgs& L, const WalshConsts& K, const double* E, const double* v, double* y,
+                 const double* jb, const double* jd, double omega, hipStream_t s) {
   // resident workgroups of this kernel on the device (thread-safe one-time init)
   static const int slots = [] {
     int dev = 0, cus = 0, per_cu = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_level_z<LV1, MODE, LANES>,
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_level_z<LV1, MODE, LANES, SPLIT>,
                                                         kLanes * kRows, 0);
     return (cus > 0 && per_cu > 0) ? cus * per_cu : 256;
   }();
@@ -886,24 +954,36 @@ void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, con
     }
   });
   // the coarsest level is special as a whole and has no moments: nothing to march
-  const bool whole = !L.count && L.nspecial == (L.nx + 1) * (L.ny + 1) * (L.nz + 1);
+  const bool whole = !SPLIT && !L.count && L.nspecial == (L.nx + 1) * (L.ny + 1) * (L.nz + 1);
   const int ntile = whole ? 0 : gx * gy * ((planes + tz - 1) / tz);
   const int nmarch = (ntile + kSub - 1) / kSub;
   const int nsp = (L.nspecial + 4 * kRows - 1) / (4 * kRows);
-  k_level_z<LV1, MODE, LANES><<<(unsigned)(nmarch + nsp), kLanes * kRows, 0, s>>>(
+  k_level_z<LV1, MODE, LANES, SPLIT><<<(unsigned)(nmarch + (SPLIT ? 0 : nsp)), kLanes * kRows, 0, s>>>(
       L, gx, gy, ntile, tz, nmarch, K, E, v, y, jb, jd, omega);
+  if (SPLIT && nsp > 0) k_level_add<MODE><<<(unsigned)nsp, 256, 0, s>>>(L, v, y, jd, omega);
+}
+
+template <bool LV1, int MODE, int LANES>
+void level_form(const LevelArgs& L, const WalshConsts& K, const double* E, const double* v, double* y,
+                const double* jb, const double* jd, double omega, hipStream_t s) {
+  // both forms where only the device knows which one the lists are for
+  if (L.gate || !L.split) level_march<LV1, MODE, LANES, false>(L, K, E, v, y, jb, jd, omega, s);
+  if (L.gate || L.split)
+    level_march<LV1, MODE, LANES, true>(L, K, LV1 ? L.Esplit : E, v, y, jb, jd, omega, s);
 }
 
 template <bool LV1, int MODE>
 void level_launch(const LevelArgs& L, const WalshConsts& K, const double* E, const double* v,
                   double* y, const double* jb, const double* jd, double omega, hipStream_t s) {
   if (L.nx <= kNarrow)
-    level_launch<LV1, MODE, kNarrowLanes>(L, K, E, v, y, jb, jd, omega, s);
+    level_form<LV1, MODE, kNarrowLanes>(L, K, E, v, y, jb, jd, omega, s);
   else
-    level_launch<LV1, MODE, kLanes>(L, K, E, v, y, jb, jd, omega, s);
+    level_form<LV1, MODE, kLanes>(L, K, E, v, y, jb, jd, omega, s);
 }
 
 }  // namespace
+
+bool level_may_split(int nx, int ny, int nz) { return (int64_t)nx * ny * nz >= kSplitLevel; }
 
 int64_t level_list_blocks(const Grid* lg, int nlev) {
   int64_t nb = 0;
@@ -926,13 +1006,21 @@ void launch_level_lists(const LevelTable& T, const uint8_t* mask, hipStream_t s)
   k_corners<<<nblk(8 * nodes, 256), 256, 0, s>>>(T);
 }
 
-void launch_level_moments(const Grid& g, int level, const double* E, const double* child, double* mom,
-                          hipStream_t s) {
+void launch_level_moments(const LevelTable& T, int level, const double* E, hipStream_t s) {
+  const int nx = T.nx[level], ny = T.ny[level], nz = T.nz[level], ne = T.ne[level];
+  const uint8_t* zero = level_may_split(nx, ny, nz) ? T.eflag[level] : nullptr;
   if (level == 2)
-    k_moments2<<<nblk(g.ne, 64), 64, 0, s>>>(g.nx, g.ny, g.nz, E, mom);
+    k_moments2<<<nblk(ne, 64), 64, 0, s>>>(nx, ny, nz, E, zero, T.mom[2]);
   else
-    k_moments_up<<<nblk(8 * g.ne, 256), 256, 0, s>>>(g.nx, g.ny, g.nz, (double)(1 << (level - 1)),
-                                                     child, mom);
+    k_moments_up<<<nblk(8 * (int64_t)ne, 256), 256, 0, s>>>(nx, ny, nz, (double)(1 << (level - 1)),
+                                                            T.mom[level - 1], zero, T.mom[level]);
+}
+
+void launch_level_moduli(const LevelTable& T, const double* E, hipStream_t s) {
+  if (!T.Esplit) return;
+  const int64_t ne = 8 * (int64_t)T.ne[1];
+  k_split_moduli<<<nblk(ne, 256), 256, 0, s>>>(T.nx[1], T.ny[1], ne, E, T.eflag[1],
+                                               T.counts + kCountSplit + 1, T.Esplit);
 }
 
 void launch_level_store(const LevelTable& T, int level, const WalshConsts& K, const double* E,
