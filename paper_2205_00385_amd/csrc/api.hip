@@ -824,8 +824,8 @@ int level_product32(aarmr_mesh* m, int l, int mode, const float* v, float* y, co
 int fine_product(aarmr_mesh* m, const double* E, const double* v, double* y, hipStream_t s,
                  bool with_springs = true) {
   if (m->dim == 2) {
-    launch_q4_fine(m->lg[0], m->KEd, E, m->mask, with_springs ? m->springs : SpringSet{}, 0, 2, v,
-                   y, nullptr, nullptr, 0.0, nullptr, s);
+    launch_q4_fine(m->lg[0], m->KEd, E, m->mask, with_springs ? m->springs : SpringSet{}, 0, false,
+                   v, y, nullptr, nullptr, 0.0, nullptr, s);
   } else
     launch_ebe(m->lg[0], m->wk, E, m->mask, v, y, false, s);
   ++m->sweeps;
@@ -836,7 +836,7 @@ int fine_product(aarmr_mesh* m, const double* E, const double* v, double* y, hip
 int apply(aarmr_mesh* m, int l, const double* v, double* y, hipStream_t s,
           bool any_input = false) {
   if (l == 0 && m->dim == 2) {
-    launch_q4_fine(m->lg[0], m->KEd, m->E, m->mask, m->springs, 0, any_input ? 0 : 2, v, y, nullptr,
+    launch_q4_fine(m->lg[0], m->KEd, m->E, m->mask, m->springs, 0, any_input, v, y, nullptr,
                    nullptr, 0.0, nullptr, s);
     ++m->sweeps;
     KCHECK();
@@ -893,8 +893,8 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
     if (l >= 1) {
       TRY(level_product(m, l, 2, x, L.t, b, s));
     } else if (plane) {
-      launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 2, 2, x, L.t, b, nullptr, 0.0, nullptr,
-                     s);
+      launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 2, false, x, L.t, b, nullptr, 0.0,
+                     nullptr, s);
       ++m->sweeps;
     } else
       TRY(apply(m, l, x, L.t, s));
@@ -918,8 +918,8 @@ int vcycle(aarmr_mesh* m, int l, const double* b, double* x, hipStream_t s,
       if (x != m->z) return fail(AARMR_E_STATE, "V-cycle iterate is not the solver's z");
       double* y = dest ? dest : m->t0;
       if (plane) {
-        const int nb = launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 1, 2, x, y, b, L.dinv,
-                                      om, m->want_rz ? m->part_rz : nullptr, s);
+        const int nb = launch_q4_fine(G, m->KEd, m->E, m->mask, m->springs, 1, false, x, y, b,
+                                      L.dinv, om, m->want_rz ? m->part_rz : nullptr, s);
         if (m->want_rz) m->rz_nb = nb;
       } else if (m->want_rz)
         m->rz_nb = launch_ebe_jacobi_dot(G, m->wk, m->E, m->mask, x, b, L.dinv, om, y, m->part_rz,
@@ -1675,8 +1675,8 @@ int pcg64(aarmr_mesh* m, double* x, int* iters, double* relres, int maxit_in, hi
     // sweep (workgroup partials of those kernels)
     for (int it = 0; it < maxit; ++it) {
       const int n_pq =
-          m->dim == 2 ? launch_q4_fine(g, m->KEd, m->E, m->mask, m->springs, 0, 2, m->pv, m->q,
-                                       nullptr, nullptr, 0.0, m->part_pq, s)
+          m->dim == 2 ? launch_q4_fine(g, m->KEd, m->E, m->mask, m->springs, 0, false, m->pv,
+                                       m->q, nullptr, nullptr, 0.0, m->part_pq, s)
                       : launch_ebe_dot(g, m->wk, m->E, m->mask, m->pv, m->q, m->part_pq, s, m->tz64);
       ++m->sweeps;
       KCHECK();

@@ -331,13 +331,13 @@ struct SpringSet {
   double k[AARMR_MAX_SPRINGS];
 };
 // Product of the fine operator.  mode 0: y = A v; 1: y = v + omega dinv (b -
-// A v), y distinct from v; 2: y = b - A v.  in: 0 any input, identity rows on
-// fixed DOFs; 1 any input, zero rows; 2 an input that is zero there.  part
-// (or null): partials of v . y (mode 0) or b . y (mode 1), at most
-// q4_partials_max(g); the return value is their number.
+// A v), y distinct from v; 2: y = b - A v.  any_input: any v, identity rows on
+// fixed DOFs; otherwise v is zero there.  part (or null): partials of v . y
+// (mode 0) or b . y (mode 1), at most q4_partials_max(g); the return value is
+// the number of workgroups.
 int q4_partials_max(const Grid& g);
 int launch_q4_fine(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
-                   const SpringSet& S, int mode, int in, const double* v, double* y,
+                   const SpringSet& S, int mode, bool any_input, const double* v, double* y,
                    const double* b, const double* dinv, double omega, double* part,
                    hipStream_t s);
 // The same modes for a coarse level's element matrices.

@@ -23,8 +23,8 @@ __host__ __device__ constexpr double phi1q(int pos, int A) {
 // Product of the fine operator (FINE: moduli E, masks, springs) or of a coarse
 // level's packed element matrices Ke.  MODE 0: y = A v; 1: a damped-Jacobi
 // sweep, y = v + omega dinv (b - A v), y distinct from v; 2: the residual
-// y = b - A v.  On fixed DOFs A v is v with identity rows (in = 0), else 0; in:
-// 0 any input with identity rows, 1 any input, 2 an input that is zero there.
+// y = b - A v.  any_input: any v, A v = v on fixed DOFs; otherwise v is zero
+// there, and so is A v.
 // With part non-null each workgroup also writes part[blockIdx.x], its sum of
 // v . y (MODE 0) or b . y (MODE 1): the partials of CG's dot products.
 //
@@ -47,7 +47,7 @@ constexpr int kQ4Nodes = 64, kQ4Blocks = 1024;
 template <bool FINE, int MODE>
 __global__ void __launch_bounds__(4 * kQ4Nodes) k_q4_product(
     int nx, int ny, const double* __restrict__ Kmat, const double* __restrict__ E,
-    const uint8_t* __restrict__ mask, int in, const double* __restrict__ v,
+    const uint8_t* __restrict__ mask, bool any_input, const double* __restrict__ v,
     double* __restrict__ y, const double* __restrict__ b, const double* __restrict__ dinv,
     double omega, double* __restrict__ part, SpringSet S) {
   __shared__ double sums[4][2][kQ4Nodes], dots[2];
@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(4 * kQ4Nodes) k_q4_product(
       const uint32_t nb = cx + (c & 1) + nxp * (cy + (c >> 1));
       ve[2 * c] = v[nb];
       ve[2 * c + 1] = v[(int64_t)nn + nb];
-      if (FINE && in != 2) me[c] = mask[nb];
+      if (FINE && any_input) me[c] = mask[nb];
     }
     const double w = FINE ? E[e] : 1.0;
 #pragma unroll
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(4 * kQ4Nodes) k_q4_product(
       if (FINE) {
         for (int t = 0; t < S.n; ++t)
           if (S.dof[t] == d) Av = fma(S.k[t], vn, Av);
-        if ((mn >> a) & 1u) Av = in == 0 ? vn : 0.0;
+        if ((mn >> a) & 1u) Av = any_input ? vn : 0.0;
       }
       const double out = MODE == 0 ? Av : MODE == 1 ? fma(omega * dn, bn - Av, vn) : bn - Av;
       y[d] = out;
@@ -360,14 +360,14 @@ static int q4_blocks(const Grid& g) {
 }
 
 int launch_q4_fine(const Grid& g, const double* KE, const double* E, const uint8_t* mask,
-                   const SpringSet& S, int mode, int in, const double* v, double* y,
+                   const SpringSet& S, int mode, bool any_input, const double* v, double* y,
                    const double* b, const double* dinv, double omega, double* part,
                    hipStream_t s) {
   const int nb = part ? q4_partials_max(g) : q4_blocks(g);
   auto k = mode == 1   ? k_q4_product<true, 1>
            : mode == 2 ? k_q4_product<true, 2>
                        : k_q4_product<true, 0>;
-  k<<<nb, 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, KE, E, mask, in, v, y, b, dinv, omega, part, S);
+  k<<<nb, 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, KE, E, mask, any_input, v, y, b, dinv, omega, part, S);
   return nb;
 }
 
@@ -376,7 +376,7 @@ void launch_q4_coarse(const Grid& g, const double* Ke, int mode, const double* v
   auto k = mode == 1   ? k_q4_product<false, 1>
            : mode == 2 ? k_q4_product<false, 2>
                        : k_q4_product<false, 0>;
-  k<<<q4_blocks(g), 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, Ke, nullptr, nullptr, 2, v, y, b, dinv, omega,
+  k<<<q4_blocks(g), 4 * kQ4Nodes, 0, s>>>(g.nx, g.ny, Ke, nullptr, nullptr, false, v, y, b, dinv, omega,
                                           nullptr, SpringSet{});
 }
 
