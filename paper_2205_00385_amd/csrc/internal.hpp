@@ -227,8 +227,7 @@ int64_t inv_scratch_doubles(const InvPlan& plan);
 void launch_invert(const InvPlan& plan, const InvTask* tasks, double* A, double* scratch,
                    hipStream_t s);
 void launch_gemv(int n, const double* A, const double* x, double* y, hipStream_t s);
-// FP32 V-cycle pieces (vectors FP32; moments, stored matrices and the coarsest
-// inverse stay FP64 and are applied with FP32 vectors).
+// FP32 V-cycle pieces (FP32 vectors; the coarsest inverse alone is read in FP64).
 void launch_restrict_f32(const Grid& coarse, const float* bf, const float* tf,
                          const uint8_t* mask, float* bc, hipStream_t s, int nr = 1,
                          const CoarseOrder* o = nullptr);

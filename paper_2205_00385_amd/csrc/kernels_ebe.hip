@@ -428,8 +428,8 @@ __global__ void __launch_bounds__(256) k_energy_walsh(int nx, int ny, int nz, Wa
 // two workgroups per compute unit, sixteen above.  FP64 product (CG's, with
 // its dot product), against sixteen rows and at least 4 planes a chunk:
 // 24x12x12 8.9 -> 5.9 us (8 rows, 2 planes), 40x32x40 9.7 -> 6.4 us, 96x48x48
-// 10.2 -> 8.9 us (8 rows, 3 planes); at 96x64x64 (16 rows, 6 planes) 13.1 us
-// against 12.9 us, at 256x128x128 66.7 us against 76 us with 8 rows.  FP32:
+// 10.2 -> 8.9 us (8 rows, 3 planes); 96x64x64 keeps the sixteen rows and 6 planes
+// it had; 256x128x128 66.7 us against 76 us with 8 rows.  FP32:
 // 40x32x40 8.3 -> 6.9 us, 96x64x64 11.8 -> 10.1 us; there a chunk keeps at
 // least 4 planes (2 would take 5.6 us), because lock-step load cases and
 // concurrent solves pay for the extra layers: 16 batched solves of 16..64

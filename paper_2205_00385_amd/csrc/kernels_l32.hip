@@ -1,13 +1,12 @@
 // FP32 products of the coarse levels, for the refinement form's V-cycle.
 //
-// They are kept apart from the moment form (kernels_level.hip) because their
-// rounding is part of the refinement form's results: an inner FP32 solve stops
-// at a residual of a few 1e-6, and another rounding of any of its products moves
-// the returned displacement by some 1e-10, by 1e-9 where an inner iteration more
-// or less is taken.  In time they are on a par below 2e5 level-1 elements (two
-// launches of 4.5 and 5.5 us a product against one of 6; below level 1 one launch
-// either way); above, the moment form would take 33 against 48 us on level 1 of
-// 256x128x128.
+// They are not in the moment form (kernels_level.hip), though it is the faster
+// one: 6 us against two launches of 4.5 and 5.5 us for a level-1 product of
+// 56x40x64, 33 against 48 us on level 1 of 256x128x128; a refinement solve of
+// 256x128x128 took 13.9 ms with it when it took 15.4 ms with these.  Another
+// rounding of any FP32 product moves the returned displacement by some 1e-10, by
+// 1e-9 where an inner iteration more or less is taken: within cg_rtol, but no
+// longer the values that were checked, so that change is a step of its own.
 #include "internal.hpp"
 
 namespace aarmr {

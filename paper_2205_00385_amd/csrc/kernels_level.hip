@@ -6,8 +6,9 @@
 // on the levels below.  An element that does ("flagged") has the masked
 // operator (Df P)^T K (Df P), which is stored as a packed 24x24 matrix.  Nodes
 // of flagged elements ("special" nodes) are computed from stored matrices
-// alone, so the elements around them are stored too.  On the coarsest level
-// every element is stored: its matrices are assembled into the dense operator.
+// alone, so the elements around them are stored too, unless the level is split
+// (k_lists).  On the coarsest level every element is stored: its matrices are
+// assembled into the dense operator.
 //
 // A level-1 product used to write its element products to a [24][ne] buffer and
 // gather them in a second launch, and a product below read the 300 stored entries
@@ -734,11 +735,9 @@ __global__ void __launch_bounds__(256) k_level_add(LevelArgs L, const double* __
 // The tiles, the march along z, the exchanges between neighbouring columns and
 // the out-of-range rule are those of the fine-grid product (k_ebe_z); the
 // element operator is moment_apply with the 8 child moduli (LV1) or 27 stored
-// moments.  Vectors of type T, arithmetic in C (the refinement form applies
-// levels >= 2 in FP64: a moment carries the whole element, so rounding it to
-// FP32 would cost the softest corner of an element of high contrast more than
-// rounding its matrix entry by entry did).  The first gridDim.x - nmarch
-// workgroups take special nodes instead.  blockIdx.z: load case.
+// moments.  FP64, one load case (the refinement form's FP32 products:
+// kernels_l32.hip).  The first gridDim.x - nmarch workgroups take special nodes
+// instead; SPLIT: there are none, and every node is marched.
 template <bool LV1, int MODE, int LANES, bool SPLIT>
 __global__ void __launch_bounds__(kLanes * kRows, 2) k_level_z(
     LevelArgs L, int gx, int gy, int ntile, int TZ, int nmarch, WalshConsts K, const double* __restrict__ E,
